@@ -735,52 +735,61 @@ void attn_fwd_kernel(AttnArgs a) {
 
 // Split-K merge (Section 4.3, Fig. 5): rescale the partial states of one
 // physical query row to their common maximum, sum, normalise, store bf16.
+// Bound by the latency of reading S partial states, so the work is cut small:
+// one workgroup merges 8 query rows of one physical row, 32 lanes of 4
+// head-dim columns each (512-byte row reads), with the loads of all its
+// partial states in flight together.  Against one workgroup per physical row
+// whose threads walked 32 columns and the states one after the other, the
+// whole forward pass of a 16384-token, 12-head, 15% top-k request with S = 8
+// went from 2.53 to 0.78 ms, of 104 rows of 314 tiles from 0.134 to 0.085 ms.
+constexpr int kMaxSplit = 8;   // largest Split-K factor of the catalog
+constexpr int kMergeRows = 8;
+
 template <int TQ>
-__global__ __launch_bounds__(256) void splitk_merge_kernel(AttnArgs a) {
-  const int64_t nt = a.ntasks_dev ? *a.ntasks_dev : a.ntasks;
-  const int64_t ti = blockIdx.x;
-  if (ti >= nt) return;
+__global__ __launch_bounds__(32 * kMergeRows) void splitk_merge_kernel(AttnArgs a) {
+  constexpr int kParts = TQ / kMergeRows;
+  const int64_t ti = a.row_task[blockIdx.x / kParts];
   const Task task = a.tasks[ti];
-  if (task.nsplit <= 1 || task.split != 0) return;
+  if (task.nsplit <= 1) return;
+  const int ql = (int)(blockIdx.x % kParts) * kMergeRows + (threadIdx.x >> 5);
+  const int col = (threadIdx.x & 31) * 4;
+  const int qrow = task.pq * TQ + ql;
+  if (qrow >= a.Nq) return;
   const int b = task.bh / a.H, h = task.bh - b * a.H;
   const int64_t slot_elems = (int64_t)TQ * (kD + 2);
   const float* base = a.ws + ti * slot_elems;
-  // 256 threads: each handles one query row and 32 head-dim columns per step
-  for (int idx = threadIdx.x; idx < TQ * 4; idx += blockDim.x) {
-    const int ql = idx >> 2, part = idx & 3;
-    const int qrow = task.pq * TQ + ql;
-    if (qrow >= a.Nq) continue;
-    float mstar = kNegInf;
-    for (int s = 0; s < task.nsplit; ++s) mstar = fmaxf(mstar, base[s * slot_elems + ql]);
-    float acc[32];
+  float m[kMaxSplit], l[kMaxSplit];
+  f32x4 part[kMaxSplit];
+  float mstar = kNegInf;
 #pragma unroll
-    for (int e = 0; e < 32; ++e) acc[e] = 0.f;
-    float L = 0.f;
-    if (mstar != kNegInf) {
-      for (int s = 0; s < task.nsplit; ++s) {
-        const float* sl = base + s * slot_elems;
-        const float ms = sl[ql];
-        if (ms == kNegInf) continue;
-        const float wgt = fast_exp2(ms - mstar);
-        L += wgt * sl[TQ + ql];
-        const float* os = sl + 2 * TQ + (int64_t)ql * kD + part * 32;
-#pragma unroll
-        for (int e = 0; e < 32; ++e) acc[e] += wgt * os[e];
-      }
-    }
-    const float inv = L > 0.f ? 1.f / L : 0.f;
-    uint16_t* op = a.o + b * a.os0 + h * a.os1 + (int64_t)qrow * a.os2 + part * 32;
-#pragma unroll
-    for (int e = 0; e < 32; e += 4) {
-      bf16x4 v4;
-#pragma unroll
-      for (int u = 0; u < 4; ++u) v4[u] = (__bf16)(acc[e + u] * inv);
-      *reinterpret_cast<bf16x4*>(op + e) = v4;
-    }
-    if (a.lse && part == 0)
-      a.lse[((int64_t)b * a.H + h) * a.Nq + qrow] =
-          L > 0.f ? (mstar + __log2f(L)) * 0.69314718055994530942f : kNegInf;
+  for (int s = 0; s < kMaxSplit; ++s) {
+    m[s] = kNegInf;
+    if (s >= task.nsplit) continue;
+    const float* sl = base + s * slot_elems;
+    m[s] = sl[ql];
+    l[s] = sl[TQ + ql];
+    part[s] = *reinterpret_cast<const f32x4*>(sl + 2 * TQ + (int64_t)ql * kD + col);
   }
+#pragma unroll
+  for (int s = 0; s < kMaxSplit; ++s) mstar = fmaxf(mstar, m[s]);
+  f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+  float L = 0.f;
+#pragma unroll
+  for (int s = 0; s < kMaxSplit; ++s) {
+    if (m[s] == kNegInf) continue;
+    const float wgt = fast_exp2(m[s] - mstar);
+    L += wgt * l[s];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) acc[e] += wgt * part[s][e];
+  }
+  const float inv = L > 0.f ? 1.f / L : 0.f;
+  bf16x4 v4;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) v4[e] = (__bf16)(acc[e] * inv);
+  *reinterpret_cast<bf16x4*>(a.o + b * a.os0 + h * a.os1 + (int64_t)qrow * a.os2 + col) = v4;
+  if (a.lse && col == 0)
+    a.lse[((int64_t)b * a.H + h) * a.Nq + qrow] =
+        L > 0.f ? (mstar + __log2f(L)) * 0.69314718055994530942f : kNegInf;
 }
 
 template <int NWAVES, int G, int TKV, int STAGES>
@@ -813,8 +822,8 @@ hipError_t launch_attention(int tq, int tkv, int waves, int stages, const AttnAr
 }
 
 hipError_t launch_splitk_merge(int tq, const AttnArgs& a, hipStream_t s) {
-  if (a.ntasks == 0) return hipSuccess;
-  const dim3 grid((unsigned)a.ntasks), block(256);
+  if (a.nrows == 0) return hipSuccess;
+  const dim3 grid((unsigned)(a.nrows * (tq / kMergeRows))), block(32 * kMergeRows);
   if (tq == 64) hipLaunchKernelGGL(splitk_merge_kernel<64>, grid, block, 0, s, a);
   else if (tq == 128) hipLaunchKernelGGL(splitk_merge_kernel<128>, grid, block, 0, s, a);
   else if (tq == 256) hipLaunchKernelGGL(splitk_merge_kernel<256>, grid, block, 0, s, a);

@@ -119,6 +119,8 @@ struct AttnArgs {
   uint16_t* o;
   float* lse;                  // may be null
   float* ws;                   // Split-K partial states (may be null when no row splits)
+  const int64_t* row_task;     // Split-K: first task of each physical row (may be null otherwise)
+  int64_t nrows;               // physical rows
   const uint16_t* zero_page;   // 256 zero bytes, read for K/V rows past the sequence end
   int64_t qs0, qs1, qs2, ks0, ks1, ks2, vs0, vs1, vs2, os0, os1, os2;
   int32_t H, Nq, Nkv;

@@ -804,6 +804,8 @@ bsa_status bsa_forward(bsa_plan_t plan, const void* q, const void* k, const void
     a.o = static_cast<uint16_t*>(o);
     a.lse = lse;
     a.ws = sg.ws;
+    a.row_task = sg.task_ptr;
+    a.nrows = sg.Rp;
     a.zero_page = plan->zero_page;
     a.qs0 = s.q_stride[0]; a.qs1 = s.q_stride[1]; a.qs2 = s.q_stride[2];
     a.ks0 = s.k_stride[0]; a.ks1 = s.k_stride[1]; a.ks2 = s.k_stride[2];
