@@ -43,7 +43,10 @@ def common_flags():
 # Per-file flags.  The attention kernel never produces NaN from finite
 # inputs (masked scores are -inf, and exp2(-inf) = 0), so NaN-quieting of
 # max operands is not needed there.
-EXTRA_FLAGS = {"attn_fwd.hip": ["-fno-honor-nans"]}
+# Its score tiles are VALU operands, so MFMA results stay in VGPRs; the
+# compiler's default for kernels with one wave per SIMD is AGPRs, from which
+# every score element would first be copied.
+EXTRA_FLAGS = {"attn_fwd.hip": ["-fno-honor-nans", "-mllvm", "-amdgpu-mfma-vgpr-form"]}
 
 
 def _compile(src: str) -> str:

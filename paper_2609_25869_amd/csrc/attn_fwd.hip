@@ -71,39 +71,6 @@ __device__ inline f32x16 mfma32(bf16x8 a, bf16x8 b, f32x16 c) {
   return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
 }
 
-// The same MFMA with the accumulator pinned to VGPRs and B read from AGPRs.
-// Once a kernel needs more than 256 registers the compiler selects the AGPR
-// form for every MFMA; score tiles are VALU operands, and from AGPRs each
-// element would first need a copy.  The hardware does not interlock an MFMA
-// result read by a VALU instruction, nor a VALU-written operand read by an
-// MFMA, and the compiler inserts no wait states around inline assembly, so
-// the callers keep those distances: the next MFMA of the same chain issues
-// at least one other MFMA later, VALU reads of the scores follow a whole
-// pipeline iteration later, and the two places where that does not hold by
-// construction (the Q operands just written, the first tile's scores just
-// computed) get an explicit wait (hazard_wait).
-__device__ inline void mfma32_vacc(f32x16& acc, bf16x8 a, bf16x8 b, bool zero) {
-  if (zero) {
-    asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, 0" : "=&v"(acc) : "v"(a), "a"(b));
-  } else {
-    asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(acc) : "v"(a), "a"(b));
-  }
-}
-
-// 24 wait states, tied to the registers they protect (the compiler can then
-// move no producer after it and no consumer before it): more than an 8-pass
-// MFMA result needs before a VALU read, and than a VALU write needs before an
-// MFMA reads it.
-template <typename T>
-__device__ inline void hazard_wait_v(T& x) { asm volatile("s_nop 7\n\ts_nop 7\n\ts_nop 7" : "+v"(x)); }
-// the same for the Q operands of a 64-row wave, all in one wait
-__device__ inline void hazard_wait_q2(bf16x8 (&q)[2][8]) {
-  asm volatile("s_nop 7\n\ts_nop 7\n\ts_nop 7"
-               : "+a"(q[0][0]), "+a"(q[0][1]), "+a"(q[0][2]), "+a"(q[0][3]), "+a"(q[0][4]), "+a"(q[0][5]),
-                 "+a"(q[0][6]), "+a"(q[0][7]), "+a"(q[1][0]), "+a"(q[1][1]), "+a"(q[1][2]), "+a"(q[1][3]),
-                 "+a"(q[1][4]), "+a"(q[1][5]), "+a"(q[1][6]), "+a"(q[1][7]));
-}
-
 __device__ inline i16x4 lds_read_tr(const uint8_t* p) {
   return __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) i16x4*)(p));
 }
@@ -169,6 +136,13 @@ __device__ inline void wait_vm_lgkm() {
   __builtin_amdgcn_s_waitcnt(0x0070 | (N & 15) | ((N >> 4) << 14));
 }
 
+// The same for vector memory alone: LDS reads may still be outstanding.
+template <int N>
+__device__ inline void wait_vm() {
+  static_assert(N >= 0 && N < 64, "vmcnt range");
+  __builtin_amdgcn_s_waitcnt(0x0F70 | (N & 15) | ((N >> 4) << 14));
+}
+
 // Workgroup barrier without a memory fence: LDS writes made by the DMA are
 // complete once vmcnt says so, and a fence here would also drain the
 // prefetches that are meant to stay in flight.  The empty asm statements
@@ -186,6 +160,7 @@ __device__ inline void block_sync() {
 // workgroups with 64 KB rings, of which only two share a CU.
 template <int NWAVES, int G, int TKV, int STAGES>
 constexpr int waves_per_simd() { return (G == 1 && (NWAVES > 2 || TKV * STAGES <= 64)) ? 2 : 1; }
+
 
 template <int NWAVES, int G, int TKV, int STAGES>
 __global__ __launch_bounds__(64 * NWAVES)
@@ -261,14 +236,20 @@ void attn_fwd_kernel(AttnArgs a) {
     }
   }
 
-  // The task's tile list and membership bits are read through the scalar
-  // cache (constant address space): vector loads would be counted together
-  // with the in-flight K/V loads and force them to drain.
-  typedef const __attribute__((address_space(4))) int32_t* ci32p;
-  typedef const __attribute__((address_space(4))) uint64_t* cu64p;
+  // The task's tile list and membership bits are held 64 entries at a time in
+  // vector registers, lane l holding entry (chunk start + l), and an
+  // iteration takes its entry with a lane read: no memory latency inside the
+  // loop.  The chunk after the current one is loaded 64 iterations before it
+  // is needed.  Entries past the end of the list repeat the last one.  (Read
+  // through the scalar cache, every iteration waited for its entries before
+  // its barrier: with one wave per SIMD nothing else ran meanwhile.  T =
+  // (64, 32) on 32-token blocks, 24576 tokens: 1.40 -> 1.08 ms with the score
+  // tiles kept in VGPRs as well; T = (128, 64), 115200 tokens under a 15%
+  // window: 21.8 -> 21.3 ms.)
   const int tb = task.tile_begin;
   const int nkv_tiles = task.tile_end - tb;
-  ci32p kvt = (ci32p)(a.kv_tile + tb);
+  auto load_ids = [&](int base) -> int { return a.kv_tile[tb + min(base + lane, nkv_tiles - 1)]; };
+  auto load_bits = [&](int base) -> uint64_t { return a.member[tb + min(base + lane, nkv_tiles - 1)]; };
 
   // ---- K/V tiles: buffer loads straight into LDS
   // One instruction moves 64 lanes x 16 bytes = 4 token rows into 1 KB of
@@ -319,9 +300,6 @@ void attn_fwd_kernel(AttnArgs a) {
 #pragma unroll
     for (int j = 0; j < kLoadsPerWave; ++j) dma_one(vrsrc, vstride, voffs, kv0, j, vslot(slot));
   };
-  // first token of tile t, clamped to the task's tiles
-  auto tile_kv0 = [&](int t) -> int { return kvt[t < 0 ? 0 : t < nkv_tiles ? t : nkv_tiles - 1] * TKV; };
-
   // lane-constant LDS offsets
   const int sw = swz(lane & 15);
   int koff[8];  // K operand: row (lane % 32) of a 32-key block, chunk 2c + hh
@@ -347,13 +325,7 @@ void attn_fwd_kernel(AttnArgs a) {
   for (int g = 0; g < G; ++g) mem_row[g] = (a.gq > 1) ? (q_local(g) >> a.bq_shift) : 0;
   const int mem_bits = a.gq * a.gkv;
   const uint64_t full = (mem_bits >= 64) ? ~0ull : ((1ull << mem_bits) - 1);
-  // membership bits of tile t: the plan's bitmap, or, for plans that record
-  // none, the zero page inverted (every member active); no branch, so the
-  // scalar loads of one iteration issue together
-  const cu64p mbits = a.member ? (cu64p)(a.member + tb) : (cu64p)a.zero_page;
-  const int mstep = a.member ? 1 : 0;
-  const uint64_t minv = a.member ? 0ull : ~0ull;
-  auto bits_of = [&](int t) -> uint64_t { return (mbits[t * mstep] ^ minv) & full; };
+  const bool has_member = a.member != nullptr;  // else every member of every tile is active
   const bf16x2 ones2 = {(__bf16)1.0f, (__bf16)1.0f};
 
   f32x16 o[G][4];
@@ -404,8 +376,7 @@ void attn_fwd_kernel(AttnArgs a) {
       if (u + 2 < kNA) op[(u + 2) % 3] = load_op(u + 2, ks, nullptr);
 #pragma unroll
       for (int g = 0; g < G; ++g) {
-        if constexpr (G == 1) s[g * kNKB + u % kNKB] = mfma32(op[u % 3], qf[g][u / kNKB], s[g * kNKB + u % kNKB]);
-        else mfma32_vacc(s[g * kNKB + u % kNKB], op[u % 3], qf[g][u / kNKB], u < kNKB);
+        s[g * kNKB + u % kNKB] = mfma32(op[u % 3], qf[g][u / kNKB], s[g * kNKB + u % kNKB]);
       }
     }
   };
@@ -471,7 +442,17 @@ void attn_fwd_kernel(AttnArgs a) {
   constexpr int kNS = kNU * G;            // MFMA slots of one iteration
   // elements whose exponential is formed by the end of slot ss
   auto a_end = [&](int ss) -> int { return ss < 0 ? 0 : ss < kNS - 1 ? (ss + 1) * kEAll / (kNS - 1) : kEAll; };
-  constexpr int kAhead = 3;  // operand read distance, in units
+    constexpr int kAhead = 3;  // operand read distance, in units
+  // Rings of four or more slots: the barrier at the end of iteration t makes
+  // slot t+3 visible, one iteration before it is needed, so the first operands
+  // of iteration t+1 are read during the last units of iteration t and the
+  // matrix pipe does not wait for the LDS behind every barrier (T = (128, 32),
+  // 115200 tokens under a 15% window: 22.9 -> 22.2 ms; the 8-wave kernel has
+  // no registers left for it).
+  constexpr bool kEarly = STAGES >= 4 && NWAVES < 8;
+  static_assert(!kEarly || (kNU % (kAhead + 1) == 0 && kNA >= kAhead),
+                "operand registers line up from one iteration to the next");
+  bf16x8 op[kAhead + 1];
 
   // probability of a raw score against the reference -nm, and the bf16
   // packing of a pair of them (register k of chunk c holds elements 8c + 2k
@@ -485,7 +466,7 @@ void attn_fwd_kernel(AttnArgs a) {
   // (into pw_cur).  Leaves each group's lane sum of those probabilities in
   // lsum; active tells whether the lane's row of a group has a key in tile t.
   auto iteration = [&](f32x16* s_cur, f32x16* s_nxt, int kv0_cur, uint64_t bits_cur, const uint8_t* ks_next,
-                       const uint8_t* vs_prev, u32x4* pw_cur, const u32x4* pw_prev, int kv0_refill_k,
+                       const uint8_t* vs_prev, const uint8_t* ks_after, u32x4* pw_cur, const u32x4* pw_prev, int kv0_refill_k,
                        int kv0_refill_v, uint8_t* k_refill, uint8_t* v_refill, bool* active, float* lsum) {
     // the ring refill of this iteration goes out one load every kDmaEvery units
 #pragma unroll
@@ -514,9 +495,10 @@ void attn_fwd_kernel(AttnArgs a) {
       // keep the sum in this unit (otherwise it is sunk to the end of the loop)
       asm volatile("" : "+v"(acc));
     };
-    bf16x8 op[kAhead + 1];
+    if constexpr (!kEarly) {
 #pragma unroll
-    for (int u = 0; u < kAhead; ++u) op[u] = load_op(u, ks_next, vs_prev);
+      for (int u = 0; u < kAhead; ++u) op[u] = load_op(u, ks_next, vs_prev);
+    }
     // one MFMA per slot: slot sl is row group sl % G of unit sl / G, so the
     // VALU work between two MFMAs of the wave stays short
 #pragma unroll
@@ -524,6 +506,7 @@ void attn_fwd_kernel(AttnArgs a) {
       const int u = sl / G, g = sl % G;
       if (g == 0) {
         if (u + kAhead < kNU) op[(u + kAhead) % (kAhead + 1)] = load_op(u + kAhead, ks_next, vs_prev);
+        else if (kEarly) op[(u + kAhead) % (kAhead + 1)] = load_op(u + kAhead - kNU, ks_after, nullptr);
         if (u % kDmaEvery == 0 && u / kDmaEvery < kGroupLoads) {
           const int i = u / kDmaEvery;
           if (i < kLoadsPerWave) dma_one(krsrc, kstride, koffs, kv0_refill_k, i, k_refill);
@@ -532,11 +515,7 @@ void attn_fwd_kernel(AttnArgs a) {
       }
       if (u < kNA) {
         f32x16& acc = s_nxt[g * kNKB + u % kNKB];
-        if constexpr (G == 1) {
-          acc = mfma32(op[u % (kAhead + 1)], qf[g][u / kNKB], u < kNKB ? f32x16{} : acc);
-        } else {
-          mfma32_vacc(acc, op[u % (kAhead + 1)], qf[g][u / kNKB], u < kNKB);
-        }
+        acc = mfma32(op[u % (kAhead + 1)], qf[g][u / kNKB], u < kNKB ? f32x16{} : acc);
       } else {
         const int j = u - kNA;
         o[g][j % 4] = mfma32(op[u % (kAhead + 1)], __builtin_bit_cast(bf16x8, pw_prev[g * kChunks + j / 4]),
@@ -583,15 +562,23 @@ void attn_fwd_kernel(AttnArgs a) {
 
   // number of DMA instructions one iteration issues (K tile and V tile)
   constexpr int kGroup = 2 * kLoadsPerWave;
-  constexpr int kInFlight = (STAGES - 2) * kGroup;
+  constexpr int kInFlight = (STAGES - (kEarly ? 3 : 2)) * kGroup;
 
   f32x16 sA[G * kNKB], sB[G * kNKB];
   u32x4 pwA[G * kChunks], pwB[G * kChunks];
 #pragma unroll
   for (int c = 0; c < G * kChunks; ++c) pwB[c] = u32x4{};  // P of "tile -1": no contribution
-  // scalars for the coming iteration, fetched one iteration ahead
-  int kv_next_k = 0, kv_next_v = 0, kv_cur = 0;
-  uint64_t bits_cur = full;
+  // kvr[j]: first token of the latest tile x = j (mod STAGES) whose K load was
+  // issued; ids / bits: the current and the next chunk of the tile list
+  int kvr[STAGES];
+  int ids = 0, ids_next = 0;
+  uint64_t bits = full, bits_next = full, bits_cur = full;
+  auto tile_id = [&](int t) -> int { return __builtin_amdgcn_readlane(ids, t & 63) * TKV; };
+  auto bits_of = [&](int t) -> uint64_t {
+    const uint32_t lo = __builtin_amdgcn_readlane((int)(uint32_t)bits, t & 63);
+    const uint32_t hi = __builtin_amdgcn_readlane((int)(uint32_t)(bits >> 32), t & 63);
+    return ((uint64_t)hi << 32 | lo) & full;
+  };
   if (nkv_tiles > 0) {
     // prologue: K of tile 0 into slot 0, then slot j <- (K of tile j, V of
     // tile j-2) for j = 1..STAGES-1, in the order they are needed (V of the
@@ -599,28 +586,32 @@ void attn_fwd_kernel(AttnArgs a) {
     // any finite data).  Ring refills are never skipped: past the end of the
     // task they re-load its last tile into the free slot, which keeps the
     // count of loads in flight the same on every path.
-    dma_k(tile_kv0(0), 0);
+    ids = load_ids(0);
+    ids_next = load_ids(64);
+    if (has_member) {
+      bits = load_bits(0);
+      bits_next = load_bits(64);
+      bits_cur = bits_of(0);
+    }
+#pragma unroll
+    for (int j = 0; j < STAGES; ++j) kvr[j] = tile_id(j);
+    dma_k(kvr[0], 0);
 #pragma unroll
     for (int j = 1; j < STAGES; ++j) {
-      dma_k(tile_kv0(j), j);
-      dma_v(tile_kv0(j - 2), j);
+      dma_k(kvr[j], j);
+      dma_v(kvr[j < 2 ? 0 : j - 2], j);
     }
-    kv_next_k = tile_kv0(STAGES);
-    kv_next_v = tile_kv0(STAGES - 2);
-    kv_cur = tile_kv0(0);
-    bits_cur = bits_of(0);
     // the scores of tile 0 need K0 only
     wait_vm_lgkm<(STAGES - 1) * kGroup>();
     block_sync();
-    if constexpr (G > 1) hazard_wait_q2(qf);
     qk_only(kslot(0), sA);
-    if constexpr (G > 1) {
-#pragma unroll
-      for (int i = 0; i < G * kNKB; ++i) hazard_wait_v(sA[i]);
-    }
     // the first iteration needs slot 1
     wait_vm_lgkm<kInFlight>();
     block_sync();  // every wave has read slot 0 before it is refilled
+    if constexpr (kEarly) {
+#pragma unroll
+      for (int u = 0; u < kAhead; ++u) op[u] = load_op(u, kslot(1), nullptr);
+    }
   }
   for (int t0 = 0; t0 < nkv_tiles; t0 += STAGES) {
 #pragma unroll
@@ -629,14 +620,18 @@ void attn_fwd_kernel(AttnArgs a) {
       if (t >= nkv_tiles) break;
       // refill slot t % STAGES with K of tile t+STAGES and V of tile
       // t+STAGES-2 (issued inside the iteration, spread over its MFMA units)
+      const int kv_cur = kvr[u];
+      const int kv_next_v = kvr[(u + STAGES - 2) % STAGES];
+      const int kv_next_k = tile_id(t + STAGES);
+      kvr[u] = kv_next_k;
       f32x16* s_cur = (u % 2 == 0) ? sA : sB;
       f32x16* s_nxt = (u % 2 == 0) ? sB : sA;
       u32x4* pw_cur = (u % 2 == 0) ? pwA : pwB;
       u32x4* pw_prev = (u % 2 == 0) ? pwB : pwA;
       bool active[G];
       float lsum[G];
-      iteration(s_cur, s_nxt, kv_cur, bits_cur, kslot((u + 1) % STAGES), vslot((u + 1) % STAGES), pw_cur, pw_prev,
-                kv_next_k, kv_next_v, kslot(u), vslot(u), active, lsum);
+      iteration(s_cur, s_nxt, kv_cur, bits_cur, kslot((u + 1) % STAGES), vslot((u + 1) % STAGES),
+                kslot((u + 2) % STAGES), pw_cur, pw_prev, kv_next_k, kv_next_v, kslot(u), vslot(u), active, lsum);
       // the check of tile t before any MFMA uses its probabilities (sums of
       // probabilities in [0, inf] are never NaN)
       auto needs_raise = [&](int g) { return lsum[g] > kSumMax || (m_run[g] == kNegInf && active[g]); };
@@ -656,16 +651,26 @@ void attn_fwd_kernel(AttnArgs a) {
       }
 #pragma unroll
       for (int g = 0; g < G; ++g) l_run[g] += lsum[g];
-      // scalars of the next iteration, complete before the barrier so no
-      // scalar load is outstanding while the next iteration's LDS reads are
-      // counted
-      kv_next_k = tile_kv0(t + 1 + STAGES);
-      kv_next_v = tile_kv0(t + STAGES - 1);
-      kv_cur = tile_kv0(t + 1);
-      bits_cur = bits_of(t + 1 < nkv_tiles ? t + 1 : nkv_tiles - 1);
-      asm volatile("" ::"s"(kv_next_k), "s"(kv_next_v), "s"(kv_cur), "s"(bits_cur));
-      // slot (t+2) % STAGES must have landed; younger loads may fly
-      wait_vm_lgkm<kInFlight>();
+      // list entries of the next iteration; every 64 tiles the next chunk
+      // becomes the current one (its load is waited for here, inside the rare
+      // branch) and the one after it is requested
+      if (__builtin_expect(((t + 1 + STAGES) & 63) == 0, 0)) {
+        ids = ids_next;
+        asm volatile("" : "+v"(ids));
+        ids_next = load_ids(t + 1 + STAGES + 64);
+      }
+      if (has_member) {
+        if (__builtin_expect(((t + 1) & 63) == 0, 0)) {
+          bits = bits_next;
+          asm volatile("" : "+v"(bits));
+          bits_next = load_bits(t + 1 + 64);
+        }
+        bits_cur = bits_of(t + 1);
+      }
+      // slot (t+2) % STAGES (kEarly: slot (t+3) % STAGES) must have landed;
+      // younger loads may fly.  The reads of this iteration's slot have
+      // retired: their MFMAs have been issued.
+      if constexpr (kEarly) wait_vm<kInFlight>(); else wait_vm_lgkm<kInFlight>();
       block_sync();
     }
   }
