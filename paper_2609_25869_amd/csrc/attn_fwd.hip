@@ -162,7 +162,12 @@ template <int NWAVES, int G, int TKV, int STAGES>
 constexpr int waves_per_simd() { return (G == 1 && (NWAVES > 2 || TKV * STAGES <= 64)) ? 2 : 1; }
 
 
-template <int NWAVES, int G, int TKV, int STAGES>
+// UNIT is the number of tokens of one tile-list entry: TKV, or 16 for
+// compacted lists, whose iterations pack the next TKV / 16 active 16-token
+// columns of the list, wherever they lie, into one TKV-key tile.  (16, 16)
+// blocks, 30011 tokens, 8 heads, 10% of the blocks: 2.69 -> 1.44 ms, 640
+// packed columns a row in place of 535 tiles of two.
+template <int NWAVES, int G, int TKV, int STAGES, int UNIT>
 __global__ __launch_bounds__(64 * NWAVES)
 __attribute__((amdgpu_waves_per_eu(waves_per_simd<NWAVES, G, TKV, STAGES>(), waves_per_simd<NWAVES, G, TKV, STAGES>())))
 void attn_fwd_kernel(AttnArgs a) {
@@ -170,6 +175,8 @@ void attn_fwd_kernel(AttnArgs a) {
   constexpr int kNKB = C::kNKB;
   static_assert(STAGES == 2 || STAGES == 4 || STAGES == 8, "ring depth");
   static_assert(G == 1 || G == 2, "row groups per wave");
+  static_assert(UNIT == TKV || (UNIT == 16 && TKV == 32), "tokens per list entry");
+  constexpr int kEnt = TKV / UNIT;  // list entries per iteration
   // A ring of STAGES slots; slot j holds K of a tile x = j (mod STAGES) and
   // V of tile x-2.  Iteration t reads slot (t+1) % STAGES: K of tile t+1
   // (scores of the next tile) and V of tile t-1 (O += P V of the previous
@@ -246,10 +253,13 @@ void attn_fwd_kernel(AttnArgs a) {
   // (64, 32) on 32-token blocks, 24576 tokens: 1.40 -> 1.08 ms with the score
   // tiles kept in VGPRs as well; T = (128, 64), 115200 tokens under a 15%
   // window: 21.8 -> 21.3 ms.)
+  struct Kv0 { int t[kEnt]; };        // first tokens of a tile's entries
+  struct Bits { uint64_t m[kEnt]; };  // member bits of a tile's entries
   const int tb = task.tile_begin;
-  const int nkv_tiles = task.tile_end - tb;
-  auto load_ids = [&](int base) -> int { return a.kv_tile[tb + min(base + lane, nkv_tiles - 1)]; };
-  auto load_bits = [&](int base) -> uint64_t { return a.member[tb + min(base + lane, nkv_tiles - 1)]; };
+  const int n_ent = task.tile_end - tb;
+  const int nkv_tiles = (n_ent + kEnt - 1) / kEnt;
+  auto load_ids = [&](int base) -> int { return a.kv_tile[tb + min(base + lane, n_ent - 1)]; };
+  auto load_bits = [&](int base) -> uint64_t { return a.member[tb + min(base + lane, n_ent - 1)]; };
 
   // ---- K/V tiles: buffer loads straight into LDS
   // One instruction moves 64 lanes x 16 bytes = 4 token rows into 1 KB of
@@ -283,20 +293,22 @@ void attn_fwd_kernel(AttnArgs a) {
       __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(kbase), 0, (int)((int64_t)a.Nkv * kstride), 0x00020000);
   const __amdgpu_buffer_rsrc_t vrsrc =
       __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(vbase), 0, (int)((int64_t)a.Nkv * vstride), 0x00020000);
-  // load j of this wave's share of the tile starting at token kv0
-  auto dma_one = [&](__amdgpu_buffer_rsrc_t rsrc, int64_t stride, const uint32_t* offs, int kv0, int j,
+  // load j of this wave's share of the tile whose entries start at tokens kv0
+  static_assert(kRep * 4 * NWAVES == 16 || UNIT == TKV, "16 rows per entry and load group");
+  auto dma_one = [&](__amdgpu_buffer_rsrc_t rsrc, int64_t stride, const uint32_t* offs, const Kv0& kv0, int j,
                      uint8_t* dst_arr) {
-    const uint32_t row0 = (uint32_t)(kv0 + (j / kRep) * (kRep * 4 * NWAVES)) * (uint32_t)stride;
+    const int first = UNIT == TKV ? kv0.t[0] + (j / kRep) * (kRep * 4 * NWAVES) : kv0.t[(j / kRep) % kEnt];
+    const uint32_t row0 = (uint32_t)first * (uint32_t)stride;
     __builtin_amdgcn_raw_ptr_buffer_load_lds(
         rsrc, (__attribute__((address_space(3))) void*)(dst_arr + 1024 * (w + j * NWAVES)), 16, offs[j % kRep] + row0,
         0, 0, 0);
   };
-  // copy the TKV tokens starting at kv0 into one ring slot
-  auto dma_k = [&](int kv0, int slot) {
+  // copy one tile into one ring slot
+  auto dma_k = [&](const Kv0& kv0, int slot) {
 #pragma unroll
     for (int j = 0; j < kLoadsPerWave; ++j) dma_one(krsrc, kstride, koffs, kv0, j, kslot(slot));
   };
-  auto dma_v = [&](int kv0, int slot) {
+  auto dma_v = [&](const Kv0& kv0, int slot) {
 #pragma unroll
     for (int j = 0; j < kLoadsPerWave; ++j) dma_one(vrsrc, vstride, voffs, kv0, j, vslot(slot));
   };
@@ -381,23 +393,54 @@ void attn_fwd_kernel(AttnArgs a) {
     }
   };
 
+  // Does any entry of the tile have an inactive member or reach past the
+  // sequence end?
+  auto all_active = [&](const Bits& bits) -> bool {
+    bool ok = true;
+#pragma unroll
+    for (int e = 0; e < kEnt; ++e) ok = ok && bits.m[e] == full;
+    return ok;
+  };
+  auto past_end = [&](const Kv0& kv0) -> bool {
+    bool past = false;
+#pragma unroll
+    for (int e = 0; e < kEnt; ++e) past = past || kv0.t[e] + UNIT > a.Nkv;
+    return past;
+  };
+
+  // Keys kSubKeys * s .. + kSubKeys - 1 of the tile, for this lane's row of a
+  // group: is their member active?  (Blocks of kSubKeys tokens or more: the
+  // keys share one member.)  64-key tiles have no registers left for four
+  // groups.
+  constexpr int kSubKeys = TKV == 64 ? 32 : 16;
+  constexpr int kSub = TKV / kSubKeys;
+  auto sub_active = [&](const Bits& bits, int mrow, int s) -> bool {
+    if constexpr (UNIT != TKV) return (bits.m[s] >> mrow) & 1ull;
+    const int col = a.gkv > 1 ? (kSubKeys * s) >> a.bkv_shift : 0;
+    return (bits.m[0] >> (mrow * a.gkv + col)) & 1ull;
+  };
+
   // entries outside the tile's active members or past the sequence end ->
   // -inf; returns whether this lane's row keeps any key of the tile
-  auto apply_mask = [&](f32x16* s, int kv0, uint64_t bits, int mrow) -> bool {
-    const uint64_t rowbits = bits >> (mrow * a.gkv);
+  auto apply_mask = [&](f32x16* s, const Kv0& kv0, const Bits& bits, int mrow) -> bool {
     // allowed-key bitmap of this lane's row over the tile
     uint64_t allowed = 0;
-    const int nvalid = min(TKV, a.Nkv - kv0);
-    const uint64_t tailmask = nvalid >= 64 ? ~0ull : ((1ull << nvalid) - 1);
-    if (a.gkv > 1) {
-      const int bkv = 1 << a.bkv_shift;
-      const uint64_t run = bkv >= 64 ? ~0ull : ((1ull << bkv) - 1);
-      for (int cm = 0; cm < a.gkv; ++cm)
-        if ((rowbits >> cm) & 1ull) allowed |= run << (cm * bkv);
-    } else {
-      allowed = (rowbits & 1ull) ? ~0ull : 0ull;
+#pragma unroll
+    for (int e = 0; e < kEnt; ++e) {
+      uint64_t keys = 0;
+      if (UNIT == TKV && a.gkv > 1) {
+        const uint64_t rowbits = bits.m[e] >> (mrow * a.gkv);
+        const int bkv = 1 << a.bkv_shift;
+        const uint64_t run = bkv >= 64 ? ~0ull : ((1ull << bkv) - 1);
+        for (int cm = 0; cm < a.gkv; ++cm)
+          if ((rowbits >> cm) & 1ull) keys |= run << (cm * bkv);
+      } else {
+        keys = ((bits.m[e] >> mrow) & 1ull) ? ~0ull : 0ull;
+      }
+      const int nvalid = min(UNIT, a.Nkv - kv0.t[e]);
+      keys &= nvalid >= 64 ? ~0ull : ((1ull << nvalid) - 1);
+      allowed |= keys << (e * UNIT);
     }
-    allowed &= tailmask;
     const uint64_t mine = allowed >> (4 * hh);
 #pragma unroll
     for (int kb = 0; kb < kNKB; ++kb) {
@@ -460,31 +503,62 @@ void attn_fwd_kernel(AttnArgs a) {
   auto exponent = [&](float sv, float nm) { return fast_exp2(__builtin_fmaf(sv, c_log2, nm)); };
   auto pack_pair = [&](float p0, float p1) { return __builtin_convertvector((f32x2){p0, p1}, bf16x2); };
 
+  // Masking.  Blocks of at least kSubKeys tokens cover whole key groups of a
+  // tile, and in the score layout kSubKeys / 2 consecutive registers of a lane
+  // hold one group, so an inactive member is masked through the exponent's addend
+  // alone: -inf in place of minus the reference, which costs nothing per
+  // score.  A masked score that is not finite gives NaN there instead of 0;
+  // the check of the probability sums catches it, and the raise path masks
+  // the scores themselves.  Smaller blocks and the sequence end mask the
+  // scores.  (Masking every score, about four instructions each: a mixture
+  // of 2 x 24 heads over 131072 tokens under T = (128, 64) tiles of two
+  // (64, 64) blocks 90.9 ms, through the addend 87.8 ms; (32, 32) blocks
+  // under (64, 32) 0.91 and 0.86 ms.)
+  const bool sub_masks = a.gkv == 1 || (1 << a.bkv_shift) >= kSubKeys;
+
   // One pipeline iteration over tile t: (rare) masking of s_cur; the S^T
   // MFMAs of tile t+1 (K from ks_next) and the O^T MFMAs of tile t-1 (V from
   // vs_prev, P from pw_prev) interleaved with the probabilities of tile t
   // (into pw_cur).  Leaves each group's lane sum of those probabilities in
   // lsum; active tells whether the lane's row of a group has a key in tile t.
-  auto iteration = [&](f32x16* s_cur, f32x16* s_nxt, int kv0_cur, uint64_t bits_cur, const uint8_t* ks_next,
-                       const uint8_t* vs_prev, const uint8_t* ks_after, u32x4* pw_cur, const u32x4* pw_prev, int kv0_refill_k,
-                       int kv0_refill_v, uint8_t* k_refill, uint8_t* v_refill, bool* active, float* lsum) {
+  auto iteration = [&](f32x16* s_cur, f32x16* s_nxt, const Kv0& kv0_cur, const Bits& bits_cur, const uint8_t* ks_next,
+                       const uint8_t* vs_prev, const uint8_t* ks_after, u32x4* pw_cur, const u32x4* pw_prev, const Kv0& kv0_refill_k,
+                       const Kv0& kv0_refill_v, uint8_t* k_refill, uint8_t* v_refill, bool* active, float* lsum) {
     // the ring refill of this iteration goes out one load every kDmaEvery units
+    float nm[G][kSub];  // exponent addend of each key group
 #pragma unroll
-    for (int g = 0; g < G; ++g) active[g] = true;
-    if (__builtin_expect(kv0_cur + TKV > a.Nkv || bits_cur != full, 0)) {
+    for (int g = 0; g < G; ++g) {
+      active[g] = true;
+      const float m = (m_run[g] == kNegInf) ? 0.f : -m_run[g];
 #pragma unroll
-      for (int g = 0; g < G; ++g) active[g] = apply_mask(s_cur + g * kNKB, kv0_cur, bits_cur, mem_row[g]);
+      for (int s = 0; s < kSub; ++s) nm[g][s] = m;
     }
-    float nm[G];
+    const bool past = past_end(kv0_cur);
+    if (__builtin_expect(past || !all_active(bits_cur), 0)) {
+      if (sub_masks && !past) {
 #pragma unroll
-    for (int g = 0; g < G; ++g) nm[g] = (m_run[g] == kNegInf) ? 0.f : -m_run[g];
+        for (int g = 0; g < G; ++g) {
+          bool any = false;
+#pragma unroll
+          for (int s = 0; s < kSub; ++s) {
+            const bool on = sub_active(bits_cur, mem_row[g], s);
+            nm[g][s] = on ? nm[g][s] : kNegInf;
+            any = any || on;
+          }
+          active[g] = any;
+        }
+      } else {
+#pragma unroll
+        for (int g = 0; g < G; ++g) active[g] = apply_mask(s_cur + g * kNKB, kv0_cur, bits_cur, mem_row[g]);
+      }
+    }
     float ls[G][2];
 #pragma unroll
     for (int g = 0; g < G; ++g) ls[g][0] = ls[g][1] = 0.f;
     float pf[kEAll];
     auto stage_a = [&](int ei) {
       const int g = ei / kE, e = ei % kE;
-      pf[ei] = exponent(s_cur[g * kNKB + e / 16][e % 16], nm[g]);
+      pf[ei] = exponent(s_cur[g * kNKB + e / 16][e % 16], nm[g][e / (kSubKeys / 2)]);
     };
     auto stage_b = [&](int pr) {
       const int e0 = 2 * pr, g = e0 / kE, el = e0 % kE;
@@ -531,6 +605,23 @@ void attn_fwd_kernel(AttnArgs a) {
     for (int g = 0; g < G; ++g) lsum[g] = ls[g][0] + ls[g][1];
   };
 
+  // The probabilities of one group's scores against its current reference,
+  // formed again from (masked) scores; returns their lane sum, added up in
+  // the iteration's order.
+  auto form_probs = [&](int g, const f32x16* s_cur, u32x4* pw_cur) -> float {
+    const float nm = (m_run[g] == kNegInf) ? 0.f : -m_run[g];
+    float ls[2] = {0.f, 0.f};
+#pragma unroll
+    for (int pr = 0; pr < kE / 2; ++pr) {
+      const int e0 = 2 * pr;
+      const bf16x2 pair = pack_pair(exponent(s_cur[g * kNKB + e0 / 16][e0 % 16], nm),
+                                    exponent(s_cur[g * kNKB + e0 / 16][e0 % 16 + 1], nm));
+      pw_cur[g * kChunks + e0 / 8][(e0 % 8) / 2] = __builtin_bit_cast(uint32_t, pair);
+      ls[pr & 1] = __builtin_amdgcn_fdot2_f32_bf16(pair, ones2, ls[pr & 1], false);
+    }
+    return ls[0] + ls[1];
+  };
+
   // Rare path after an iteration, for row group g: in the rows flagged by
   // `mine` (both lane halves of a row agree) a probability of tile t may
   // exceed 2^8, or the row met its first key.  Raise those rows' reference
@@ -547,16 +638,7 @@ void attn_fwd_kernel(AttnArgs a) {
     l_run[g] *= alpha;
 #pragma unroll
     for (int d = 0; d < 4; ++d) scale_inplace<G == 1>(o[g][d], alpha);
-    const float nm = (m_run[g] == kNegInf) ? 0.f : -m_run[g];
-    float ls = 0.f;
-#pragma unroll
-    for (int pr = 0; pr < kE / 2; ++pr) {
-      const int e0 = 2 * pr;
-      const bf16x2 pair = pack_pair(exponent(s_cur[g * kNKB + e0 / 16][e0 % 16], nm),
-                                    exponent(s_cur[g * kNKB + e0 / 16][e0 % 16 + 1], nm));
-      pw_cur[g * kChunks + e0 / 8][(e0 % 8) / 2] = __builtin_bit_cast(uint32_t, pair);
-      ls = __builtin_amdgcn_fdot2_f32_bf16(pair, ones2, ls, false);
-    }
+    const float ls = form_probs(g, s_cur, pw_cur);
     return mine ? ls : lsum_old;
   };
 
@@ -568,16 +650,33 @@ void attn_fwd_kernel(AttnArgs a) {
   u32x4 pwA[G * kChunks], pwB[G * kChunks];
 #pragma unroll
   for (int c = 0; c < G * kChunks; ++c) pwB[c] = u32x4{};  // P of "tile -1": no contribution
-  // kvr[j]: first token of the latest tile x = j (mod STAGES) whose K load was
-  // issued; ids / bits: the current and the next chunk of the tile list
-  int kvr[STAGES];
+  // kvr[j]: first tokens of the latest tile x = j (mod STAGES) whose K load
+  // was issued; ids / bits: the current and the next chunk of the tile list.
+  // A tile's entries never straddle a chunk (kEnt divides 64).
+  Kv0 kvr[STAGES];
   int ids = 0, ids_next = 0;
-  uint64_t bits = full, bits_next = full, bits_cur = full;
-  auto tile_id = [&](int t) -> int { return __builtin_amdgcn_readlane(ids, t & 63) * TKV; };
-  auto bits_of = [&](int t) -> uint64_t {
-    const uint32_t lo = __builtin_amdgcn_readlane((int)(uint32_t)bits, t & 63);
-    const uint32_t hi = __builtin_amdgcn_readlane((int)(uint32_t)(bits >> 32), t & 63);
-    return ((uint64_t)hi << 32 | lo) & full;
+  uint64_t bits = full, bits_next = full;
+  Bits bits_cur;
+#pragma unroll
+  for (int e = 0; e < kEnt; ++e) bits_cur.m[e] = full;
+  auto tile_at = [&](int t) -> Kv0 {
+    Kv0 k;
+#pragma unroll
+    for (int e = 0; e < kEnt; ++e) k.t[e] = __builtin_amdgcn_readlane(ids, (t * kEnt + e) & 63) * UNIT;
+    return k;
+  };
+  auto bits_at_tile = [&](int t) -> Bits {
+    Bits b;
+#pragma unroll
+    for (int e = 0; e < kEnt; ++e) {
+      const int p = (t * kEnt + e) & 63;
+      const uint32_t lo = __builtin_amdgcn_readlane((int)(uint32_t)bits, p);
+      const uint32_t hi = __builtin_amdgcn_readlane((int)(uint32_t)(bits >> 32), p);
+      b.m[e] = ((uint64_t)hi << 32 | lo) & full;
+      // the places of the last tile past the end of the list
+      if (e > 0 && t * kEnt + e >= n_ent) b.m[e] = 0;
+    }
+    return b;
   };
   if (nkv_tiles > 0) {
     // prologue: K of tile 0 into slot 0, then slot j <- (K of tile j, V of
@@ -591,10 +690,10 @@ void attn_fwd_kernel(AttnArgs a) {
     if (has_member) {
       bits = load_bits(0);
       bits_next = load_bits(64);
-      bits_cur = bits_of(0);
     }
+    if (has_member || kEnt > 1) bits_cur = bits_at_tile(0);
 #pragma unroll
-    for (int j = 0; j < STAGES; ++j) kvr[j] = tile_id(j);
+    for (int j = 0; j < STAGES; ++j) kvr[j] = tile_at(j);
     dma_k(kvr[0], 0);
 #pragma unroll
     for (int j = 1; j < STAGES; ++j) {
@@ -620,9 +719,10 @@ void attn_fwd_kernel(AttnArgs a) {
       if (t >= nkv_tiles) break;
       // refill slot t % STAGES with K of tile t+STAGES and V of tile
       // t+STAGES-2 (issued inside the iteration, spread over its MFMA units)
-      const int kv_cur = kvr[u];
-      const int kv_next_v = kvr[(u + STAGES - 2) % STAGES];
-      const int kv_next_k = tile_id(t + STAGES);
+      const Kv0 kv_cur = kvr[u];
+      const Kv0 kv_next_v = kvr[(u + STAGES - 2) % STAGES];
+      const Kv0 kv_next_k = tile_at(t + STAGES);
+      const Bits bits_at = bits_cur;
       kvr[u] = kv_next_k;
       f32x16* s_cur = (u % 2 == 0) ? sA : sB;
       f32x16* s_nxt = (u % 2 == 0) ? sB : sA;
@@ -630,17 +730,26 @@ void attn_fwd_kernel(AttnArgs a) {
       u32x4* pw_prev = (u % 2 == 0) ? pwB : pwA;
       bool active[G];
       float lsum[G];
-      iteration(s_cur, s_nxt, kv_cur, bits_cur, kslot((u + 1) % STAGES), vslot((u + 1) % STAGES),
+      iteration(s_cur, s_nxt, kv_cur, bits_at, kslot((u + 1) % STAGES), vslot((u + 1) % STAGES),
                 kslot((u + 2) % STAGES), pw_cur, pw_prev, kv_next_k, kv_next_v, kslot(u), vslot(u), active, lsum);
-      // the check of tile t before any MFMA uses its probabilities (sums of
-      // probabilities in [0, inf] are never NaN)
-      auto needs_raise = [&](int g) { return lsum[g] > kSumMax || (m_run[g] == kNegInf && active[g]); };
+      // the check of tile t before any MFMA uses its probabilities (their sum
+      // is >= 0 or NaN, which as an integer is above every number)
+      auto needs_raise = [&](int g) {
+        return __float_as_uint(lsum[g]) > __float_as_uint(kSumMax) || (m_run[g] == kNegInf && active[g]);
+      };
       uint64_t need_any = 0;
 #pragma unroll
       for (int g = 0; g < G; ++g) need_any |= __ballot(needs_raise(g));
       if (__builtin_expect(need_any != 0, 0)) {
 #pragma unroll
         for (int g = 0; g < G; ++g) {
+          // a tile with inactive members: mask the scores themselves, so that
+          // only active ones count below, and form its probabilities from
+          // them (the same bits wherever the masked scores were finite)
+          if (past_end(kv_cur) || !all_active(bits_at)) {
+            (void)apply_mask(s_cur + g * kNKB, kv_cur, bits_at, mem_row[g]);
+            lsum[g] = form_probs(g, s_cur, pw_cur);
+          }
           // both lane halves of a row take the same decision; the exchange
           // runs in every lane (under a short-circuit || it would run only in
           // some lanes, and a lane swap there reads inactive partners)
@@ -651,22 +760,20 @@ void attn_fwd_kernel(AttnArgs a) {
       }
 #pragma unroll
       for (int g = 0; g < G; ++g) l_run[g] += lsum[g];
-      // list entries of the next iteration; every 64 tiles the next chunk
+      // list entries of the next iteration; every 64 entries the next chunk
       // becomes the current one (its load is waited for here, inside the rare
       // branch) and the one after it is requested
-      if (__builtin_expect(((t + 1 + STAGES) & 63) == 0, 0)) {
+      if (__builtin_expect(((t + 1 + STAGES) * kEnt & 63) == 0, 0)) {
         ids = ids_next;
         asm volatile("" : "+v"(ids));
-        ids_next = load_ids(t + 1 + STAGES + 64);
+        ids_next = load_ids((t + 1 + STAGES) * kEnt + 64);
       }
-      if (has_member) {
-        if (__builtin_expect(((t + 1) & 63) == 0, 0)) {
-          bits = bits_next;
-          asm volatile("" : "+v"(bits));
-          bits_next = load_bits(t + 1 + 64);
-        }
-        bits_cur = bits_of(t + 1);
+      if (has_member && __builtin_expect(((t + 1) * kEnt & 63) == 0, 0)) {
+        bits = bits_next;
+        asm volatile("" : "+v"(bits));
+        bits_next = load_bits((t + 1) * kEnt + 64);
       }
+      if (has_member || kEnt > 1) bits_cur = bits_at_tile(t + 1);
       // slot (t+2) % STAGES (kEarly: slot (t+3) % STAGES) must have landed;
       // younger loads may fly.  The reads of this iteration's slot have
       // retired: their MFMAs have been issued.
@@ -797,11 +904,11 @@ __global__ __launch_bounds__(32 * kMergeRows) void splitk_merge_kernel(AttnArgs 
         L > 0.f ? (mstar + __log2f(L)) * 0.69314718055994530942f : kNegInf;
 }
 
-template <int NWAVES, int G, int TKV, int STAGES>
+template <int NWAVES, int G, int TKV, int STAGES, int UNIT = TKV>
 hipError_t launch_variant(const AttnArgs& a, hipStream_t s) {
   const int64_t slots = a.nslots > 0 ? a.nslots : default_slots(a.ntasks);
   if (slots == 0) return hipSuccess;
-  hipLaunchKernelGGL((attn_fwd_kernel<NWAVES, G, TKV, STAGES>), dim3((unsigned)slots), dim3(64 * NWAVES), 0, s, a);
+  hipLaunchKernelGGL((attn_fwd_kernel<NWAVES, G, TKV, STAGES, UNIT>), dim3((unsigned)slots), dim3(64 * NWAVES), 0, s, a);
   return hipGetLastError();
 }
 
@@ -814,6 +921,13 @@ hipError_t launch_variant(const AttnArgs& a, hipStream_t s) {
 // groups sharing every K and V operand, one workgroup per CU, eight slots);
 // with 64-key tiles eight waves of 32 rows.
 hipError_t launch_attention(int tq, int tkv, int waves, int stages, const AttnArgs& a, hipStream_t s) {
+  if (a.unit == 16) {
+    if (tq == 64 && tkv == 32 && waves == 2 && stages == 4) return launch_variant<2, 1, 32, 4, 16>(a, s);
+    if (tq == 64 && tkv == 32 && waves == 2 && stages == 2) return launch_variant<2, 1, 32, 2, 16>(a, s);
+    if (tq == 128 && tkv == 32 && waves == 4 && stages == 4) return launch_variant<4, 1, 32, 4, 16>(a, s);
+    if (tq == 128 && tkv == 32 && waves == 4 && stages == 2) return launch_variant<4, 1, 32, 2, 16>(a, s);
+    return hipErrorInvalidValue;
+  }
   if (tq == 64 && tkv == 32 && waves == 2 && stages == 4) return launch_variant<2, 1, 32, 4>(a, s);
   if (tq == 64 && tkv == 32 && waves == 2 && stages == 2) return launch_variant<2, 1, 32, 2>(a, s);
   if (tq == 64 && tkv == 64 && waves == 2 && stages == 2) return launch_variant<2, 1, 64, 2>(a, s);

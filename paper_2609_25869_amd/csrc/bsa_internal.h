@@ -69,6 +69,13 @@ struct MapArgs {
   const int64_t* tile_ptr;   // fill pass
   int32_t* tile_kv;
   uint64_t* member;          // may be null (no membership metadata)
+  // Compacted list of a tile list with gkv == 2 (null: none): one entry per
+  // KV block of the row with an active member, bit a of its member word for
+  // query block a.
+  int32_t* counts2;          // count pass
+  const int64_t* tile_ptr2;  // fill pass
+  int32_t* tile_kv2;
+  uint64_t* member2;         // may be null
   int32_t wide;              // mask rows 4-byte aligned and nkb % 4 == 0 (see MaskStateArgs)
 };
 
@@ -125,7 +132,8 @@ struct AttnArgs {
   int64_t qs0, qs1, qs2, ks0, ks1, ks2, vs0, vs1, vs2, os0, os1, os2;
   int32_t H, Nq, Nkv;
   int32_t bq_shift, bkv_shift;  // log2 of the logical block sizes
-  int32_t gq, gkv;              // membership grid of a tile
+  int32_t gq, gkv;              // membership grid of a list entry
+  int32_t unit;                 // 16: the list entries are 16-token columns (gkv = 1); else whole tiles
   float scale_log2;             // log2(e) / sqrt(d)
   int32_t slot_group, slot_run; // launch-slot to task map: XCDs per group (1, 2, 4 or 8) and run length
   int32_t balanced;             // nonzero: group g's share of the task list is [share_lo[g], share_lo[g + 1])

@@ -240,6 +240,22 @@ __global__ void zero_i64(int64_t* out) {
 // ---------------------------------------------------------------------------
 constexpr int kMapBatch = 16;
 
+// Bits 0, 1, 2, ... of x moved to bits 0, step, 2 step, ... (step 2 or 4;
+// tiles have at most 64 members).
+__device__ inline uint64_t spread_bits(uint64_t x, int step) {
+  if (step == 2) {
+    x = (x | (x << 16)) & 0x0000FFFF0000FFFFull;
+    x = (x | (x << 8)) & 0x00FF00FF00FF00FFull;
+    x = (x | (x << 4)) & 0x0F0F0F0F0F0F0F0Full;
+    x = (x | (x << 2)) & 0x3333333333333333ull;
+    return (x | (x << 1)) & 0x5555555555555555ull;
+  }
+  x = (x | (x << 24)) & 0x000000FF000000FFull;
+  x = (x | (x << 12)) & 0x000F000F000F000Full;
+  x = (x | (x << 6)) & 0x0303030303030303ull;
+  return (x | (x << 3)) & 0x1111111111111111ull;
+}
+
 // Physical mapping of one geometry segment (Section 4.2): tile (pq, pk) is
 // active iff one of its member logical blocks is; bit a*gkv + c records
 // member (a, c) for Coarsened tiles.
@@ -264,7 +280,79 @@ __global__ __launch_bounds__(256) void map_rows_kernel(MapArgs a) {
     nqm = 1;
   }
   const int64_t out_base = kFill ? a.tile_ptr[rp] : 0;
-  int64_t n = 0;
+  const bool compact = kFill ? a.tile_ptr2 != nullptr : a.counts2 != nullptr;
+  const int64_t out_base2 = kFill && compact ? a.tile_ptr2[rp] : 0;
+  int64_t n = 0, n2 = 0;
+  if ((a.gkv == 2 || a.gkv == 4) && a.wide) {
+    // Two or four blocks along KV per tile, word-aligned rows: a lane's word
+    // holds four blocks, i.e. two tiles (gkv = 2) or one (gkv = 4); mem[j]
+    // collects block j's activity over the tile's query rows.
+    const uint8_t* base = mh + (int64_t)qb0 * a.nkb;
+    const int nw = a.nkb >> 2;
+    const int per = 4 / a.gkv;  // tiles of a word
+    for (int w0 = 0; w0 < nw; w0 += 64) {
+      const int wi = w0 + lane;
+      const int wc = min(wi, nw - 1);
+      uint64_t mem[4] = {0ull, 0ull, 0ull, 0ull};
+      for (int a0 = 0; a0 < nqm; a0 += 4) {
+        uint32_t x[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+          x[k] = reinterpret_cast<const uint32_t*>(base + (int64_t)min(a0 + k, nqm - 1) * a.nkb)[wc];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          const uint32_t word = (wi < nw && a0 + k < nqm) ? x[k] : 0u;
+#pragma unroll
+          for (int j = 0; j < 4; ++j)
+            mem[j] |= (((word >> (8 * j)) & 0xFFu) != 0 ? 1ull : 0ull) << (a0 + k);
+        }
+      }
+      uint64_t tile[2];
+      tile[0] = spread_bits(mem[0], a.gkv) | spread_bits(mem[1], a.gkv) << 1;
+      tile[1] = spread_bits(mem[2], a.gkv) | spread_bits(mem[3], a.gkv) << 1;
+      if (a.gkv == 4) {
+        tile[0] |= tile[1] << 2;
+        tile[1] = 0ull;
+      }
+      const uint64_t below = lanes_below(lane);
+      const uint64_t t0 = __ballot(tile[0] != 0), t1 = __ballot(tile[1] != 0);
+      if (kFill) {
+        int64_t pos = out_base + n + __popcll(t0 & below) + __popcll(t1 & below);
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+          if (tile[j] != 0) {
+            a.tile_kv[pos] = per * wi + j;
+            if (a.member) a.member[pos] = tile[j];
+            ++pos;
+          }
+        }
+      }
+      n += __popcll(t0) + __popcll(t1);
+      if (compact) {
+        uint64_t bb[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) bb[j] = __ballot(mem[j] != 0);
+        if (kFill) {
+          int64_t pos = out_base2 + n2 + __popcll(bb[0] & below) + __popcll(bb[1] & below) +
+                        __popcll(bb[2] & below) + __popcll(bb[3] & below);
+#pragma unroll
+          for (int j = 0; j < 4; ++j) {
+            if (mem[j] != 0) {
+              a.tile_kv2[pos] = 4 * wi + j;
+              if (a.member2) a.member2[pos] = mem[j];
+              ++pos;
+            }
+          }
+        }
+        n2 += __popcll(bb[0]) + __popcll(bb[1]) + __popcll(bb[2]) + __popcll(bb[3]);
+      }
+    }
+    if (!kFill && lane == 0) {
+      a.counts[rp] = (int32_t)n;
+      if (compact) a.counts2[rp] = (int32_t)n2;
+    }
+    return;
+  }
   if (a.gkv == 1 && a.wide) {
     // One member block along KV per tile (Direct, Refined, Coarsened along Q,
     // and Q-coarsened / KV-refined), word-aligned rows: lane l reads blocks
@@ -382,8 +470,31 @@ __global__ __launch_bounds__(256) void map_rows_kernel(MapArgs a) {
       if (a.member) a.member[pos] = bits;
     }
     n += __popcll(ball);
+    if (compact) {  // gkv == 2: member (a, c) is bit 2 a + c
+      uint64_t col[2] = {0ull, 0ull};
+      for (int ai = 0; ai < nqm; ++ai) {
+        col[0] |= ((bits >> (2 * ai)) & 1ull) << ai;
+        col[1] |= ((bits >> (2 * ai + 1)) & 1ull) << ai;
+      }
+      const uint64_t b0 = __ballot(col[0] != 0), b1 = __ballot(col[1] != 0);
+      if (kFill) {
+        int64_t pos = out_base2 + n2 + __popcll(b0 & lanes_below(lane)) + __popcll(b1 & lanes_below(lane));
+#pragma unroll
+        for (int c = 0; c < 2; ++c) {
+          if (col[c] != 0) {
+            a.tile_kv2[pos] = 2 * pk + c;
+            if (a.member2) a.member2[pos] = col[c];
+            ++pos;
+          }
+        }
+      }
+      n2 += __popcll(b0) + __popcll(b1);
+    }
   }
-  if (!kFill && lane == 0) a.counts[rp] = (int32_t)n;
+  if (!kFill && lane == 0) {
+    a.counts[rp] = (int32_t)n;
+    if (compact) a.counts2[rp] = (int32_t)n2;
+  }
 }
 
 // ---------------------------------------------------------------------------

@@ -176,6 +176,12 @@ struct Segment {
   int64_t* tile_ptr = nullptr;  // null for Direct (logical CSR is used)
   int32_t* tile_kv = nullptr;
   uint64_t* member = nullptr;
+  // Compacted list the kernel runs instead of the tile list (see
+  // runs_compacted): entries of one 16-token KV block with an active member
+  bool compact = false;
+  int64_t* run_ptr = nullptr;
+  int32_t* run_kv = nullptr;
+  uint64_t* run_member = nullptr;
   int32_t* counts = nullptr;
   int64_t* scan_tmp = nullptr;
   Task* tasks = nullptr;
@@ -316,6 +322,18 @@ bsa_status select_segment_plan(Segment& sg, const bsa_shapes& s, const bsa_plan_
 }  // namespace
 
 namespace {
+// Whether a segment's kernel packs the active 16-token blocks of its rows
+// into 32-key tiles instead of running the tiles (32 aligned keys) as they
+// are.  A tile of two 16-token blocks by T_Q / B_Q query blocks is active
+// when any member is, so with few active blocks about half of its keys are
+// inactive columns; the packed list leaves those out and is never longer in
+// keys than the tile list (plus one half tile).  Split-K plans cut rows by
+// tiles and keep the tile list.
+bool runs_compacted(const Segment& sg) {
+  const CatalogEntry& e = sg.plan;
+  return sg.bkv == 16 && e.tkv == 32 && e.split == 1 && (e.waves == 2 || e.waves == 4) && e.tq == 32 * e.waves;
+}
+
 // Every logical mask row starts on a 4-byte boundary and spans whole words,
 // so the mask kernels may read rows as 32-bit words.
 bool mask_rows_word_aligned(const bsa_mask* mask, const std::vector<HeadDesc>& heads) {
@@ -664,11 +682,16 @@ bsa_status bsa_plan(const bsa_mask* mask, const int32_t* B_Q, const int32_t* B_K
     size_t need = 0;
     auto take = [&](size_t bytes) { size_t at = need; need = align256(need + bytes); return at; };
     const bool direct = sg.mapping == 0;
+    sg.compact = runs_compacted(sg);
     const size_t o_counts2 = take(sizeof(int32_t) * (size_t)sg.Rp);
     const size_t o_scan2 = take(sizeof(int64_t) * (size_t)scan_tmp_elems(sg.Rp));
     const size_t o_tptr = direct ? 0 : take(sizeof(int64_t) * (size_t)(sg.Rp + 1));
     const size_t o_tkv = direct ? 0 : take(sizeof(int32_t) * (size_t)sg.tiles_bound);
     const size_t o_mem = (direct || !coarse) ? 0 : take(sizeof(uint64_t) * (size_t)sg.tiles_bound);
+    const size_t o_rcnt = sg.compact ? take(sizeof(int32_t) * (size_t)sg.Rp) : 0;
+    const size_t o_rptr = sg.compact ? take(sizeof(int64_t) * (size_t)(sg.Rp + 1)) : 0;
+    const size_t o_rkv = sg.compact ? take(sizeof(int32_t) * (size_t)sg.tiles_bound) : 0;
+    const size_t o_rmem = sg.compact && sg.gq > 1 ? take(sizeof(uint64_t) * (size_t)sg.tiles_bound) : 0;
     const size_t o_tasks = take(sizeof(Task) * (size_t)sg.tasks_bound);
     const size_t o_taskptr = e.split > 1 ? take(sizeof(int64_t) * (size_t)(sg.Rp + 1)) : 0;
     // dispatch order: tasks with equal KV lists side by side.  Up to 512
@@ -717,15 +740,27 @@ bsa_status bsa_plan(const bsa_mask* mask, const int32_t* B_Q, const int32_t* B_K
       m.Rp = sg.Rp;
       m.counts = sg.counts;
       m.wide = mask_rows_word_aligned(mask, p->heads) ? 1 : 0;
+      if (sg.compact) {
+        sg.run_ptr = reinterpret_cast<int64_t*>(b8 + o_rptr);
+        sg.run_kv = reinterpret_cast<int32_t*>(b8 + o_rkv);
+        sg.run_member = sg.gq > 1 ? reinterpret_cast<uint64_t*>(b8 + o_rmem) : nullptr;
+        m.counts2 = reinterpret_cast<int32_t*>(b8 + o_rcnt);
+      }
       HIP_TRY(launch_map_count(m, stream));
       HIP_TRY(launch_scan_i32(sg.counts, sg.tile_ptr, sg.Rp, sg.scan_tmp, stream));
+      if (sg.compact) {
+        HIP_TRY(launch_scan_i32(m.counts2, sg.run_ptr, sg.Rp, sg.scan_tmp, stream));
+        m.tile_ptr2 = sg.run_ptr;
+        m.tile_kv2 = sg.run_kv;
+        m.member2 = sg.run_member;
+      }
       m.tile_ptr = sg.tile_ptr;
       m.tile_kv = sg.tile_kv;
       m.member = sg.member;
       HIP_TRY(launch_map_fill(m, stream));
     }
     TaskArgs ta{};
-    ta.tile_ptr = direct ? p->row_ptr_dev : sg.tile_ptr;
+    ta.tile_ptr = direct ? p->row_ptr_dev : sg.compact ? sg.run_ptr : sg.tile_ptr;
     ta.row_base = p->row_base_dev;
     ta.seg_heads = p->seg_heads_dev + sg.seg_heads_off;
     ta.nsh = (int32_t)sg.heads.size();
@@ -752,8 +787,9 @@ bsa_status bsa_plan(const bsa_mask* mask, const int32_t* B_Q, const int32_t* B_K
       oa.tasks = sg.tasks;
       oa.ntasks_dev = e.split > 1 ? sg.task_ptr + sg.Rp : nullptr;
       oa.ntasks = sg.tasks_bound;
-      oa.tile_kv = sg.tile_kv;
-      oa.member = sg.member;
+      // (equal tile lists and members are equal compacted lists and members)
+      oa.tile_kv = sg.compact ? sg.run_kv : sg.tile_kv;
+      oa.member = sg.compact ? sg.run_member : sg.member;
       oa.table_key = reinterpret_cast<uint64_t*>(b8 + o_tkey);
       oa.table_min = reinterpret_cast<int32_t*>(b8 + o_tmin);
       oa.table_size = table_size;
@@ -796,8 +832,9 @@ bsa_status bsa_forward(bsa_plan_t plan, const void* q, const void* k, const void
     a.ntasks = (int32_t)sg.tasks_bound;
     a.ntasks_dev = e.split > 1 ? sg.task_ptr + sg.Rp : nullptr;
     a.order = sg.order;
-    a.kv_tile = sg.tile_kv;
-    a.member = sg.member;
+    a.kv_tile = sg.compact ? sg.run_kv : sg.tile_kv;
+    a.member = sg.compact ? sg.run_member : sg.member;
+    a.unit = sg.compact ? 16 : e.tkv;
     a.q = static_cast<const uint16_t*>(q);
     a.k = static_cast<const uint16_t*>(k);
     a.v = static_cast<const uint16_t*>(v);
@@ -815,9 +852,9 @@ bsa_status bsa_forward(bsa_plan_t plan, const void* q, const void* k, const void
     a.Nq = s.seq_q;
     a.Nkv = s.seq_kv;
     a.bq_shift = sg.gq > 1 ? ilog2_exact(sg.bq) : 0;
-    a.bkv_shift = sg.gkv > 1 ? ilog2_exact(sg.bkv) : 0;
     a.gq = sg.gq;
-    a.gkv = sg.gkv;
+    a.gkv = sg.compact ? 1 : sg.gkv;
+    a.bkv_shift = a.gkv > 1 ? ilog2_exact(sg.bkv) : 0;
     a.scale_log2 = (float)(1.4426950408889634 / std::sqrt((double)s.head_dim));
     a.slot_group = e.xcd_group;
     a.slot_run = kSlotRun;
@@ -968,11 +1005,17 @@ bsa_status bsa_plan_export(bsa_plan_t plan, int32_t segment, int32_t what, void*
       if (nt) HIP_TRY(hipMemcpyAsync(t.data(), sg.tasks, sizeof(Task) * nt, hipMemcpyDeviceToHost, s));
       HIP_TRY(hipStreamSynchronize(s));
       int64_t* dst = static_cast<int64_t*>(host_buf);
+      // a compacted segment's tasks hold ranges of the compacted list; its
+      // tasks are its rows, so the tile ranges are the rows' own
+      if (sg.compact && (st = host_vec_i64(sg.tile_ptr, sg.Rp + 1, &seg_ptr)) != BSA_OK) return st;
       std::vector<int32_t> slot_of_head((size_t)plan->H, -1);
       for (size_t j = 0; j < sg.heads.size(); ++j) slot_of_head[(size_t)sg.heads[j]] = (int32_t)j;
       for (int64_t i = 0; i < nt; ++i) {
         int64_t lo = t[i].tile_begin, hi = t[i].tile_end;
-        if (sg.mapping == 0) {
+        if (sg.compact) {
+          lo = seg_ptr[(size_t)i];
+          hi = seg_ptr[(size_t)i + 1];
+        } else if (sg.mapping == 0) {
           // rebase from the global block-CSR onto the segment's tile list
           const int64_t b = t[i].bh / plan->H, h = t[i].bh % plan->H;
           const int64_t rs = (b * (int64_t)sg.heads.size() + slot_of_head[(size_t)h]) * sg.npq + t[i].pq;
