@@ -156,17 +156,32 @@ hipError_t task_order_temp_bytes(int64_t n, size_t* bytes);
 hipError_t launch_task_order(const OrderArgs& a, hipStream_t s);
 hipError_t launch_splitk_merge(int tq, const AttnArgs& a, hipStream_t s);
 
-// Top-k sparsifier (sparsify.hip): block means of a [B, N, H, 128] bf16
-// tensor for heads [bh0, bh0 + nbh) into out[nbh][ceil(N / blk)][128] (fp64),
-// the score rows of those heads, and the uint8 mask rows they select.
+// Top-k sparsifier (sparsify.hip) over heads [bh0, bh0 + nbh): block means
+// (fp64, [nbh][nb][128]) of Q (index 0) and K (index 1), bf16 [B, N, H, 128]
+// tensors; fp32 scores [nbh][nqb][nkb] with, per head, `nparts` partial
+// maxima of the mean keys' 2-norms; the uint8 mask rows they select.
+struct MeanArgs {
+  const uint16_t* x[2];
+  int64_t s0[2], s1[2], s2[2];
+  int32_t n[2], blk[2], nb[2];
+  int32_t H, bh0, nbh;
+  double* out[2];
+};
+struct SelectArgs {
+  const float* scores;
+  const float* knorm;
+  int32_t nparts;
+  const double* pq;
+  const double* pk;
+  int64_t rows;  // nbh * nqb
+  int32_t nqb, nkb, k, diagonal, nq, nkv, bq, bkv, bh0;
+  uint8_t* mask;
+};
 int32_t sparsify_max_kv_blocks();
-hipError_t launch_block_mean(const uint16_t* x, int64_t s0, int64_t s1, int64_t s2, int32_t H, int32_t n,
-                             int32_t blk, int32_t bh0, int32_t nbh, double* out, hipStream_t s);
+int32_t sparsify_norm_parts(int32_t nkb);  // room per head for the partial maxima
+hipError_t launch_block_mean(const MeanArgs& a, hipStream_t s);
 hipError_t launch_block_scores(const double* pq, const double* pk, int32_t nqb, int32_t nkb, int32_t nbh,
-                               double* scores, hipStream_t s);
-hipError_t launch_topk_select(const double* scores, int32_t nqb, int32_t nkb, int32_t k, int32_t diagonal,
-                              int32_t nq, int32_t nkv, int32_t bq, int32_t bkv, int32_t bh0, int32_t nbh,
-                              uint8_t* mask, hipStream_t s);
-
+                               float* scores, float* knorm, int32_t* nparts, hipStream_t s);
+hipError_t launch_topk_select(const SelectArgs& a, hipStream_t s);
 
 }  // namespace bsa

@@ -1073,38 +1073,78 @@ bsa_status sparsify_validate(const void* q, const void* k, const bsa_shapes* sha
   return BSA_OK;
 }
 
-// Device bytes of one head's block means (queries and keys) and score rows.
+// Device bytes of one head's block means (queries and keys), score rows and
+// key norms.
 int64_t sparsify_head_bytes(int64_t nqb, int64_t nkb) {
-  return (nqb + nkb) * kHeadDim * (int64_t)sizeof(double) + nqb * nkb * (int64_t)sizeof(double);
+  return (nqb + nkb) * kHeadDim * (int64_t)sizeof(double) + nqb * nkb * (int64_t)sizeof(float) +
+         sparsify_norm_parts((int32_t)nkb) * (int64_t)sizeof(float);
 }
 
-// The sparsifier's passes over the heads, `chunk` heads at a time, with the
-// block means and score rows of a pass in `work` (at least chunk * head bytes).
+// The sparsifier's passes over the heads, at most `most` heads at a time
+// (shared out evenly), with the block means, score rows and norms of a pass in
+// `work` (at least `most` * head bytes).
 hipError_t sparsify_passes(const void* q, const void* k, const bsa_shapes& s, int32_t bq, int32_t bkv, int32_t topk,
-                           int32_t diagonal, uint8_t* mask, int64_t nqb, int64_t nkb, int64_t chunk, void* work,
+                           int32_t diagonal, uint8_t* mask, int64_t nqb, int64_t nkb, int64_t most, void* work,
                            hipStream_t stream) {
   const int64_t nbh = (int64_t)s.batch * s.heads;
+  const int64_t chunk = cdiv(nbh, cdiv(nbh, most));
   const size_t bytes_q = (size_t)(chunk * nqb * kHeadDim) * sizeof(double);
   const size_t bytes_k = (size_t)(chunk * nkb * kHeadDim) * sizeof(double);
-  double* pq = static_cast<double*>(work);
-  double* pk = reinterpret_cast<double*>(static_cast<uint8_t*>(work) + bytes_q);
-  double* sc = reinterpret_cast<double*>(static_cast<uint8_t*>(work) + bytes_q + bytes_k);
-  const uint16_t* qh = static_cast<const uint16_t*>(q);
-  const uint16_t* kh = static_cast<const uint16_t*>(k);
+  const size_t bytes_s = (size_t)(chunk * nqb * nkb) * sizeof(float);
+  uint8_t* w8 = static_cast<uint8_t*>(work);
+  MeanArgs m{};
+  m.x[0] = static_cast<const uint16_t*>(q);
+  m.x[1] = static_cast<const uint16_t*>(k);
+  const int64_t* st[2] = {s.q_stride, s.k_stride};
+  for (int t = 0; t < 2; ++t) {
+    m.s0[t] = st[t][0];
+    m.s1[t] = st[t][1];
+    m.s2[t] = st[t][2];
+  }
+  m.n[0] = s.seq_q;
+  m.n[1] = s.seq_kv;
+  m.blk[0] = bq;
+  m.blk[1] = bkv;
+  m.nb[0] = (int32_t)nqb;
+  m.nb[1] = (int32_t)nkb;
+  m.H = s.heads;
+  m.out[0] = reinterpret_cast<double*>(w8);
+  m.out[1] = reinterpret_cast<double*>(w8 + bytes_q);
+  float* scores = reinterpret_cast<float*>(w8 + bytes_q + bytes_k);
+  float* knorm = reinterpret_cast<float*>(w8 + bytes_q + bytes_k + bytes_s);
   hipError_t e = hipSuccess;
   for (int64_t bh0 = 0; bh0 < nbh && e == hipSuccess; bh0 += chunk) {
     const int32_t n = (int32_t)std::min<int64_t>(chunk, nbh - bh0);
-    e = launch_block_mean(qh, s.q_stride[0], s.q_stride[1], s.q_stride[2], s.heads, s.seq_q, bq, (int32_t)bh0, n, pq,
-                          stream);
+    m.bh0 = (int32_t)bh0;
+    m.nbh = n;
+    SelectArgs a{};
+    a.scores = scores;
+    a.knorm = knorm;
+    a.pq = m.out[0];
+    a.pk = m.out[1];
+    a.rows = n * nqb;
+    a.nqb = (int32_t)nqb;
+    a.nkb = (int32_t)nkb;
+    a.k = topk;
+    a.diagonal = diagonal ? 1 : 0;
+    a.nq = s.seq_q;
+    a.nkv = s.seq_kv;
+    a.bq = bq;
+    a.bkv = bkv;
+    a.bh0 = (int32_t)bh0;
+    a.mask = mask;
+    e = launch_block_mean(m, stream);
     if (e == hipSuccess)
-      e = launch_block_mean(kh, s.k_stride[0], s.k_stride[1], s.k_stride[2], s.heads, s.seq_kv, bkv, (int32_t)bh0, n,
-                            pk, stream);
-    if (e == hipSuccess) e = launch_block_scores(pq, pk, (int32_t)nqb, (int32_t)nkb, n, sc, stream);
-    if (e == hipSuccess)
-      e = launch_topk_select(sc, (int32_t)nqb, (int32_t)nkb, topk, diagonal ? 1 : 0, s.seq_q, s.seq_kv, bq, bkv,
-                             (int32_t)bh0, n, mask, stream);
+      e = launch_block_scores(a.pq, a.pk, a.nqb, a.nkb, n, scores, knorm, &a.nparts, stream);
+    if (e == hipSuccess) e = launch_topk_select(a, stream);
   }
   return e;
+}
+
+// Heads of one pass: at most `room` bytes of `per` bytes a head, and what one
+// launch's grid can hold.
+int64_t sparsify_heads_per_pass(int64_t nbh, int64_t room, int64_t per) {
+  return std::max<int64_t>(1, std::min<int64_t>({nbh, room / per, 65535}));
 }
 
 // Scratch of the allocation-free sparsifier: one copy per device, resident
@@ -1112,7 +1152,7 @@ hipError_t sparsify_passes(const void* q, const void* k, const bsa_shapes& s, in
 // kernel (in host code it names a host-side stand-in); it uses the device
 // address that hipGetSymbolAddress returns for the current device.
 constexpr int64_t kNoAllocScratchBytes = int64_t(64) << 20;
-static __device__ __attribute__((aligned(256))) uint8_t scratch[kNoAllocScratchBytes];
+static __device__ __attribute__((aligned(256))) uint8_t scratch[kNoAllocScratchBytes + 4096];
 
 constexpr int kMaxDevices = 64;
 std::mutex g_scratch_mu;
@@ -1147,10 +1187,9 @@ bsa_status bsa_sparsify_topk(const void* q, const void* k, const bsa_shapes* sha
   int dev = 0;
   HIP_TRY(hipGetDevice(&dev));
   prepare_pool(dev);
-  const int64_t nbh = (int64_t)s.batch * s.heads;
   // heads per pass: score rows of at most 256 MiB
-  const int64_t per_scores = nqb * nkb * (int64_t)sizeof(double);
-  const int64_t chunk = std::max<int64_t>(1, std::min<int64_t>(nbh, (int64_t(256) << 20) / per_scores));
+  const int64_t chunk = sparsify_heads_per_pass((int64_t)s.batch * s.heads, int64_t(256) << 20,
+                                                nqb * nkb * (int64_t)sizeof(float));
   void* work = nullptr;
   HIP_TRY(hipMallocAsync(&work, (size_t)(chunk * sparsify_head_bytes(nqb, nkb)), stream));
   const hipError_t e = sparsify_passes(q, k, s, bq, bkv, topk, diagonal, mask, nqb, nkb, chunk, work, stream);
@@ -1165,7 +1204,9 @@ bsa_status bsa_sparsify_topk_noalloc(const void* q, const void* k, const bsa_sha
   int64_t nqb = 0, nkb = 0;
   bsa_status st = sparsify_validate(q, k, shapes, bq, bkv, mask, &nqb, &nkb);
   if (st != BSA_OK) return st;
-  const int64_t per_head = sparsify_head_bytes(nqb, nkb);
+  // the documented limit counts eight bytes a score; what is used is less, but
+  // for the key norms of single rows (the array's last 4096 bytes)
+  const int64_t per_head = (nqb + nkb) * kHeadDim * (int64_t)sizeof(double) + nqb * nkb * (int64_t)sizeof(double);
   if (per_head > kNoAllocScratchBytes)
     return fail(BSA_ERR_INVALID, "one head needs " + std::to_string(per_head) +
                                      " bytes of block means and scores, more than the " +
@@ -1175,8 +1216,8 @@ bsa_status bsa_sparsify_topk_noalloc(const void* q, const void* k, const bsa_sha
   HIP_TRY(hipGetDevice(&dev));
   void* work = nullptr;
   if ((st = scratch_address(dev, &work)) != BSA_OK) return st;
-  const int64_t nbh = (int64_t)s.batch * s.heads;
-  const int64_t chunk = std::max<int64_t>(1, std::min<int64_t>(nbh, kNoAllocScratchBytes / per_head));
+  const int64_t chunk = sparsify_heads_per_pass((int64_t)s.batch * s.heads, kNoAllocScratchBytes,
+                                                sparsify_head_bytes(nqb, nkb));
   // every byte of the scratch that a pass reads is written earlier in the
   // same pass (means before scores, scores before the selection), so nothing
   // needs clearing

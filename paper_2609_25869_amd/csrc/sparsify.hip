@@ -7,102 +7,226 @@
 // largest scores of each row are active (ties to the lower kb), and
 // optionally every block the token diagonal passes through.  The selection
 // is an integer decided by floating point, so the arithmetic is pinned:
-// block sums of bf16 values in IEEE double (exact for these magnitudes), the
-// mean as one double division, and each score accumulated over the head
-// dimension in increasing order with one rounding per multiply and per add
-// (contraction into fused multiply-adds is switched off).  Any
-// implementation that follows the same steps selects the same blocks.
+// block sums of bf16 values in IEEE double in token order, the mean as one
+// double division, and each score accumulated over the head dimension in
+// increasing order with one rounding per multiply and per add (contraction
+// into fused multiply-adds is switched off).  Any implementation that follows
+// the same steps selects the same blocks.
 //
-// Kernels (all HBM- or latency-bound; the attention kernel dominates):
-//   block_mean_kernel    one workgroup per (b, h, block): 128 threads, one per
-//                        head-dim column, sum the block's rows in order
-//   block_score_kernel   64 x 64 score tiles, operand chunks staged in LDS,
-//                        each thread 4 x 4 scores
-//   topk_select_kernel   one workgroup per score row: MSB-first radix select
-//                        of the k-th largest score (8 passes of 8 bits over
-//                        order-preserving 64-bit keys held in LDS), ties ranked
-//                        by column with a workgroup prefix count, coalesced
-//                        write of the mask row with the diagonal added
+// The pinned scores decide, but few of them have to be formed: the matrix
+// units give every score within a proven distance of the pinned one, the
+// selection finds the k-th largest of those, and only columns closer to it
+// than that distance allows to tell apart are scored again in the pinned
+// arithmetic.
+//
+// Kernels (115200 tokens, 24 heads, (64, 64) blocks, k = 216 of 1800; before:
+// fp64 scores of every pair on the vector units and a radix select of 64-bit
+// keys per workgroup):
+//   block_mean_kernel    HBM-bound: the tensors once, 16 bytes per lane and
+//                        row where the layout allows
+//   block_score_kernel   MFMA-bound: fp32 matrix instructions on the means
+//                        rounded to fp32, 128 x 128 or 64 x 64 score tiles
+//   topk_select_kernel   one wave per score row with the row's keys in
+//                        registers: bisection over the keys, counting with
+//                        ballots (VALU-bound; no LDS, no barrier)
 #include "bsa_internal.h"
 
 namespace bsa {
 
 namespace {
 
-__device__ inline double bf16_to_f64(uint16_t b) { return (double)__uint_as_float((uint32_t)b << 16); }
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef double f64x2 __attribute__((ext_vector_type(2)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
-__global__ __launch_bounds__(128) void block_mean_kernel(const uint16_t* x, int64_t s0, int64_t s1, int64_t s2,
-                                                         int32_t H, int32_t n, int32_t blk, int32_t nb, int32_t bh0,
-                                                         double* out) {
-  const int64_t w = blockIdx.x;  // (bh - bh0) * nb + i
-  const int32_t i = (int32_t)(w % nb), bh = bh0 + (int32_t)(w / nb);
-  const int32_t b = bh / H, h = bh - b * H;
-  const int c = threadIdx.x;
-  const uint16_t* p = x + b * s0 + h * s1 + c;
-  const int32_t r0 = i * blk, r1 = min(n, r0 + blk);
-  // rows in increasing order; eight loads go out before their additions
-  double s = 0.0;
-  int32_t r = r0;
-  for (; r + 8 <= r1; r += 8) {
-    double v[8];
+__device__ inline double bf16_to_f64(uint32_t b) { return (double)__uint_as_float(b << 16); }
+
+// Block means of Q and K in one launch.  A thread sums COLS columns of one
+// block over its tokens in order, eight rows' loads in flight: COLS = 8 reads
+// 16 bytes a row (16 lanes a block), COLS = 2 reads 4 bytes (one wave a
+// block), COLS = 1 takes any stride and alignment.
+template <int COLS>
+__device__ inline void load_cols(const uint16_t* p, uint32_t (&v)[COLS]) {
+  if constexpr (COLS == 8) {
+    const u32x4 x = *reinterpret_cast<const u32x4*>(p);
 #pragma unroll
-    for (int j = 0; j < 8; ++j) v[j] = bf16_to_f64(p[(int64_t)(r + j) * s2]);
-#pragma unroll
-    for (int j = 0; j < 8; ++j) s += v[j];
+    for (int j = 0; j < 8; ++j) v[j] = (x[j / 2] >> (16 * (j % 2))) & 0xFFFFu;
+  } else if constexpr (COLS == 2) {
+    const uint32_t x = *reinterpret_cast<const uint32_t*>(p);
+    v[0] = x & 0xFFFFu;
+    v[1] = x >> 16;
+  } else {
+    v[0] = *p;
   }
-  for (; r < r1; ++r) s += bf16_to_f64(p[(int64_t)r * s2]);
-  out[w * kHeadDim + c] = s / (double)(r1 - r0);
 }
 
-constexpr int kST = 64;   // score tile edge
-constexpr int kSC = 32;   // head-dim chunk staged per step
-
-__global__ __launch_bounds__(256) void block_score_kernel(const double* pq, const double* pk, int32_t nqb,
-                                                          int32_t nkb, double* scores) {
-#pragma clang fp contract(off)
-  __shared__ double sq[kST][kSC + 1];
-  __shared__ double sk[kST][kSC + 1];
-  const int64_t bhl = blockIdx.z;
-  const int32_t q0 = blockIdx.y * kST, k0 = blockIdx.x * kST;
-  const int tx = threadIdx.x % 16, ty = threadIdx.x / 16;
-  double acc[4][4];
+template <int COLS>
+__global__ __launch_bounds__(256) void block_mean_kernel(MeanArgs a) {
+  constexpr int kLanes = kHeadDim / COLS;  // threads per block
+  const int64_t w = (int64_t)blockIdx.x * (256 / kLanes) + threadIdx.x / kLanes;
+  const int64_t nq = (int64_t)a.nbh * a.nb[0];
+  if (w >= nq + (int64_t)a.nbh * a.nb[1]) return;
+  const int t = w < nq ? 0 : 1;  // Q blocks first, then K blocks
+  const int64_t wi = t ? w - nq : w;
+  const int32_t nb = a.nb[t], blk = a.blk[t], n = a.n[t];
+  const int32_t i = (int32_t)(wi % nb), bh = a.bh0 + (int32_t)(wi / nb);
+  const int32_t b = bh / a.H, h = bh - b * a.H;
+  const int c = (threadIdx.x % kLanes) * COLS;
+  const int64_t s2 = a.s2[t];
+  const int32_t r0 = i * blk, r1 = min(n, r0 + blk);
+  const uint16_t* p = a.x[t] + b * a.s0[t] + h * a.s1[t] + c + r0 * s2;
+  double s[COLS];
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
+  for (int j = 0; j < COLS; ++j) s[j] = 0.0;
+  int32_t r = r0;
+  for (; r + 8 <= r1; r += 8, p += 8 * s2) {
+    uint32_t v[8][COLS];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) acc[i][j] = 0.0;
+    for (int k = 0; k < 8; ++k) load_cols<COLS>(p + k * s2, v[k]);
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+#pragma unroll
+      for (int j = 0; j < COLS; ++j) s[j] += bf16_to_f64(v[k][j]);
+    }
   }
+  for (; r < r1; ++r, p += s2) {
+    uint32_t v[COLS];
+    load_cols<COLS>(p, v);
+#pragma unroll
+    for (int j = 0; j < COLS; ++j) s[j] += bf16_to_f64(v[j]);
+  }
+  double* out = a.out[t] + wi * kHeadDim + c;
+#pragma unroll
+  for (int j = 0; j < COLS; ++j) out[j] = s[j] / (double)(r1 - r0);
+}
+
+// ---------------------------------------------------------------------------
+// Scores in fp32 on the matrix units.
+//
+// Their distance from the pinned score of a pair is at most kScoreEps * |q|
+// |k| (2-norms of the means): both operands are rounded to fp32 (2^-24 each),
+// 32 products are accumulated at a time (at most 2^-23 of the sum of
+// magnitudes per accumulation, whichever way the unit rounds), and the four
+// partial sums are added (2^-24 each): 70 * 2^-24 in all, and the pinned
+// score itself is within 2^-45.  The sum of magnitudes is at most |q| |k|.
+// Underflow adds nothing that matters while both norms lie in
+// [kNormMin, kNormMax]; other rows take the pinned scores throughout.
+constexpr float kScoreEps = 0x1p-17f;
+constexpr float kNormMin = 0x1p-40f, kNormMax = 0x1p40f;
+
+constexpr int kSC = 32;  // head-dim chunk staged per step
+constexpr int kSP = kSC + 4;  // padded LDS row: 16 rows' 16-byte reads on distinct banks
+
+template <int TILE>
+__global__ __launch_bounds__(256) void block_score_kernel(const double* pq, const double* pk, int32_t nqb,
+                                                          int32_t nkb, float* scores, float* knorm, int32_t nparts) {
+  constexpr int R = TILE / 64;            // 32 x 32 score tiles per wave and side
+  constexpr int kLoads = TILE * kSC / 2 / 256;  // pairs per thread, chunk and operand
+  __shared__ __attribute__((aligned(16))) float sq[TILE * kSP];
+  __shared__ __attribute__((aligned(16))) float sk[TILE * kSP];
+  __shared__ float wave_max[4];
+  const int64_t bhl = blockIdx.z;
+  const int32_t q0 = blockIdx.y * TILE, k0 = blockIdx.x * TILE;
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  const int n = lane & 31, hh = lane >> 5;
+  const int wr = (w >> 1) * 32 * R, wc = (w & 1) * 32 * R;
+  const double* gq = pq + bhl * nqb * kHeadDim;
+  const double* gk = pk + bhl * nkb * kHeadDim;
+  f64x2 lq[kLoads], lk[kLoads];
+  auto fetch = [&](int c0) {
+#pragma unroll
+    for (int i = 0; i < kLoads; ++i) {
+      const int idx = tid + 256 * i, r = idx / (kSC / 2), cc = 2 * (idx % (kSC / 2));
+      lq[i] = q0 + r < nqb ? *reinterpret_cast<const f64x2*>(gq + (int64_t)(q0 + r) * kHeadDim + c0 + cc) : f64x2{0.0, 0.0};
+      lk[i] = k0 + r < nkb ? *reinterpret_cast<const f64x2*>(gk + (int64_t)(k0 + r) * kHeadDim + c0 + cc) : f64x2{0.0, 0.0};
+    }
+  };
+  const bool norms = blockIdx.y == 0;  // the first row of tiles also reports the key norms
+  float sumsq[kLoads];
+#pragma unroll
+  for (int i = 0; i < kLoads; ++i) sumsq[i] = 0.f;
+  f32x16 tot[R][R];
+#pragma unroll
+  for (int i = 0; i < R; ++i) {
+#pragma unroll
+    for (int j = 0; j < R; ++j) tot[i][j] = f32x16{};
+  }
+  fetch(0);
   for (int c0 = 0; c0 < kHeadDim; c0 += kSC) {
-    for (int idx = threadIdx.x; idx < kST * kSC; idx += 256) {
-      const int r = idx / kSC, cc = idx % kSC;
-      sq[r][cc] = (q0 + r < nqb) ? pq[(bhl * nqb + q0 + r) * kHeadDim + c0 + cc] : 0.0;
-      sk[r][cc] = (k0 + r < nkb) ? pk[(bhl * nkb + k0 + r) * kHeadDim + c0 + cc] : 0.0;
+#pragma unroll
+    for (int i = 0; i < kLoads; ++i) {
+      const int idx = tid + 256 * i, r = idx / (kSC / 2), cc = 2 * (idx % (kSC / 2));
+      const f32x2 fq = {(float)lq[i][0], (float)lq[i][1]}, fk = {(float)lk[i][0], (float)lk[i][1]};
+      *reinterpret_cast<f32x2*>(sq + r * kSP + cc) = fq;
+      *reinterpret_cast<f32x2*>(sk + r * kSP + cc) = fk;
+      if (norms) sumsq[i] += fk[0] * fk[0] + fk[1] * fk[1];
     }
     __syncthreads();
-    for (int cc = 0; cc < kSC; ++cc) {
-      double a[4], bv[4];
+    if (c0 + kSC < kHeadDim) fetch(c0 + kSC);
+    f32x16 acc[R][R];
 #pragma unroll
-      for (int i = 0; i < 4; ++i) a[i] = sq[ty + 16 * i][cc];
+    for (int i = 0; i < R; ++i) {
 #pragma unroll
-      for (int j = 0; j < 4; ++j) bv[j] = sk[tx + 16 * j][cc];
+      for (int j = 0; j < R; ++j) acc[i][j] = f32x16{};
+    }
+    // eight head-dim columns per step: the lane halves take four each, one
+    // per matrix instruction (the order inside a chunk is free)
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
+    for (int g = 0; g < kSC / 8; ++g) {
+      f32x4 av[R], bv[R];
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          const double prod = a[i] * bv[j];
-          acc[i][j] = acc[i][j] + prod;
+      for (int i = 0; i < R; ++i) {
+        av[i] = *reinterpret_cast<const f32x4*>(sq + (wr + 32 * i + n) * kSP + 8 * g + 4 * hh);
+        bv[i] = *reinterpret_cast<const f32x4*>(sk + (wc + 32 * i + n) * kSP + 8 * g + 4 * hh);
+      }
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+#pragma unroll
+        for (int i = 0; i < R; ++i) {
+#pragma unroll
+          for (int j = 0; j < R; ++j)
+            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(av[i][e], bv[j][e], acc[i][j], 0, 0, 0);
         }
       }
     }
+#pragma unroll
+    for (int i = 0; i < R; ++i) {
+#pragma unroll
+      for (int j = 0; j < R; ++j) tot[i][j] += acc[i][j];
+    }
     __syncthreads();
   }
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int32_t qb = q0 + ty + 16 * i;
-    if (qb >= nqb) continue;
+  for (int i = 0; i < R; ++i) {
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int32_t kb = k0 + tx + 16 * j;
-      if (kb < nkb) scores[(bhl * nqb + qb) * nkb + kb] = acc[i][j];
+    for (int j = 0; j < R; ++j) {
+      const int32_t kb = k0 + wc + 32 * j + n;
+      if (kb >= nkb) continue;
+#pragma unroll
+      for (int e = 0; e < 16; ++e) {
+        const int32_t qb = q0 + wr + 32 * i + 8 * (e / 4) + 4 * hh + e % 4;
+        if (qb < nqb) scores[(bhl * nqb + qb) * nkb + kb] = tot[i][j][e];
+      }
+    }
+  }
+  if (norms) {
+    // the largest 2-norm of the tile's mean keys
+    float mx = 0.f;
+#pragma unroll
+    for (int i = 0; i < kLoads; ++i) {
+      float v = sumsq[i];
+#pragma unroll
+      for (int o = 1; o < kSC / 2; o <<= 1) v += __shfl_xor(v, o, 64);
+      mx = fmaxf(mx, v);
+    }
+    for (int o = kSC / 2; o < 64; o <<= 1) mx = fmaxf(mx, __shfl_xor(mx, o, 64));
+    if (lane == 0) wave_max[w] = mx;
+    __syncthreads();
+    if (tid == 0) {
+      mx = fmaxf(fmaxf(wave_max[0], wave_max[1]), fmaxf(wave_max[2], wave_max[3]));
+      knorm[bhl * nparts + blockIdx.x] = sqrtf(mx) * 1.0001f;
     }
   }
 }
@@ -126,111 +250,351 @@ __device__ inline uint32_t wave_inclusive_scan(uint32_t x) {
   return x;
 }
 
-__global__ __launch_bounds__(256) void topk_select_kernel(const double* scores, int32_t nqb, int32_t nkb, int32_t k,
-                                                          int32_t diagonal, int32_t nq, int32_t nkv, int32_t bq,
-                                                          int32_t bkv, int32_t bh0, uint8_t* mask) {
-  extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
-  uint64_t* keys = reinterpret_cast<uint64_t*>(smem);
-  uint8_t* take = smem + (size_t)nkb * 8;
+// The same for a float.
+__device__ inline uint32_t order_key32(float x) {
+  if (x == 0.f) x = 0.f;
+  const uint32_t u = __float_as_uint(x);
+  return (u >> 31) ? ~u : (u | 0x80000000u);
+}
+__device__ inline float key32_value(uint32_t k) { return __uint_as_float((k >> 31) ? (k & 0x7FFFFFFFu) : ~k); }
+
+// The pinned score of (mean query row q, mean key row k), by one thread.
+__device__ inline double pinned_score(const double* q, const double* k) {
+#pragma clang fp contract(off)
+  double acc = 0.0;
+  for (int c = 0; c < kHeadDim; ++c) {
+    const double prod = q[c] * k[c];
+    acc = acc + prod;
+  }
+  return acc;
+}
+
+// The same by one wave: the products in parallel, then the sum in order.
+__device__ inline double pinned_score_wave(const double* q, const double* k) {
+#pragma clang fp contract(off)
+  const int lane = threadIdx.x & 63;
+  double acc = 0.0;
+#pragma unroll
+  for (int half = 0; half < kHeadDim; half += 64) {
+    const double prod = q[half + lane] * k[half + lane];
+    const uint64_t u = (uint64_t)__double_as_longlong(prod);
+#pragma unroll 8
+    for (int c = 0; c < 64; ++c) {
+      const uint32_t lo = __builtin_amdgcn_readlane((int)(uint32_t)u, c);
+      const uint32_t hi = __builtin_amdgcn_readlane((int)(uint32_t)(u >> 32), c);
+      acc = acc + __longlong_as_double((long long)((uint64_t)hi << 32 | lo));
+    }
+  }
+  return acc;
+}
+
+// One row in the pinned arithmetic throughout, by the whole workgroup:
+// MSB-first radix select of the k-th largest score (8 passes of 8 bits over
+// order-preserving 64-bit keys in LDS), ties ranked by column with a
+// workgroup prefix count.  Fills take[0 .. nkb).
+__device__ void select_row_pinned(const double* q, const double* pk, int32_t nkb, int32_t k, uint64_t* keys,
+                                  uint8_t* take) {
   __shared__ uint32_t hist[256];
   __shared__ uint32_t chunk_ties[256];
   __shared__ uint64_t s_prefix;
   __shared__ int32_t s_remaining;
   const int tid = threadIdx.x;
-  const int64_t row = blockIdx.x;  // (bh - bh0) * nqb + qb
-  const int32_t qb = (int32_t)(row % nqb);
-  const double* srow = scores + row * nkb;
-  for (int32_t kb = tid; kb < nkb; kb += 256) keys[kb] = order_key(srow[kb]);
+  for (int32_t kb = tid; kb < nkb; kb += 256) keys[kb] = order_key(pinned_score(q, pk + (int64_t)kb * kHeadDim));
   __syncthreads();
-
-  if (k >= nkb || k <= 0) {
-    for (int32_t kb = tid; kb < nkb; kb += 256) take[kb] = k > 0;
-  } else {
-    // k-th largest key: fix one byte per pass from the most significant
-    uint64_t prefix = 0, pmask = 0;
-    int32_t remaining = k;  // rank of the sought key among those matching prefix
-    for (int shift = 56; shift >= 0; shift -= 8) {
-      hist[tid] = 0;
-      __syncthreads();
-      for (int32_t kb = tid; kb < nkb; kb += 256) {
-        const uint64_t key = keys[kb];
-        if ((key & pmask) == prefix) atomicAdd(&hist[(key >> shift) & 255], 1u);
-      }
-      __syncthreads();
-      if (tid < 64) {
-        // digit d of the sought key: the largest d whose keys, counted from
-        // digit 255 down to d, reach `remaining` (d = 0 if none does before).
-        // Lane l holds digits 255-4l .. 252-4l.
-        uint32_t cnt[4], local = 0;
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          cnt[j] = hist[255 - 4 * tid - j];
-          local += cnt[j];
-        }
-        const uint32_t incl = wave_inclusive_scan(local);
-        const uint64_t reach = __ballot(incl >= (uint32_t)remaining || tid == 63);
-        const int first = __builtin_ctzll(reach);
-        if (tid == first) {
-          int32_t above = (int32_t)(incl - local);
-          int d = 255 - 4 * tid;
-#pragma unroll
-          for (int j = 0; j < 4; ++j) {
-            if (d == 0 || above + (int32_t)cnt[j] >= remaining) break;
-            above += (int32_t)cnt[j];
-            --d;
-          }
-          s_remaining = remaining - above;
-          s_prefix = prefix | ((uint64_t)d << shift);
-        }
-      }
-      __syncthreads();
-      remaining = s_remaining;
-      prefix = s_prefix;
-      pmask |= 0xFFull << shift;
+  // k-th largest key: fix one byte per pass from the most significant
+  uint64_t prefix = 0, pmask = 0;
+  int32_t remaining = k;  // rank of the sought key among those matching prefix
+  for (int shift = 56; shift >= 0; shift -= 8) {
+    hist[tid] = 0;
+    __syncthreads();
+    for (int32_t kb = tid; kb < nkb; kb += 256) {
+      const uint64_t key = keys[kb];
+      if ((key & pmask) == prefix) atomicAdd(&hist[(key >> shift) & 255], 1u);
     }
-    // prefix is the k-th largest key; `remaining` of the keys equal to it are
-    // taken, the lowest columns first
-    const int32_t per = (nkb + 255) / 256;
-    const int32_t c0 = min(nkb, tid * per), c1 = min(nkb, c0 + per);
-    uint32_t ties = 0;
-    for (int32_t kb = c0; kb < c1; ++kb) ties += keys[kb] == prefix;
-    chunk_ties[tid] = ties;
     __syncthreads();
     if (tid < 64) {
-      // exclusive prefix over the 256 chunks, four per lane
-      uint32_t t[4], local = 0;
+      // digit d of the sought key: the largest d whose keys, counted from
+      // digit 255 down to d, reach `remaining` (d = 0 if none does before).
+      // Lane l holds digits 255-4l .. 252-4l.
+      uint32_t cnt[4], local = 0;
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
-        t[j] = chunk_ties[4 * tid + j];
-        local += t[j];
+        cnt[j] = hist[255 - 4 * tid - j];
+        local += cnt[j];
       }
-      uint32_t run = wave_inclusive_scan(local) - local;
+      const uint32_t incl = wave_inclusive_scan(local);
+      const uint64_t reach = __ballot(incl >= (uint32_t)remaining || tid == 63);
+      const int first = __builtin_ctzll(reach);
+      if (tid == first) {
+        int32_t above = (int32_t)(incl - local);
+        int d = 255 - 4 * tid;
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        chunk_ties[4 * tid + j] = run;
-        run += t[j];
+        for (int j = 0; j < 4; ++j) {
+          if (d == 0 || above + (int32_t)cnt[j] >= remaining) break;
+          above += (int32_t)cnt[j];
+          --d;
+        }
+        s_remaining = remaining - above;
+        s_prefix = prefix | ((uint64_t)d << shift);
       }
     }
     __syncthreads();
-    int32_t rank = (int32_t)chunk_ties[tid];
-    for (int32_t kb = c0; kb < c1; ++kb) {
-      const uint64_t key = keys[kb];
-      if (key == prefix) {
-        take[kb] = rank < remaining;
-        ++rank;
-      } else {
-        take[kb] = key > prefix;
-      }
+    remaining = s_remaining;
+    prefix = s_prefix;
+    pmask |= 0xFFull << shift;
+  }
+  // prefix is the k-th largest key; `remaining` of the keys equal to it are
+  // taken, the lowest columns first
+  const int32_t per = (nkb + 255) / 256;
+  const int32_t c0 = min(nkb, tid * per), c1 = min(nkb, c0 + per);
+  uint32_t ties = 0;
+  for (int32_t kb = c0; kb < c1; ++kb) ties += keys[kb] == prefix;
+  chunk_ties[tid] = ties;
+  __syncthreads();
+  if (tid < 64) {
+    // exclusive prefix over the 256 chunks, four per lane
+    uint32_t t[4], local = 0;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      t[j] = chunk_ties[4 * tid + j];
+      local += t[j];
+    }
+    uint32_t run = wave_inclusive_scan(local) - local;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      chunk_ties[4 * tid + j] = run;
+      run += t[j];
     }
   }
   __syncthreads();
+  int32_t rank = (int32_t)chunk_ties[tid];
+  for (int32_t kb = c0; kb < c1; ++kb) {
+    const uint64_t key = keys[kb];
+    if (key == prefix) {
+      take[kb] = rank < remaining;
+      ++rank;
+    } else {
+      take[kb] = key > prefix;
+    }
+  }
+  __syncthreads();
+}
+
+// Selection of one score row by one wave.  Lane l holds the row's keys in
+// registers, KPL of them: columns 256 g + 4 l + j in register 4 g + j (VEC:
+// score and mask rows are whole 16- and 4-byte words) or 64 j + l in
+// register j.
+//
+// The k-th largest fp32 score T and the k-th largest pinned score differ by
+// at most the error bound, so columns above T by more than twice the bound
+// are taken, those below T by more than that are not, and the candidates in
+// between (usually T's own column alone) are settled by their pinned scores,
+// ties to the lower column.  Up to 64 of them are scored and ranked by the
+// wave; rows with more, with scores that are not finite, or with norms
+// outside the bound's range go through select_row_pinned.
+constexpr int kSelWaves = 4;
+constexpr int kMaxCand = 64;
+
+template <int KPL, bool VEC>
+__global__ __launch_bounds__(64 * kSelWaves) void topk_select_kernel(SelectArgs a) {
+  extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
+  __shared__ int32_t cand[kSelWaves][kMaxCand];
+  __shared__ uint8_t cand_take[kSelWaves][kMaxCand];
+  __shared__ int32_t unsettled[kSelWaves];
+  constexpr int kG = VEC ? 4 : 1;  // registers of one column group
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  const int64_t row0 = (int64_t)blockIdx.x * kSelWaves;
+  const int32_t nkb = a.nkb;
+  auto column = [&](int j) { return VEC ? 256 * (j / 4) + 4 * lane + j % 4 : 64 * j + lane; };
   // the diagonal: columns [lo / bkv, (hi - 1) / bkv] for the row's tokens
   // [lo, hi) that also exist as keys
-  const int32_t lo = qb * bq, hi = min(min(nq, nkv), lo + bq);
-  const int32_t d0 = (diagonal && lo < hi) ? lo / bkv : 1, d1 = (diagonal && lo < hi) ? (hi - 1) / bkv : 0;
-  uint8_t* out = mask + ((int64_t)bh0 * nqb + row) * nkb;
-  for (int32_t kb = tid; kb < nkb; kb += 256) out[kb] = (take[kb] || (kb >= d0 && kb <= d1)) ? 1 : 0;
+  auto diagonal = [&](int64_t r, int32_t* d0, int32_t* d1) {
+    const int32_t qb = (int32_t)(r % a.nqb);
+    const int32_t lo = qb * a.bq, hi = min(min(a.nq, a.nkv), lo + a.bq);
+    const bool any = a.diagonal && lo < hi;
+    *d0 = any ? lo / a.bkv : 1;
+    *d1 = any ? (hi - 1) / a.bkv : 0;
+  };
+  auto mask_row = [&](int64_t r) { return a.mask + ((int64_t)a.bh0 * a.nqb + r) * nkb; };
+
+  // one row; false if it has to go through the pinned arithmetic
+  auto select = [&](int64_t row) -> bool {
+    int32_t d0, d1;
+    diagonal(row, &d0, &d1);
+    uint8_t* out = mask_row(row);
+    if (a.k <= 0 || a.k >= nkb) {
+      for (int32_t c = lane; c < nkb; c += 64) out[c] = (a.k > 0 || (c >= d0 && c <= d1)) ? 1 : 0;
+      return true;
+    }
+    const int64_t bhl = row / a.nqb;
+    const double* q = a.pq + row * kHeadDim;
+    const double* pk = a.pk + bhl * nkb * kHeadDim;
+    const float* srow = a.scores + row * nkb;
+    uint32_t key[KPL];  // 0 past the row's end, below every finite score's key
+    bool finite = true;
+#pragma unroll
+    for (int g = 0; g < KPL; g += kG) {
+      float x[kG];
+      const bool in = column(g) < nkb;
+      if constexpr (VEC) {
+        const f32x4 v = in ? *reinterpret_cast<const f32x4*>(srow + column(g)) : f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int j = 0; j < kG; ++j) x[j] = v[j];
+      } else {
+        x[0] = in ? srow[column(g)] : 0.f;
+      }
+#pragma unroll
+      for (int j = 0; j < kG; ++j) {
+        finite = finite && (__float_as_uint(x[j]) & 0x7F800000u) != 0x7F800000u;
+        key[g + j] = in ? order_key32(x[j]) : 0u;
+      }
+    }
+    // norms: |q| of the row, the largest |k| of the head
+    const double q0 = q[lane], q1 = q[64 + lane];
+    float qn = (float)(q0 * q0 + q1 * q1), kn = 0.f;
+    for (int32_t i = lane; i < a.nparts; i += 64) kn = fmaxf(kn, a.knorm[bhl * a.nparts + i]);
+    uint32_t lo = 0xFFFFFFFFu, hi = 0u;
+#pragma unroll
+    for (int j = 0; j < KPL; ++j) {
+      hi = max(hi, key[j]);
+      lo = min(lo, key[j] == 0u ? 0xFFFFFFFFu : key[j]);
+    }
+    for (int o = 32; o > 0; o >>= 1) {
+      hi = max(hi, (uint32_t)__shfl_xor((int)hi, o, 64));
+      lo = min(lo, (uint32_t)__shfl_xor((int)lo, o, 64));
+      qn += __shfl_xor(qn, o, 64);
+      kn = fmaxf(kn, __shfl_xor(kn, o, 64));
+    }
+    qn = sqrtf(qn) * 1.0001f;
+    const bool zero = __ballot(q0 != 0.0 || q1 != 0.0) == 0;  // then every finite score is exactly 0
+    const bool in_range = qn >= kNormMin && qn <= kNormMax && kn >= kNormMin && kn <= kNormMax;
+    if (__ballot(!finite) != 0 || !(in_range || zero)) return false;
+
+    auto count_ge = [&](uint32_t t) -> int32_t {
+      int32_t c = 0;
+#pragma unroll
+      for (int j = 0; j < KPL; ++j) c += __popcll(__ballot(key[j] >= t));
+      return c;
+    };
+    // T: the largest key with at least k keys >= it, by bisection
+    lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)lo);
+    hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)hi);
+    while (lo < hi) {
+      const uint32_t mid = lo + ((hi - lo) >> 1) + ((hi - lo) & 1u);
+      const int32_t c = count_ge(mid);
+      if (c > a.k) {
+        lo = mid;
+      } else if (c < a.k) {
+        hi = mid - 1u;
+      } else {  // exactly k: T is the smallest of them
+        uint32_t t = 0xFFFFFFFFu;
+#pragma unroll
+        for (int j = 0; j < KPL; ++j) t = min(t, key[j] >= mid ? key[j] : 0xFFFFFFFFu);
+        for (int o = 32; o > 0; o >>= 1) t = min(t, (uint32_t)__shfl_xor((int)t, o, 64));
+        lo = hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)t);
+      }
+    }
+    const float T = key32_value(lo);
+    // twice the bound, and more than the rounding of the two sums below
+    const float reach = zero ? 0.f : (2.f * kScoreEps + 0x1p-21f) * qn * kn;
+    const uint32_t from = order_key32(T - reach), to = order_key32(T + reach);
+    const int32_t sure = count_ge(to + 1u);
+    const int32_t need = a.k - sure, m = count_ge(from) - sure;  // of m candidates, `need` are taken
+
+    // candidate bits of one group's registers and the number of candidates
+    // before this lane's first in column order; `base` counts on
+    auto group = [&](int g, int32_t& base, uint64_t (&bits)[kG]) -> int32_t {
+      const uint64_t under = lane == 0 ? 0ull : (~0ull >> (64 - lane));
+      int32_t pos = base;
+#pragma unroll
+      for (int j = 0; j < kG; ++j) {
+        bits[j] = __ballot(key[g + j] >= from && key[g + j] <= to);
+        pos += __popcll(bits[j] & under);
+        base += __popcll(bits[j]);
+      }
+      return pos;
+    };
+    const bool by_column = need >= m || zero;  // all, or equal scores: the lowest columns
+    if (!by_column) {
+      if (m > kMaxCand) return false;
+      int32_t base = 0;
+#pragma unroll
+      for (int g = 0; g < KPL; g += kG) {
+        uint64_t bits[kG];
+        int32_t pos = group(g, base, bits);
+#pragma unroll
+        for (int j = 0; j < kG; ++j)
+          if ((bits[j] >> lane) & 1ull) cand[wv][pos++] = column(g + j);
+      }
+      __builtin_amdgcn_wave_barrier();
+      uint64_t mine = 0;  // lane i: candidate i's pinned score
+      for (int32_t i = 0; i < m; ++i) {
+        const int32_t c = __builtin_amdgcn_readfirstlane(cand[wv][i]);
+        const uint64_t s = order_key(pinned_score_wave(q, pk + (int64_t)c * kHeadDim));
+        if (lane == i) mine = s;
+      }
+      int32_t rank = 0;
+      for (int32_t i = 0; i < m; ++i) {
+        const uint64_t other = (uint64_t)__shfl((unsigned long long)mine, i, 64);
+        rank += (other > mine || (other == mine && i < lane)) ? 1 : 0;
+      }
+      if (lane < m) cand_take[wv][lane] = rank < need ? 1 : 0;
+      __builtin_amdgcn_wave_barrier();
+    }
+    int32_t base = 0;
+#pragma unroll
+    for (int g = 0; g < KPL; g += kG) {
+      uint64_t bits[kG];
+      int32_t pos = group(g, base, bits);
+      uint32_t word = 0;
+#pragma unroll
+      for (int j = 0; j < kG; ++j) {
+        const int32_t c = column(g + j);
+        bool take = key[g + j] > to;
+        if ((bits[j] >> lane) & 1ull) {
+          take = by_column ? pos < need : cand_take[wv][pos] != 0;
+          ++pos;
+        }
+        word |= (take || (c >= d0 && c <= d1) ? 1u : 0u) << (8 * j);
+      }
+      if (column(g) < nkb) {
+        if constexpr (VEC) *reinterpret_cast<uint32_t*>(out + column(g)) = word;
+        else out[column(g)] = (uint8_t)word;
+      }
+    }
+    return true;
+  };
+
+  const bool settled = row0 + wv >= a.rows || select(row0 + wv);
+  if (lane == 0) unsettled[wv] = settled ? 0 : 1;
+  __syncthreads();
+  for (int w = 0; w < kSelWaves; ++w) {
+    if (!unsettled[w]) continue;
+    const int64_t row = row0 + w;
+    uint64_t* keys = reinterpret_cast<uint64_t*>(smem);
+    uint8_t* take = smem + (size_t)nkb * 8;
+    select_row_pinned(a.pq + row * kHeadDim, a.pk + row / a.nqb * nkb * kHeadDim, nkb, a.k, keys, take);
+    int32_t d0, d1;
+    diagonal(row, &d0, &d1);
+    uint8_t* out = mask_row(row);
+    for (int32_t kb = tid; kb < nkb; kb += 64 * kSelWaves) out[kb] = (take[kb] || (kb >= d0 && kb <= d1)) ? 1 : 0;
+    __syncthreads();
+  }
 }
+
+template <int KPL>
+hipError_t launch_select(const SelectArgs& a, hipStream_t s) {
+  const bool vec = a.nkb % 4 == 0 && (reinterpret_cast<uintptr_t>(a.scores) & 15) == 0 &&
+                   (reinterpret_cast<uintptr_t>(a.mask) & 3) == 0;
+  const dim3 grid((unsigned)((a.rows + kSelWaves - 1) / kSelWaves)), block(64 * kSelWaves);
+  const size_t lds = (size_t)a.nkb * 9;  // the pinned path's keys and flags
+  if (vec) hipLaunchKernelGGL((topk_select_kernel<KPL, true>), grid, block, lds, s, a);
+  else hipLaunchKernelGGL((topk_select_kernel<KPL, false>), grid, block, lds, s, a);
+  return hipGetLastError();
+}
+
+// Score tiles of 128 x 128 leave the chip idle below two workgroups per CU.
+constexpr int64_t kBigTileMin = 512;
 
 }  // namespace
 
@@ -238,32 +602,51 @@ __global__ __launch_bounds__(256) void topk_select_kernel(const double* scores, 
 // stay within 64 KB of LDS
 int32_t sparsify_max_kv_blocks() { return 6144; }
 
-hipError_t launch_block_mean(const uint16_t* x, int64_t s0, int64_t s1, int64_t s2, int32_t H, int32_t n,
-                             int32_t blk, int32_t bh0, int32_t nbh, double* out, hipStream_t s) {
-  const int32_t nb = (n + blk - 1) / blk;
-  const int64_t grid = (int64_t)nbh * nb;
-  if (grid == 0) return hipSuccess;
-  hipLaunchKernelGGL(block_mean_kernel, dim3((unsigned)grid), dim3(128), 0, s, x, s0, s1, s2, H, n, blk, nb, bh0,
-                     out);
+hipError_t launch_block_mean(const MeanArgs& a, hipStream_t s) {
+  const int64_t blocks = (int64_t)a.nbh * (a.nb[0] + (int64_t)a.nb[1]);
+  if (blocks == 0) return hipSuccess;
+  uint64_t mis = 0;
+  for (int t = 0; t < 2; ++t)
+    mis |= reinterpret_cast<uintptr_t>(a.x[t]) | (uint64_t)(2 * a.s0[t]) | (uint64_t)(2 * a.s1[t]) | (uint64_t)(2 * a.s2[t]);
+  // 16 bytes a row while that leaves at least two waves per SIMD (four blocks
+  // a wave), else one block a wave with 4 bytes a row
+  const int cols = (mis & 15) == 0 && blocks >= 8192 ? 8 : (mis & 3) == 0 ? 2 : 1;
+  const int per = 256 * cols / kHeadDim;  // blocks per workgroup
+  const dim3 grid((unsigned)((blocks + per - 1) / per)), block(256);
+  if (cols == 8) hipLaunchKernelGGL(block_mean_kernel<8>, grid, block, 0, s, a);
+  else if (cols == 2) hipLaunchKernelGGL(block_mean_kernel<2>, grid, block, 0, s, a);
+  else hipLaunchKernelGGL(block_mean_kernel<1>, grid, block, 0, s, a);
   return hipGetLastError();
 }
+
+namespace {
+int score_tile(int32_t nqb, int32_t nkb, int32_t nbh) {
+  const int64_t big = (int64_t)((nqb + 127) / 128) * ((nkb + 127) / 128) * nbh;
+  return big >= kBigTileMin ? 128 : 64;
+}
+}  // namespace
+
+int32_t sparsify_norm_parts(int32_t nkb) { return (nkb + 63) / 64; }
 
 hipError_t launch_block_scores(const double* pq, const double* pk, int32_t nqb, int32_t nkb, int32_t nbh,
-                               double* scores, hipStream_t s) {
-  const dim3 grid((unsigned)((nkb + kST - 1) / kST), (unsigned)((nqb + kST - 1) / kST), (unsigned)nbh);
-  hipLaunchKernelGGL(block_score_kernel, grid, dim3(256), 0, s, pq, pk, nqb, nkb, scores);
+                               float* scores, float* knorm, int32_t* nparts, hipStream_t s) {
+  const int tile = score_tile(nqb, nkb, nbh);
+  const dim3 grid((unsigned)((nkb + tile - 1) / tile), (unsigned)((nqb + tile - 1) / tile), (unsigned)nbh);
+  *nparts = (int32_t)grid.x;
+  if (tile == 128)
+    hipLaunchKernelGGL(block_score_kernel<128>, grid, dim3(256), 0, s, pq, pk, nqb, nkb, scores, knorm, *nparts);
+  else
+    hipLaunchKernelGGL(block_score_kernel<64>, grid, dim3(256), 0, s, pq, pk, nqb, nkb, scores, knorm, *nparts);
   return hipGetLastError();
 }
 
-hipError_t launch_topk_select(const double* scores, int32_t nqb, int32_t nkb, int32_t k, int32_t diagonal,
-                              int32_t nq, int32_t nkv, int32_t bq, int32_t bkv, int32_t bh0, int32_t nbh,
-                              uint8_t* mask, hipStream_t s) {
-  const int64_t rows = (int64_t)nbh * nqb;
-  if (rows == 0) return hipSuccess;
-  const size_t lds = (size_t)nkb * 9;
-  hipLaunchKernelGGL(topk_select_kernel, dim3((unsigned)rows), dim3(256), lds, s, scores, nqb, nkb, k, diagonal, nq,
-                     nkv, bq, bkv, bh0, mask);
-  return hipGetLastError();
+hipError_t launch_topk_select(const SelectArgs& a, hipStream_t s) {
+  if (a.rows == 0) return hipSuccess;
+  if (a.nkb <= 64 * 8) return launch_select<8>(a, s);
+  if (a.nkb <= 64 * 16) return launch_select<16>(a, s);
+  if (a.nkb <= 64 * 32) return launch_select<32>(a, s);
+  if (a.nkb <= 64 * 64) return launch_select<64>(a, s);
+  return launch_select<96>(a, s);
 }
 
 }  // namespace bsa
