@@ -48,8 +48,10 @@ struct MaskStateArgs {
   int32_t* runs;            // [R]   (count pass) active blocks of the row in runs of length >= 2
   const RowChunk* chunks;   // [nchunks] (count pass) reduction ranges
   int32_t nchunks;
+  int64_t* chunk_sum;       // [nchunks] (count pass) active blocks of each chunk
   const int64_t* row_ptr;   // [R+1] (fill pass)
   int32_t* col_idx;         // [nnz] (fill pass)
+  uint64_t* row_hash;       // [R] (fill pass, may be null) see RowHash in plan_kernels.hip
   SegStats* seg_stats;      // [nseg]
   unsigned long long* bh_nnz;  // [B*H]
   int32_t wide;             // every mask row starts 4-byte aligned and nkb % 4 == 0
@@ -76,6 +78,10 @@ struct MapArgs {
   const int64_t* tile_ptr2;  // fill pass
   int32_t* tile_kv2;
   uint64_t* member2;         // may be null
+  // Fill pass, plans without Split-K (null: none): the row's task, and the
+  // hash of its list for the dispatch order.
+  Task* tasks;
+  uint64_t* row_hash;
   int32_t wide;              // mask rows 4-byte aligned and nkb % 4 == 0 (see MaskStateArgs)
 };
 
@@ -113,6 +119,20 @@ struct OrderArgs {
   size_t temp_bytes;
 };
 
+// The same order for plans without Split-K, whose tasks are the physical rows
+// ((b, head) by (b, head), npq rows each), from the rows' list hashes.
+struct RowOrderArgs {
+  const uint64_t* row_hash;   // by segment row, or (direct) by logical row
+  const int64_t* row_base;    // logical row base per (b, h); used when direct
+  const int32_t* seg_heads;
+  int32_t nsh, H, npq, direct;
+  int32_t nbh;                // (b, head) pairs of the segment
+  const Task* tasks;
+  int32_t* order;             // out
+  Task* tasks_out;            // out: tasks[order[i]] at i
+};
+constexpr int32_t kRowOrderMax = 2048;  // most rows per (b, head)
+
 struct AttnArgs {
   const Task* tasks;
   int32_t ntasks;              // exact count, or an upper bound when ntasks_dev is set
@@ -144,6 +164,9 @@ struct AttnArgs {
 // Kernel launchers (defined in the .hip files).
 hipError_t launch_mask_count(const MaskStateArgs& a, hipStream_t s);
 hipError_t launch_mask_fill(const MaskStateArgs& a, hipStream_t s);
+hipError_t launch_mask_scan(const MaskStateArgs& a, int64_t* row_ptr, int64_t* scan_tmp, int32_t nseg,
+                            unsigned long long* stats_host, hipStream_t s);
+hipError_t launch_row_order(const RowOrderArgs& a, hipStream_t s);
 hipError_t launch_scan_i32(const int32_t* in, int64_t* out, int64_t n, int64_t* block_tmp, hipStream_t s);
 int64_t scan_tmp_elems(int64_t n);
 hipError_t launch_map_count(const MapArgs& a, hipStream_t s);

@@ -23,6 +23,29 @@ __device__ inline int find_bh(const int64_t* row_base, int nbh, int64_t r) {
   return lo;
 }
 
+// Row hashes.  Rows get equal hashes if their lists of (column, member bits)
+// are equal, and otherwise different ones but for collisions of a 64-bit
+// hash, which can only cost locality in the dispatch order.  A list is in
+// column order, so the sum of its entries' hashes stands for it.
+struct RowHash {
+  // SplitMix64 finaliser (Steele, Lea and Flood, "Fast splittable
+  // pseudorandom number generators", OOPSLA 2014)
+  __device__ static uint64_t mix64(uint64_t z) {
+    z = (z ^ (z >> 30)) * 0xbf58476d1ce4e5b9ull;
+    z = (z ^ (z >> 27)) * 0x94d049bb133111ebull;
+    return z ^ (z >> 31);
+  }
+  uint64_t h = 0;
+  __device__ void add(int column, uint64_t members) {
+    h += mix64(members + 0x9e3779b97f4a7c15ull * (uint64_t)(column + 1));
+  }
+  __device__ uint64_t wave_total() const {
+    uint64_t t = h;
+    for (int off = 32; off > 0; off >>= 1) t += (uint64_t)__shfl_xor((unsigned long long)t, off, 64);
+    return mix64(t);
+  }
+};
+
 __device__ inline uint64_t lanes_below(int lane) { return (lane == 0) ? 0ull : ((~0ull) >> (64 - lane)); }
 
 // Logical rows read as 32-bit words, for masks whose rows are 4-byte
@@ -38,6 +61,7 @@ __device__ inline void mask_row_words(const MaskStateArgs& a, const uint8_t* row
   const uint32_t* row32 = reinterpret_cast<const uint32_t*>(row);
   const int nw = nkb >> 2;
   int64_t nnz = 0, run = 0;
+  RowHash hash;
   uint64_t carry = 0;  // activity of the column just before the current step
   for (int w00 = 0; w00 < nw; w00 += 64 * kWordSteps) {
     // the loads of kWordSteps steps (clamped addresses, none behind a branch)
@@ -60,7 +84,10 @@ __device__ inline void mask_row_words(const MaskStateArgs& a, const uint8_t* row
                       __popcll(bb[2] & below) + __popcll(bb[3] & below);
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-          if ((bb[j] >> lane) & 1ull) a.col_idx[pos++] = 4 * wi + j;
+          if ((bb[j] >> lane) & 1ull) {
+            a.col_idx[pos++] = 4 * wi + j;
+            if (a.row_hash) hash.add(4 * wi + j, 1);
+          }
         }
       } else {
         // the first column after this step: byte 0 of the next step's lane 0
@@ -83,6 +110,10 @@ __device__ inline void mask_row_words(const MaskStateArgs& a, const uint8_t* row
     a.counts[r] = (int32_t)nnz;
     a.runs[r] = (int32_t)run;
   }
+  if (kFill && a.row_hash) {
+    const uint64_t t = hash.wave_total();
+    if (lane == 0) a.row_hash[r] = t;
+  }
 }
 
 // Logical rows: count (with statistics) or fill the block-CSR columns.
@@ -102,13 +133,17 @@ __global__ __launch_bounds__(256) void mask_rows_kernel(MaskStateArgs a) {
     return;
   }
   int64_t nnz = 0, run = 0;
+  RowHash hash;
   uint64_t carry = 0;  // activity of the column just before the current step
   for (int c0 = 0; c0 < hd.nkb; c0 += 64) {
     const int c = c0 + lane;
     const bool act = (c < hd.nkb) && row[c] != 0;
     const uint64_t bits = __ballot(act);
     if (kFill) {
-      if (act) a.col_idx[out_base + nnz + __popcll(bits & lanes_below(lane))] = c;
+      if (act) {
+        a.col_idx[out_base + nnz + __popcll(bits & lanes_below(lane))] = c;
+        if (a.row_hash) hash.add(c, 1);
+      }
     } else {
       const uint64_t next = (c0 + 64 < hd.nkb && row[c0 + 64] != 0) ? 1ull : 0ull;
       const uint64_t left = (bits << 1) | carry;        // column c-1 active
@@ -121,6 +156,10 @@ __global__ __launch_bounds__(256) void mask_rows_kernel(MaskStateArgs a) {
   if (!kFill && lane == 0) {
     a.counts[r] = (int32_t)nnz;
     a.runs[r] = (int32_t)run;
+  }
+  if (kFill && a.row_hash) {
+    const uint64_t t = hash.wave_total();
+    if (lane == 0) a.row_hash[r] = t;
   }
 }
 
@@ -158,6 +197,7 @@ __global__ __launch_bounds__(kStatThreads) void row_stats_kernel(MaskStateArgs a
       run += part[1][i];
       mx = part[2][i] > mx ? part[2][i] : mx;
     }
+    a.chunk_sum[blockIdx.x] = (int64_t)nnz;
     SegStats* st = a.seg_stats + ch.seg;
     atomicAdd(&st->nnz, nnz);
     atomicAdd(&st->run_blocks, run);
@@ -167,14 +207,22 @@ __global__ __launch_bounds__(kStatThreads) void row_stats_kernel(MaskStateArgs a
 }
 
 // ---------------------------------------------------------------------------
-// Exclusive scan int32 -> int64 with the total in out[n]; three passes:
-// per-block sums, a one-block scan of those sums, per-block rescans.
+// Exclusive scan int32 -> int64 with the total in out[n].  These scans are
+// bound by launches and latency, not by their bytes: up to kScanOneBlock
+// elements (8 per thread) one workgroup does it all in 3 to 8 us (21600
+// elements would take it 24 us, the two launches below 10), beyond that per-block sums and per-block rescans, where every
+// block adds up the sums before its own; above kScanSelfSum blocks a scan of
+// the sums comes in between.
 constexpr int kScanThreads = 256;
 constexpr int kScanItems = 8;
 constexpr int kScanTile = kScanThreads * kScanItems;
+constexpr int kScanBig = 1024;             // threads of the one-workgroup scan
+constexpr int64_t kScanOneBlock = 8192;
+constexpr int64_t kScanSelfSum = 4096;
 
+template <int THREADS>
 __device__ inline int64_t block_exclusive_scan(int64_t x, int64_t* total) {
-  __shared__ int64_t wsum[kScanThreads / 64];
+  __shared__ int64_t wsum[THREADS / 64];
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   int64_t incl = x;
   for (int off = 1; off < 64; off <<= 1) {
@@ -184,7 +232,7 @@ __device__ inline int64_t block_exclusive_scan(int64_t x, int64_t* total) {
   if (lane == 63) wsum[w] = incl;
   __syncthreads();
   int64_t before = 0, all = 0;
-  for (int i = 0; i < kScanThreads / 64; ++i) {
+  for (int i = 0; i < THREADS / 64; ++i) {
     if (i < w) before += wsum[i];
     all += wsum[i];
   }
@@ -193,13 +241,52 @@ __device__ inline int64_t block_exclusive_scan(int64_t x, int64_t* total) {
   return before + incl - x;
 }
 
+// Sum of x[0 .. n) in every thread.
+__device__ inline int64_t block_prefix_sum(const int64_t* x, int64_t n) {
+  int64_t s = 0, total;
+  for (int64_t i = threadIdx.x; i < n; i += kScanThreads) s += x[i];
+  (void)block_exclusive_scan<kScanThreads>(s, &total);
+  return total;
+}
+
+// Exclusive scan of in[begin .. end) (at most THREADS * kScanItems elements)
+// from `start`; returns the total.
+template <int THREADS>
+__device__ inline int64_t scan_range(const int32_t* in, int64_t begin, int64_t end, int64_t start, int64_t* out) {
+  const int64_t base = begin + (int64_t)threadIdx.x * kScanItems;
+  int64_t v[kScanItems];
+  int64_t s = 0;
+#pragma unroll
+  for (int i = 0; i < kScanItems; ++i) {
+    v[i] = (base + i < end) ? in[base + i] : 0;
+    s += v[i];
+  }
+  int64_t total;
+  int64_t run = start + block_exclusive_scan<THREADS>(s, &total);
+#pragma unroll
+  for (int i = 0; i < kScanItems; ++i) {
+    if (base + i < end) out[base + i] = run;
+    run += v[i];
+  }
+  return total;
+}
+
+__global__ __launch_bounds__(kScanBig) void scan_one_block(const int32_t* in, int64_t n, int64_t* out) {
+  int64_t carry = 0;
+  for (int64_t base = 0; base < n; base += (int64_t)kScanBig * kScanItems) {
+    const int64_t end = base + (int64_t)kScanBig * kScanItems < n ? base + (int64_t)kScanBig * kScanItems : n;
+    carry += scan_range<kScanBig>(in, base, end, carry, out);
+  }
+  if (threadIdx.x == 0) out[n] = carry;
+}
+
 __global__ __launch_bounds__(kScanThreads) void scan_block_sums(const int32_t* in, int64_t n, int64_t* sums) {
   const int64_t base = (int64_t)blockIdx.x * kScanTile + threadIdx.x * kScanItems;
   int64_t s = 0;
   for (int i = 0; i < kScanItems; ++i)
     if (base + i < n) s += in[base + i];
   int64_t total;
-  (void)block_exclusive_scan(s, &total);
+  (void)block_exclusive_scan<kScanThreads>(s, &total);
   if (threadIdx.x == 0) sums[blockIdx.x] = total;
 }
 
@@ -209,28 +296,45 @@ __global__ __launch_bounds__(kScanThreads) void scan_sums(int64_t* sums, int64_t
     const int64_t i = base + threadIdx.x;
     const int64_t x = i < nblocks ? sums[i] : 0;
     int64_t total;
-    const int64_t ex = block_exclusive_scan(x, &total);
+    const int64_t ex = block_exclusive_scan<kScanThreads>(x, &total);
     if (i < nblocks) sums[i] = carry + ex;
     carry += total;
   }
 }
 
+// kScanned: sums holds the scanned block sums, else the sums themselves.
+template <bool kScanned>
 __global__ __launch_bounds__(kScanThreads) void scan_apply(const int32_t* in, int64_t n, const int64_t* sums,
                                                            int64_t* out) {
-  const int64_t base = (int64_t)blockIdx.x * kScanTile + threadIdx.x * kScanItems;
-  int64_t v[kScanItems];
-  int64_t s = 0;
-  for (int i = 0; i < kScanItems; ++i) {
-    v[i] = (base + i < n) ? in[base + i] : 0;
-    s += v[i];
-  }
-  int64_t total;
-  int64_t run = sums[blockIdx.x] + block_exclusive_scan(s, &total);
-  for (int i = 0; i < kScanItems; ++i) {
-    if (base + i < n) out[base + i] = run;
-    run += v[i];
-  }
-  if (base < n && base + kScanItems >= n) out[n] = run;  // the thread holding the last element
+  const int64_t start = kScanned ? sums[blockIdx.x] : block_prefix_sum(sums, blockIdx.x);
+  const int64_t begin = (int64_t)blockIdx.x * kScanTile, end = begin + kScanTile < n ? begin + kScanTile : n;
+  const int64_t total = scan_range<kScanThreads>(in, begin, end, start, out);
+  if (threadIdx.x == 0 && end == n) out[n] = start + total;
+}
+
+// Block-CSR offsets from the row counts and the chunks' sums (row_stats_kernel),
+// one workgroup per chunk; the first one also writes the statistics to the
+// host's pinned buffer, segment statistics and then the per-(b, h) counts.
+static_assert(kScanTile == 2048, "a row chunk fits one scan");
+
+__device__ inline void write_stats(const MaskStateArgs& a, int32_t nseg, unsigned long long* host) {
+  const unsigned long long* st = reinterpret_cast<const unsigned long long*>(a.seg_stats);
+  const int ns = nseg * (int)(sizeof(SegStats) / 8);
+  for (int i = threadIdx.x; i < ns + a.nbh; i += blockDim.x) host[i] = i < ns ? st[i] : a.bh_nnz[i - ns];
+}
+
+__global__ __launch_bounds__(kScanThreads) void mask_scan_kernel(MaskStateArgs a, int64_t* row_ptr, int32_t nseg,
+                                                                 unsigned long long* host) {
+  const RowChunk ch = a.chunks[blockIdx.x];
+  const int64_t start = block_prefix_sum(a.chunk_sum, blockIdx.x);
+  const int64_t total = scan_range<kScanThreads>(a.counts, ch.begin, ch.end, start, row_ptr);
+  if (threadIdx.x == 0 && ch.end == a.R) row_ptr[a.R] = start + total;
+  if (blockIdx.x == 0) write_stats(a, nseg, host);
+}
+
+__global__ __launch_bounds__(kScanThreads) void write_stats_kernel(MaskStateArgs a, int32_t nseg,
+                                                                   unsigned long long* host) {
+  write_stats(a, nseg, host);
 }
 
 __global__ void zero_i64(int64_t* out) {
@@ -283,6 +387,16 @@ __global__ __launch_bounds__(256) void map_rows_kernel(MapArgs a) {
   const bool compact = kFill ? a.tile_ptr2 != nullptr : a.counts2 != nullptr;
   const int64_t out_base2 = kFill && compact ? a.tile_ptr2[rp] : 0;
   int64_t n = 0, n2 = 0;
+  RowHash hash;
+  if (kFill && a.tasks && lane == 0) {
+    const int64_t* ptr = compact ? a.tile_ptr2 : a.tile_ptr;
+    a.tasks[rp] = Task{b * a.H + h, pq, (int32_t)ptr[rp], (int32_t)ptr[rp + 1], 0, 1, 0, 0};
+  }
+  auto store_hash = [&]() {
+    if (!kFill || !a.row_hash) return;
+    const uint64_t t = hash.wave_total();
+    if (lane == 0) a.row_hash[rp] = t;
+  };
   if ((a.gkv == 2 || a.gkv == 4) && a.wide) {
     // Two or four blocks along KV per tile, word-aligned rows: a lane's word
     // holds four blocks, i.e. two tiles (gkv = 2) or one (gkv = 4); mem[j]
@@ -323,6 +437,7 @@ __global__ __launch_bounds__(256) void map_rows_kernel(MapArgs a) {
           if (tile[j] != 0) {
             a.tile_kv[pos] = per * wi + j;
             if (a.member) a.member[pos] = tile[j];
+            if (a.row_hash) hash.add(per * wi + j, tile[j]);
             ++pos;
           }
         }
@@ -351,6 +466,7 @@ __global__ __launch_bounds__(256) void map_rows_kernel(MapArgs a) {
       a.counts[rp] = (int32_t)n;
       if (compact) a.counts2[rp] = (int32_t)n2;
     }
+    store_hash();
     return;
   }
   if (a.gkv == 1 && a.wide) {
@@ -405,6 +521,7 @@ __global__ __launch_bounds__(256) void map_rows_kernel(MapArgs a) {
               a.tile_kv[pos + mine + s2] = kb * a.rkv + s2;
               if (a.member) a.member[pos + mine + s2] = mem[j];
             }
+            if (a.row_hash) hash.add(kb, mem[j]);
           }
           mine += nt;
         }
@@ -414,6 +531,7 @@ __global__ __launch_bounds__(256) void map_rows_kernel(MapArgs a) {
            (last_active ? deficit : 0);
     }
     if (!kFill && lane == 0) a.counts[rp] = (int32_t)n;
+    store_hash();
     return;
   }
   if (a.gq == 1 && a.gkv == 1) {
@@ -437,11 +555,13 @@ __global__ __launch_bounds__(256) void map_rows_kernel(MapArgs a) {
           const int64_t pos = out_base + n + __popcll(ball & lanes_below(lane));
           a.tile_kv[pos] = p00 + 64 * j + lane;
           if (a.member) a.member[pos] = 1ull;
+          if (a.row_hash) hash.add(p00 + 64 * j + lane, 1);
         }
         n += __popcll(ball);
       }
     }
     if (!kFill && lane == 0) a.counts[rp] = (int32_t)n;
+    store_hash();
     return;
   }
   for (int p0 = 0; p0 < a.npk; p0 += 64) {
@@ -468,6 +588,7 @@ __global__ __launch_bounds__(256) void map_rows_kernel(MapArgs a) {
       const int64_t pos = out_base + n + __popcll(ball & lanes_below(lane));
       a.tile_kv[pos] = pk;
       if (a.member) a.member[pos] = bits;
+      if (a.row_hash) hash.add(pk, bits);
     }
     n += __popcll(ball);
     if (compact) {  // gkv == 2: member (a, c) is bit 2 a + c
@@ -495,6 +616,7 @@ __global__ __launch_bounds__(256) void map_rows_kernel(MapArgs a) {
     a.counts[rp] = (int32_t)n;
     if (compact) a.counts2[rp] = (int32_t)n2;
   }
+  store_hash();
 }
 
 // ---------------------------------------------------------------------------
@@ -570,10 +692,33 @@ hipError_t launch_scan_i32(const int32_t* in, int64_t* out, int64_t n, int64_t* 
     hipLaunchKernelGGL(zero_i64, dim3(1), dim3(64), 0, s, out);
     return hipGetLastError();
   }
+  if (n <= kScanOneBlock) {
+    hipLaunchKernelGGL(scan_one_block, dim3(1), dim3(kScanBig), 0, s, in, n, out);
+    return hipGetLastError();
+  }
   const int64_t nb = (n + kScanTile - 1) / kScanTile;
   hipLaunchKernelGGL(scan_block_sums, dim3((unsigned)nb), dim3(kScanThreads), 0, s, in, n, block_tmp);
-  hipLaunchKernelGGL(scan_sums, dim3(1), dim3(kScanThreads), 0, s, block_tmp, nb);
-  hipLaunchKernelGGL(scan_apply, dim3((unsigned)nb), dim3(kScanThreads), 0, s, in, n, block_tmp, out);
+  if (nb <= kScanSelfSum) {
+    hipLaunchKernelGGL(scan_apply<false>, dim3((unsigned)nb), dim3(kScanThreads), 0, s, in, n, block_tmp, out);
+  } else {
+    hipLaunchKernelGGL(scan_sums, dim3(1), dim3(kScanThreads), 0, s, block_tmp, nb);
+    hipLaunchKernelGGL(scan_apply<true>, dim3((unsigned)nb), dim3(kScanThreads), 0, s, in, n, block_tmp, out);
+  }
+  return hipGetLastError();
+}
+
+// Block-CSR offsets and the statistics' way to the host: one launch on the
+// chunks' sums, or (more chunks than a workgroup should add up) a plain scan.
+hipError_t launch_mask_scan(const MaskStateArgs& a, int64_t* row_ptr, int64_t* scan_tmp, int32_t nseg,
+                            unsigned long long* stats_host, hipStream_t s) {
+  if (a.nchunks <= kScanSelfSum) {
+    hipLaunchKernelGGL(mask_scan_kernel, dim3((unsigned)a.nchunks), dim3(kScanThreads), 0, s, a, row_ptr, nseg,
+                       stats_host);
+    return hipGetLastError();
+  }
+  const hipError_t e = launch_scan_i32(a.counts, row_ptr, a.R, scan_tmp, s);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(write_stats_kernel, dim3(1), dim3(kScanThreads), 0, s, a, nseg, stats_host);
   return hipGetLastError();
 }
 

@@ -187,6 +187,8 @@ struct Segment {
   Task* tasks = nullptr;
   int64_t* task_ptr = nullptr;  // split > 1: [Rp + 1], device task count at [Rp]
   int64_t tasks_bound = 0;
+  bool ordered = false;         // the tasks are dispatched in an order of their own
+  bool by_rows = false;         // ... formed per (b, head) from row hashes
   int32_t* order = nullptr;     // dispatch order of the tasks (Split-K plans); null: as stored
   Task* tasks_run = nullptr;    // the tasks in dispatch order (plans without Split-K); null: row order
   int32_t* dispatch = nullptr;  // the dispatch order (exported); null: row order
@@ -557,7 +559,8 @@ bsa_status bsa_plan(const bsa_mask* mask, const int32_t* B_Q, const int32_t* B_K
   const size_t o_bhnnz = align256(o_stats + sizeof(SegStats) * nseg);
   const size_t o_chunks = align256(o_bhnnz + sizeof(unsigned long long) * (size_t)B * H);
   const size_t upload_bytes = o_chunks + sizeof(RowChunk) * chunks.size();
-  const size_t o_counts = align256(upload_bytes);
+  const size_t o_csum = align256(upload_bytes);
+  const size_t o_counts = align256(o_csum + sizeof(int64_t) * chunks.size());
   const size_t o_runs = align256(o_counts + sizeof(int32_t) * (size_t)p->R);
   const size_t o_rowptr = align256(o_runs + sizeof(int32_t) * (size_t)p->R);
   const size_t o_scan = align256(o_rowptr + sizeof(int64_t) * (size_t)(p->R + 1));
@@ -581,9 +584,8 @@ bsa_status bsa_plan(const bsa_mask* mask, const int32_t* B_Q, const int32_t* B_K
     Staging& stg = staging();
     std::lock_guard<std::mutex> lk(stg.mu);
     const size_t stats_at = align256(upload_bytes);
-    const size_t bhnnz_at = align256(stats_at + sizeof(SegStats) * nseg);
-    if (bhnnz_at - stats_at != o_bhnnz - o_stats) return fail(BSA_ERR_HIP, "statistics staging layout");
-    if ((st = stg.reserve(bhnnz_at + sizeof(unsigned long long) * (size_t)B * H)) != BSA_OK) return st;
+    const size_t stats_bytes = sizeof(SegStats) * nseg;
+    if ((st = stg.reserve(stats_at + stats_bytes + sizeof(unsigned long long) * (size_t)B * H)) != BSA_OK) return st;
     uint8_t* h8 = static_cast<uint8_t*>(stg.ptr);
     std::memset(h8, 0, upload_bytes);
     std::memcpy(h8 + o_heads, p->heads.data(), sizeof(HeadDesc) * H);
@@ -606,21 +608,22 @@ bsa_status bsa_plan(const bsa_mask* mask, const int32_t* B_Q, const int32_t* B_K
     ma.runs = reinterpret_cast<int32_t*>(pre8 + o_runs);
     ma.chunks = reinterpret_cast<const RowChunk*>(pre8 + o_chunks);
     ma.nchunks = (int32_t)chunks.size();
+    ma.chunk_sum = reinterpret_cast<int64_t*>(pre8 + o_csum);
     ma.seg_stats = p->stats_dev;
     ma.bh_nnz = p->bh_nnz_dev;
     HIP_TRY(launch_mask_count(ma, stream));
-    HIP_TRY(launch_scan_i32(p->counts_dev, p->row_ptr_dev, p->R, p->scan_tmp_dev, stream));
     // the request's single synchronisation: the segment statistics and the
-    // per-(b, h) active block counts
-    // (one copy: both buffers start 256-aligned and lie at the same distance
-    // apart on the device and in the staging buffer)
+    // per-(b, h) active block counts, which the scan kernel writes to the
+    // pinned buffer itself (a copy command costs a launch and 4 us more)
     static_assert(sizeof(SegStats) % 8 == 0, "statistics layout");
-    HIP_TRY(hipMemcpyAsync(h8 + stats_at, p->stats_dev, (o_bhnnz - o_stats) + sizeof(unsigned long long) * (size_t)B * H,
-                           hipMemcpyDeviceToHost, stream));
+    void* stats_out = nullptr;
+    HIP_TRY(hipHostGetDevicePointer(&stats_out, h8 + stats_at, 0));
+    HIP_TRY(launch_mask_scan(ma, p->row_ptr_dev, p->scan_tmp_dev, nseg, static_cast<unsigned long long*>(stats_out),
+                             stream));
     HIP_TRY(hipStreamSynchronize(stream));
-    std::memcpy(stats.data(), h8 + stats_at, sizeof(SegStats) * nseg);
+    std::memcpy(stats.data(), h8 + stats_at, stats_bytes);
     bh_nnz.resize((size_t)B * H);
-    std::memcpy(bh_nnz.data(), h8 + bhnnz_at, sizeof(unsigned long long) * (size_t)B * H);
+    std::memcpy(bh_nnz.data(), h8 + stats_at + stats_bytes, sizeof(unsigned long long) * (size_t)B * H);
   }
 
   // ---- regime lookup and ranked fallback per segment (host)
@@ -658,9 +661,22 @@ bsa_status bsa_plan(const bsa_mask* mask, const int32_t* B_Q, const int32_t* B_K
   if (p->nnz >= INT32_MAX) return fail(BSA_ERR_UNSUPPORTED, "too many active blocks");
 
   // ---- launch preparation of the selected plans only
+  // Dispatch order: tasks with equal KV lists side by side.  Up to 512 tasks
+  // (two workgroups on each of 256 CUs) run all at once, so their order does
+  // not change what shares an L2.  Plans without Split-K are ordered from row
+  // hashes that the fill kernels form on the way.
+  bool direct_hash = false;
+  for (Segment& sg : p->segs) {
+    sg.ordered = !opts.keep_row_order && sg.tasks_bound > kOrderMinTasks;
+    sg.by_rows = sg.ordered && sg.plan.split == 1 && sg.npq <= kRowOrderMax;
+    direct_hash = direct_hash || (sg.by_rows && sg.mapping == 0);
+  }
   void* cptr = nullptr;
-  if ((st = p->alloc(&cptr, sizeof(int32_t) * (size_t)p->nnz)) != BSA_OK) return st;
+  const size_t o_rowhash = align256(sizeof(int32_t) * (size_t)p->nnz);
+  if ((st = p->alloc(&cptr, direct_hash ? o_rowhash + sizeof(uint64_t) * (size_t)p->R : sizeof(int32_t) * (size_t)p->nnz)) != BSA_OK)
+    return st;
   p->col_idx_dev = static_cast<int32_t*>(cptr);
+  uint64_t* row_hash = direct_hash ? reinterpret_cast<uint64_t*>(static_cast<uint8_t*>(cptr) + o_rowhash) : nullptr;
   {
     MaskStateArgs ma{};
     ma.mask = mask->data;
@@ -672,6 +688,7 @@ bsa_status bsa_plan(const bsa_mask* mask, const int32_t* B_Q, const int32_t* B_K
     ma.R = p->R;
     ma.row_ptr = p->row_ptr_dev;
     ma.col_idx = p->col_idx_dev;
+    ma.row_hash = row_hash;
     ma.wide = mask_rows_word_aligned(mask, p->heads) ? 1 : 0;
     HIP_TRY(launch_mask_fill(ma, stream));
   }
@@ -694,20 +711,18 @@ bsa_status bsa_plan(const bsa_mask* mask, const int32_t* B_Q, const int32_t* B_K
     const size_t o_rmem = sg.compact && sg.gq > 1 ? take(sizeof(uint64_t) * (size_t)sg.tiles_bound) : 0;
     const size_t o_tasks = take(sizeof(Task) * (size_t)sg.tasks_bound);
     const size_t o_taskptr = e.split > 1 ? take(sizeof(int64_t) * (size_t)(sg.Rp + 1)) : 0;
-    // dispatch order: tasks with equal KV lists side by side.  Up to 512
-    // tasks (two workgroups on each of 256 CUs) run all at once, so their
-    // order does not change what shares an L2.
-    const bool ordered = !opts.keep_row_order && sg.tasks_bound > kOrderMinTasks;
     size_t order_temp = 0;
-    if (ordered) HIP_TRY(task_order_temp_bytes(sg.tasks_bound, &order_temp));
-    const size_t nb = ordered ? (size_t)sg.tasks_bound : 0;
-    const int64_t table_size = ordered ? task_order_table_size(sg.tasks_bound) : 0;
+    const bool general_order = sg.ordered && !sg.by_rows;
+    if (general_order) HIP_TRY(task_order_temp_bytes(sg.tasks_bound, &order_temp));
+    const size_t nb = general_order ? (size_t)sg.tasks_bound : 0;
+    const int64_t table_size = general_order ? task_order_table_size(sg.tasks_bound) : 0;
     const size_t o_tkey = take(sizeof(uint64_t) * (size_t)table_size), o_tmin = take(sizeof(int32_t) * (size_t)table_size);
     const size_t o_slot = take(sizeof(int32_t) * nb), o_iin = take(sizeof(int32_t) * nb);
     const size_t o_rep = take(sizeof(uint32_t) * nb), o_rsort = take(sizeof(uint32_t) * nb);
-    const size_t o_order = take(sizeof(int32_t) * nb);
+    const size_t o_order = take(sg.ordered ? sizeof(int32_t) * (size_t)sg.tasks_bound : 0);
     const size_t o_otemp = take(order_temp);
-    const size_t o_trun = take(e.split == 1 ? sizeof(Task) * nb : 0);
+    const size_t o_trun = take(sg.ordered && e.split == 1 ? sizeof(Task) * (size_t)sg.tasks_bound : 0);
+    const size_t o_hash = take(sg.by_rows && !direct ? sizeof(uint64_t) * (size_t)sg.Rp : 0);
     void* buf = nullptr;
     if ((st = p->alloc(&buf, need)) != BSA_OK) return st;
     uint8_t* b8 = static_cast<uint8_t*>(buf);
@@ -757,6 +772,8 @@ bsa_status bsa_plan(const bsa_mask* mask, const int32_t* B_Q, const int32_t* B_K
       m.tile_ptr = sg.tile_ptr;
       m.tile_kv = sg.tile_kv;
       m.member = sg.member;
+      if (e.split == 1) m.tasks = sg.tasks;
+      if (sg.by_rows) m.row_hash = reinterpret_cast<uint64_t*>(b8 + o_hash);
       HIP_TRY(launch_map_fill(m, stream));
     }
     TaskArgs ta{};
@@ -781,8 +798,25 @@ bsa_status bsa_plan(const bsa_mask* mask, const int32_t* B_Q, const int32_t* B_K
       if ((st = p->alloc(&ws, (size_t)sg.ws_bytes)) != BSA_OK) return st;
       sg.ws = static_cast<float*>(ws);
     }
-    HIP_TRY(launch_task_fill(ta, stream));
-    if (ordered) {
+    // (the mapping's fill has written the tasks of split-free plans)
+    if (direct || e.split > 1) HIP_TRY(launch_task_fill(ta, stream));
+    if (sg.by_rows) {
+      RowOrderArgs ra{};
+      ra.row_hash = direct ? row_hash : reinterpret_cast<const uint64_t*>(b8 + o_hash);
+      ra.row_base = p->row_base_dev;
+      ra.seg_heads = ta.seg_heads;
+      ra.nsh = ta.nsh;
+      ra.H = H;
+      ra.npq = sg.npq;
+      ra.direct = ta.direct;
+      ra.nbh = B * ta.nsh;
+      ra.tasks = sg.tasks;
+      ra.order = reinterpret_cast<int32_t*>(b8 + o_order);
+      ra.tasks_out = reinterpret_cast<Task*>(b8 + o_trun);
+      HIP_TRY(launch_row_order(ra, stream));
+      sg.tasks_run = ra.tasks_out;
+      sg.dispatch = ra.order;
+    } else if (sg.ordered) {
       OrderArgs oa{};
       oa.tasks = sg.tasks;
       oa.ntasks_dev = e.split > 1 ? sg.task_ptr + sg.Rp : nullptr;

@@ -176,7 +176,117 @@ __global__ __launch_bounds__(256) void copy_pairs_kernel(const uint32_t* k, cons
   v2[i] = v[i];
 }
 
+// The order for plans without Split-K, in one launch: a task moves only
+// within its (b, head), so one workgroup orders the rows of one of them.
+// Rows with equal hashes find each other through an open-addressing table in
+// LDS (slots hold the row that claimed them; at most half full, so a probe
+// ends), groups take places by their first row, and a row's place inside its
+// group is the number of its members before it.  (The general path below
+// takes 16 to 21 launches for the same: 47 us of 110 us of planning kernels
+// for 21600 tasks.)
+constexpr int kRowOrderThreads = 1024;
+constexpr int kRowOrderPer = kRowOrderMax / kRowOrderThreads;
+constexpr int kRowOrderTable = 2 * kRowOrderMax;
+
+__global__ __launch_bounds__(kRowOrderThreads) void row_order_kernel(RowOrderArgs a) {
+  __shared__ uint64_t hash[kRowOrderMax];
+  __shared__ int32_t table[kRowOrderTable];
+  __shared__ int32_t first[kRowOrderMax];    // lowest row of the group that row i claimed a slot for
+  __shared__ int32_t count[kRowOrderMax];    // members, later the first place, of the group led by row i
+  __shared__ int32_t members[kRowOrderMax];
+  __shared__ int32_t wave_sum[kRowOrderThreads / 64];
+  const int tid = threadIdx.x, n = a.npq;
+  const int64_t base = (int64_t)blockIdx.x * n;
+  const int bh = (int)(blockIdx.x / a.nsh) * a.H + a.seg_heads[blockIdx.x % a.nsh];
+  const uint64_t* in = a.row_hash + (a.direct ? a.row_base[bh] : base);
+  for (int i = tid; i < kRowOrderTable; i += kRowOrderThreads) table[i] = -1;
+  for (int i = tid; i < n; i += kRowOrderThreads) {
+    hash[i] = in[i];
+    first[i] = INT32_MAX;
+  }
+  for (int i = tid; i < kRowOrderMax; i += kRowOrderThreads) count[i] = 0;
+  __syncthreads();
+  int lead[kRowOrderPer], place[kRowOrderPer], size[kRowOrderPer];
+#pragma unroll
+  for (int j = 0; j < kRowOrderPer; ++j) {
+    const int i = tid + j * kRowOrderThreads;
+    lead[j] = i;
+    if (i >= n) continue;
+    const uint64_t h = hash[i];
+    uint32_t slot = (uint32_t)h & (kRowOrderTable - 1);
+    for (int probe = 0; probe < kRowOrderTable; ++probe) {
+      const int v = atomicCAS(&table[slot], -1, i);
+      if (v == -1 || hash[v] == h) {
+        lead[j] = v == -1 ? i : v;
+        break;
+      }
+      slot = (slot + 1) & (kRowOrderTable - 1);
+    }
+    atomicMin(&first[lead[j]], i);
+  }
+  __syncthreads();
+#pragma unroll
+  for (int j = 0; j < kRowOrderPer; ++j) {
+    const int i = tid + j * kRowOrderThreads;
+    if (i >= n) continue;
+    lead[j] = first[lead[j]];
+    place[j] = atomicAdd(&count[lead[j]], 1);
+  }
+  __syncthreads();
+#pragma unroll
+  for (int j = 0; j < kRowOrderPer; ++j) size[j] = tid + j * kRowOrderThreads < n ? count[lead[j]] : 0;
+  __syncthreads();
+  {
+    // exclusive scan of the counts: thread t holds rows kRowOrderPer t ..
+    const int lane = tid & 63, w = tid >> 6;
+    int own[kRowOrderPer], sum = 0;
+#pragma unroll
+    for (int j = 0; j < kRowOrderPer; ++j) {
+      own[j] = count[kRowOrderPer * tid + j];
+      sum += own[j];
+    }
+    int incl = sum;
+    for (int off = 1; off < 64; off <<= 1) {
+      const int y = __shfl_up(incl, off, 64);
+      if (lane >= off) incl += y;
+    }
+    if (lane == 63) wave_sum[w] = incl;
+    __syncthreads();
+    int run = incl - sum;
+    for (int i = 0; i < w; ++i) run += wave_sum[i];
+#pragma unroll
+    for (int j = 0; j < kRowOrderPer; ++j) {
+      count[kRowOrderPer * tid + j] = run;
+      run += own[j];
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int j = 0; j < kRowOrderPer; ++j) {
+    const int i = tid + j * kRowOrderThreads;
+    if (i < n) members[count[lead[j]] + place[j]] = i;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int j = 0; j < kRowOrderPer; ++j) {
+    const int i = tid + j * kRowOrderThreads;
+    if (i >= n) continue;
+    const int start = count[lead[j]];
+    int before = 0;
+    for (int m = 0; m < size[j]; ++m) before += members[start + m] < i ? 1 : 0;
+    const int64_t at = base + start + before;
+    a.order[at] = (int32_t)(base + i);
+    a.tasks_out[at] = a.tasks[base + i];
+  }
+}
+
 }  // namespace
+
+hipError_t launch_row_order(const RowOrderArgs& a, hipStream_t s) {
+  if (a.npq < 1 || a.npq > kRowOrderMax) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(row_order_kernel, dim3((unsigned)a.nbh), dim3(kRowOrderThreads), 0, s, a);
+  return hipGetLastError();
+}
 
 int64_t task_order_table_size(int64_t n) {
   int64_t s = 1;
