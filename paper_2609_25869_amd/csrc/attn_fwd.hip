@@ -854,7 +854,7 @@ void attn_fwd_kernel(AttnArgs a) {
 // whose threads walked 32 columns and the states one after the other, the
 // whole forward pass of a 16384-token, 12-head, 15% top-k request with S = 8
 // went from 2.53 to 0.78 ms, of 104 rows of 314 tiles from 0.134 to 0.085 ms.
-constexpr int kMaxSplit = 8;   // largest Split-K factor of the catalog
+constexpr int kMergeBatch = 8;  // partial states loaded together
 constexpr int kMergeRows = 8;
 
 template <int TQ>
@@ -870,29 +870,37 @@ __global__ __launch_bounds__(32 * kMergeRows) void splitk_merge_kernel(AttnArgs 
   const int b = task.bh / a.H, h = task.bh - b * a.H;
   const int64_t slot_elems = (int64_t)TQ * (kD + 2);
   const float* base = a.ws + ti * slot_elems;
-  float m[kMaxSplit], l[kMaxSplit];
-  f32x4 part[kMaxSplit];
   float mstar = kNegInf;
+  for (int s0 = 0; s0 < task.nsplit; s0 += kMergeBatch) {
+    float m[kMergeBatch];
 #pragma unroll
-  for (int s = 0; s < kMaxSplit; ++s) {
-    m[s] = kNegInf;
-    if (s >= task.nsplit) continue;
-    const float* sl = base + s * slot_elems;
-    m[s] = sl[ql];
-    l[s] = sl[TQ + ql];
-    part[s] = *reinterpret_cast<const f32x4*>(sl + 2 * TQ + (int64_t)ql * kD + col);
+    for (int s = 0; s < kMergeBatch; ++s)
+      m[s] = s0 + s < task.nsplit ? base[(s0 + s) * slot_elems + ql] : kNegInf;
+#pragma unroll
+    for (int s = 0; s < kMergeBatch; ++s) mstar = fmaxf(mstar, m[s]);
   }
-#pragma unroll
-  for (int s = 0; s < kMaxSplit; ++s) mstar = fmaxf(mstar, m[s]);
   f32x4 acc = {0.f, 0.f, 0.f, 0.f};
   float L = 0.f;
+  for (int s0 = 0; s0 < task.nsplit; s0 += kMergeBatch) {
+    float m[kMergeBatch], l[kMergeBatch];
+    f32x4 part[kMergeBatch];
 #pragma unroll
-  for (int s = 0; s < kMaxSplit; ++s) {
-    if (m[s] == kNegInf) continue;
-    const float wgt = fast_exp2(m[s] - mstar);
-    L += wgt * l[s];
+    for (int s = 0; s < kMergeBatch; ++s) {
+      m[s] = kNegInf;
+      if (s0 + s >= task.nsplit) continue;
+      const float* sl = base + (s0 + s) * slot_elems;
+      m[s] = sl[ql];
+      l[s] = sl[TQ + ql];
+      part[s] = *reinterpret_cast<const f32x4*>(sl + 2 * TQ + (int64_t)ql * kD + col);
+    }
 #pragma unroll
-    for (int e = 0; e < 4; ++e) acc[e] += wgt * part[s][e];
+    for (int s = 0; s < kMergeBatch; ++s) {
+      if (m[s] == kNegInf) continue;
+      const float wgt = fast_exp2(m[s] - mstar);
+      L += wgt * l[s];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) acc[e] += wgt * part[s][e];
+    }
   }
   const float inv = L > 0.f ? 1.f / L : 0.f;
   bf16x4 v4;

@@ -91,6 +91,7 @@ struct TaskArgs {
   const int32_t* seg_heads;
   int32_t nsh, H, npq, split;
   int32_t direct;
+  int32_t grain;             // list entries that stay together (2 for compacted lists, else 1)
   int64_t Rp;
   int32_t* counts;           // count pass (split > 1)
   const int64_t* task_ptr;   // fill pass (split > 1), null when split == 1
@@ -173,6 +174,9 @@ hipError_t launch_map_count(const MapArgs& a, hipStream_t s);
 hipError_t launch_map_fill(const MapArgs& a, hipStream_t s);
 hipError_t launch_task_count(const TaskArgs& a, hipStream_t s);
 hipError_t launch_task_fill(const TaskArgs& a, hipStream_t s);
+// Count, offsets and fill of at most kTasksOneBlock rows in one launch.
+constexpr int64_t kTasksOneBlock = 1024;
+hipError_t launch_tasks_one_block(const TaskArgs& a, int64_t* task_ptr, hipStream_t s);
 hipError_t launch_attention(int tq, int tkv, int waves, int stages, const AttnArgs& a, hipStream_t s);
 int64_t task_order_table_size(int64_t n);
 hipError_t task_order_temp_bytes(int64_t n, size_t* bytes);

@@ -622,7 +622,8 @@ __global__ __launch_bounds__(256) void map_rows_kernel(MapArgs a) {
 // ---------------------------------------------------------------------------
 // Task organisation (Section 4.3): physical row rs of the segment is cut into
 // `split` contiguous slices [floor(s*n/S), floor((s+1)*n/S)); empty slices
-// are dropped; a row without active tiles keeps one empty task.
+// are dropped; a row without active tiles keeps one empty task.  Lists whose
+// entries stay together in twos are cut in units of two.
 __device__ inline void task_row(const TaskArgs& a, int64_t rs, int* bh, int* pq, int64_t* lo, int64_t* hi) {
   const int64_t per_b = (int64_t)a.nsh * a.npq;
   const int b = (int)(rs / per_b);
@@ -634,14 +635,35 @@ __device__ inline void task_row(const TaskArgs& a, int64_t rs, int* bh, int* pq,
   *hi = a.tile_ptr[row + 1];
 }
 
+// tasks of a row of n list entries
+__device__ inline int row_tasks(const TaskArgs& a, int64_t n) {
+  const int64_t units = (n + a.grain - 1) / a.grain;
+  return (int)(n == 0 ? 1 : (units < a.split ? units : a.split));
+}
+
 __global__ __launch_bounds__(256) void task_count_kernel(TaskArgs a) {
   const int64_t rs = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (rs >= a.Rp) return;
   int bh, pq;
   int64_t lo, hi;
   task_row(a, rs, &bh, &pq, &lo, &hi);
-  const int64_t n = hi - lo;
-  a.counts[rs] = (int32_t)(n == 0 ? 1 : (n < a.split ? n : a.split));
+  a.counts[rs] = row_tasks(a, hi - lo);
+}
+
+__device__ inline void write_row_tasks(const TaskArgs& a, int bh, int pq, int64_t lo, int64_t hi, int64_t out) {
+  const int64_t n = hi - lo, units = (n + a.grain - 1) / a.grain;
+  if (n == 0 || a.split == 1) {
+    a.tasks[out] = Task{bh, pq, (int32_t)lo, (int32_t)hi, 0, 1, 0, 0};
+    return;
+  }
+  const int nsplit = row_tasks(a, n);
+  int s_out = 0;
+  for (int s = 0; s < a.split; ++s) {
+    const int64_t b0 = lo + (s * units) / a.split * a.grain, b1 = min(hi, lo + ((s + 1) * units) / a.split * a.grain);
+    if (b1 <= b0) continue;
+    a.tasks[out + s_out] = Task{bh, pq, (int32_t)b0, (int32_t)b1, s_out, nsplit, 0, 0};
+    ++s_out;
+  }
 }
 
 __global__ __launch_bounds__(256) void task_fill_kernel(TaskArgs a) {
@@ -650,22 +672,24 @@ __global__ __launch_bounds__(256) void task_fill_kernel(TaskArgs a) {
   int bh, pq;
   int64_t lo, hi;
   task_row(a, rs, &bh, &pq, &lo, &hi);
-  const int64_t n = hi - lo;
-  int64_t out = a.task_ptr ? a.task_ptr[rs] : rs;
-  if (n == 0 || a.split == 1) {
-    Task t{bh, pq, (int32_t)lo, (int32_t)hi, 0, 1, 0, 0};
-    a.tasks[out] = t;
-    return;
+  write_row_tasks(a, bh, pq, lo, hi, a.task_ptr ? a.task_ptr[rs] : rs);
+}
+
+__global__ __launch_bounds__(kTasksOneBlock) void tasks_one_block_kernel(TaskArgs a, int64_t* task_ptr) {
+  const int64_t rs = threadIdx.x;
+  int bh = 0, pq = 0, count = 0;
+  int64_t lo = 0, hi = 0;
+  if (rs < a.Rp) {
+    task_row(a, rs, &bh, &pq, &lo, &hi);
+    count = row_tasks(a, hi - lo);
   }
-  const int nsplit = (int)(n < a.split ? n : a.split);
-  int s_out = 0;
-  for (int s = 0; s < a.split; ++s) {
-    const int64_t b0 = lo + (s * n) / a.split, b1 = lo + ((s + 1) * n) / a.split;
-    if (b1 == b0) continue;
-    Task t{bh, pq, (int32_t)b0, (int32_t)b1, s_out, nsplit, 0, 0};
-    a.tasks[out + s_out] = t;
-    ++s_out;
+  int64_t total;
+  const int64_t out = block_exclusive_scan<kTasksOneBlock>(count, &total);
+  if (rs < a.Rp) {
+    task_ptr[rs] = out;
+    write_row_tasks(a, bh, pq, lo, hi, out);
   }
+  if (rs == 0) task_ptr[a.Rp] = total;
 }
 
 inline unsigned grid_for(int64_t rows, int per_block) { return (unsigned)((rows + per_block - 1) / per_block); }
@@ -743,6 +767,12 @@ hipError_t launch_task_count(const TaskArgs& a, hipStream_t s) {
 hipError_t launch_task_fill(const TaskArgs& a, hipStream_t s) {
   if (a.Rp == 0) return hipSuccess;
   hipLaunchKernelGGL(task_fill_kernel, dim3(grid_for(a.Rp, 256)), dim3(256), 0, s, a);
+  return hipGetLastError();
+}
+
+hipError_t launch_tasks_one_block(const TaskArgs& a, int64_t* task_ptr, hipStream_t s) {
+  if (a.Rp > kTasksOneBlock) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(tasks_one_block_kernel, dim3(1), dim3(kTasksOneBlock), 0, s, a, task_ptr);
   return hipGetLastError();
 }
 

@@ -56,6 +56,11 @@ size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
 // Task count above which the planner sorts a segment's tasks into KV order.
 constexpr int64_t kOrderMinTasks = 512;
 
+// Slices of rows that are too few to fill the chip (slice_rows below).
+constexpr int64_t kSliceTasks = 512;   // two workgroups on each of 256 CUs
+constexpr int64_t kSliceKeys = 448;    // active keys a slice should keep
+constexpr int64_t kSliceMost = 64;     // slices of one row
+
 // Length of the runs of consecutive tasks that the XCDs of one group take
 // turns over (see the plan's traversal order, CatalogEntry::xcd_group).
 constexpr int32_t kSlotRun = 8;
@@ -184,9 +189,11 @@ struct Segment {
   uint64_t* run_member = nullptr;
   int32_t* counts = nullptr;
   int64_t* scan_tmp = nullptr;
-  Task* tasks = nullptr;
-  int64_t* task_ptr = nullptr;  // split > 1: [Rp + 1], device task count at [Rp]
-  int64_t tasks_bound = 0;
+  Task* tasks = nullptr;        // the kernel's tasks in row order
+  int64_t* task_ptr = nullptr;  // slices > 1: [Rp + 1], device task count at [Rp]
+  int64_t tasks_bound = 0;      // tasks of the plan
+  int32_t slices = 1;           // slices the kernel's tasks cut a row into (slice_rows); plan.split or more
+  int64_t run_bound = 0;        // tasks the kernel runs
   bool ordered = false;         // the tasks are dispatched in an order of their own
   bool by_rows = false;         // ... formed per (b, head) from row hashes
   int32_t* order = nullptr;     // dispatch order of the tasks (Split-K plans); null: as stored
@@ -331,6 +338,23 @@ namespace {
 // inactive columns; the packed list leaves those out and is never longer in
 // keys than the tile list (plus one half tile).  Split-K plans cut rows by
 // tiles and keep the tile list.
+// Slices per physical row for the kernel.  A request of few rows leaves CUs
+// idle however long its rows are, and the plan's Split-K factor ends at 8, so
+// rows are cut further until the tasks fill the chip or a slice would hold
+// fewer than kSliceKeys active keys (the tile loop's start and the merge then
+// cost more than the slice saves).  The partial states merge as for Split-K;
+// the plan, its tasks and their exports stay what they are.  T_Q = 64, rows x
+// active keys: 104 x 10000 in 0.187 ms uncut, 0.078 in four slices (0.087 in
+// nine); 2 x 13000 in 0.236 and 0.024 ms (40 slices); 64 x 640 in 0.020 uncut
+// and 0.023 in four, 64 x 820 in 0.022 and 0.024 in two, which sets the line.
+int32_t slice_rows(const Segment& sg, int64_t logical_rows) {
+  const int32_t split = sg.plan.split;
+  if (sg.Rp * split * 2 > kSliceTasks || logical_rows == 0) return split;
+  const int64_t keys = sg.nnz * sg.bkv / logical_rows;  // per query-block row; a taller tile's union has more
+  const int64_t s = std::min({kSliceTasks / sg.Rp, keys / kSliceKeys, kSliceMost});
+  return (int32_t)std::max<int64_t>(split, s);
+}
+
 bool runs_compacted(const Segment& sg) {
   const CatalogEntry& e = sg.plan;
   return sg.bkv == 16 && e.tkv == 32 && e.split == 1 && (e.waves == 2 || e.waves == 4) && e.tq == 32 * e.waves;
@@ -359,6 +383,43 @@ std::vector<int64_t> segment_logical_rows(bsa_plan_t plan, const Segment& sg) {
     for (int32_t h : sg.heads)
       for (int32_t pq = 0; pq < sg.npq; ++pq) rows.push_back(plan->row_base[(size_t)b * plan->H + h] + pq);
   return rows;
+}
+
+// Tile offsets of a segment's physical rows, read back to the host: rebased
+// onto the segment's own tile list for Direct segments, whose tiles are the
+// logical block-CSR's columns.
+bsa_status segment_tile_ptr(bsa_plan_t plan, const Segment& sg, std::vector<int64_t>* ptr) {
+  const bool direct = sg.mapping == 0;
+  const int64_t n = direct ? plan->R + 1 : sg.Rp + 1;
+  std::vector<int64_t> v((size_t)n);
+  HIP_TRY(hipMemcpyAsync(v.data(), direct ? plan->row_ptr_dev : sg.tile_ptr, sizeof(int64_t) * n, hipMemcpyDeviceToHost,
+                         plan->stream));
+  HIP_TRY(hipStreamSynchronize(plan->stream));
+  if (direct) {
+    const std::vector<int64_t> rows = segment_logical_rows(plan, sg);
+    ptr->assign(rows.size() + 1, 0);
+    for (size_t r = 0; r < rows.size(); ++r)
+      (*ptr)[r + 1] = (*ptr)[r] + v[(size_t)rows[r] + 1] - v[(size_t)rows[r]];
+  } else {
+    *ptr = std::move(v);
+  }
+  return BSA_OK;
+}
+
+// Tasks of a physical row of n tiles under the plan's Split-K factor.
+int64_t plan_row_tasks(int64_t n, int64_t split) { return n == 0 ? 1 : std::min(n, split); }
+
+// Number of the plan's tasks (the kernel may run more: slice_rows).
+bsa_status plan_task_count(bsa_plan_t plan, const Segment& sg, int64_t* n) {
+  *n = sg.Rp;
+  if (sg.plan.split == 1) return BSA_OK;
+  if (sg.slices == sg.plan.split) return read_device_i64(plan, sg.task_ptr + sg.Rp, n);
+  std::vector<int64_t> ptr;
+  const bsa_status st = segment_tile_ptr(plan, sg, &ptr);
+  if (st != BSA_OK) return st;
+  *n = 0;
+  for (int64_t r = 0; r < sg.Rp; ++r) *n += plan_row_tasks(ptr[(size_t)r + 1] - ptr[(size_t)r], sg.plan.split);
+  return BSA_OK;
 }
 }  // namespace
 
@@ -649,7 +710,9 @@ bsa_status bsa_plan(const bsa_mask* mask, const int32_t* B_Q, const int32_t* B_K
       return fail(BSA_ERR_UNSUPPORTED, "too many active tiles for 32-bit tile indices");
     sg.tasks_bound = e.split == 1 ? sg.Rp : std::min(sg.Rp * e.split, sg.Rp + sg.tiles_bound);
     if (sg.tasks_bound >= INT32_MAX) return fail(BSA_ERR_UNSUPPORTED, "too many tasks for one launch");
-    sg.balanced = e.split == 1 && (e.xcd_group == 2 || e.xcd_group == 4);
+    sg.slices = slice_rows(sg, (int64_t)B * (int64_t)sg.heads.size() * sg.nqb);
+    sg.run_bound = sg.slices == e.split ? sg.tasks_bound : std::min(sg.Rp * sg.slices, sg.Rp + sg.tiles_bound);
+    sg.balanced = sg.slices == 1 && (e.xcd_group == 2 || e.xcd_group == 4);
     if (sg.balanced) {
       std::vector<int64_t> work;
       for (int b = 0; b < B; ++b)
@@ -709,8 +772,8 @@ bsa_status bsa_plan(const bsa_mask* mask, const int32_t* B_Q, const int32_t* B_K
     const size_t o_rptr = sg.compact ? take(sizeof(int64_t) * (size_t)(sg.Rp + 1)) : 0;
     const size_t o_rkv = sg.compact ? take(sizeof(int32_t) * (size_t)sg.tiles_bound) : 0;
     const size_t o_rmem = sg.compact && sg.gq > 1 ? take(sizeof(uint64_t) * (size_t)sg.tiles_bound) : 0;
-    const size_t o_tasks = take(sizeof(Task) * (size_t)sg.tasks_bound);
-    const size_t o_taskptr = e.split > 1 ? take(sizeof(int64_t) * (size_t)(sg.Rp + 1)) : 0;
+    const size_t o_tasks = take(sizeof(Task) * (size_t)sg.run_bound);
+    const size_t o_taskptr = sg.slices > 1 ? take(sizeof(int64_t) * (size_t)(sg.Rp + 1)) : 0;
     size_t order_temp = 0;
     const bool general_order = sg.ordered && !sg.by_rows;
     if (general_order) HIP_TRY(task_order_temp_bytes(sg.tasks_bound, &order_temp));
@@ -772,7 +835,7 @@ bsa_status bsa_plan(const bsa_mask* mask, const int32_t* B_Q, const int32_t* B_K
       m.tile_ptr = sg.tile_ptr;
       m.tile_kv = sg.tile_kv;
       m.member = sg.member;
-      if (e.split == 1) m.tasks = sg.tasks;
+      if (sg.slices == 1) m.tasks = sg.tasks;
       if (sg.by_rows) m.row_hash = reinterpret_cast<uint64_t*>(b8 + o_hash);
       HIP_TRY(launch_map_fill(m, stream));
     }
@@ -783,23 +846,29 @@ bsa_status bsa_plan(const bsa_mask* mask, const int32_t* B_Q, const int32_t* B_K
     ta.nsh = (int32_t)sg.heads.size();
     ta.H = H;
     ta.npq = sg.npq;
-    ta.split = e.split;
+    ta.split = sg.slices;
+    ta.grain = sg.compact ? 2 : 1;
     ta.direct = direct ? 1 : 0;
     ta.Rp = sg.Rp;
     ta.tasks = sg.tasks;
-    if (e.split > 1) {
+    if (sg.slices > 1) {
       sg.task_ptr = reinterpret_cast<int64_t*>(b8 + o_taskptr);
-      ta.counts = sg.counts;
-      HIP_TRY(launch_task_count(ta, stream));
-      HIP_TRY(launch_scan_i32(sg.counts, sg.task_ptr, sg.Rp, sg.scan_tmp, stream));
-      ta.task_ptr = sg.task_ptr;
-      sg.ws_bytes = (int64_t)sizeof(float) * sg.tasks_bound * e.tq * (kHeadDim + 2);
+      sg.ws_bytes = (int64_t)sizeof(float) * sg.run_bound * e.tq * (kHeadDim + 2);
       void* ws = nullptr;
       if ((st = p->alloc(&ws, (size_t)sg.ws_bytes)) != BSA_OK) return st;
       sg.ws = static_cast<float*>(ws);
     }
-    // (the mapping's fill has written the tasks of split-free plans)
-    if (direct || e.split > 1) HIP_TRY(launch_task_fill(ta, stream));
+    if (sg.slices > 1 && sg.Rp <= kTasksOneBlock) {
+      HIP_TRY(launch_tasks_one_block(ta, sg.task_ptr, stream));
+    } else if (sg.slices > 1) {
+      ta.counts = sg.counts;
+      HIP_TRY(launch_task_count(ta, stream));
+      HIP_TRY(launch_scan_i32(sg.counts, sg.task_ptr, sg.Rp, sg.scan_tmp, stream));
+      ta.task_ptr = sg.task_ptr;
+      HIP_TRY(launch_task_fill(ta, stream));
+    } else if (direct) {  // (the mapping's fill has written the others' tasks)
+      HIP_TRY(launch_task_fill(ta, stream));
+    }
     if (sg.by_rows) {
       RowOrderArgs ra{};
       ra.row_hash = direct ? row_hash : reinterpret_cast<const uint64_t*>(b8 + o_hash);
@@ -863,8 +932,8 @@ bsa_status bsa_forward(bsa_plan_t plan, const void* q, const void* k, const void
     const CatalogEntry& e = sg.plan;
     AttnArgs a{};
     a.tasks = sg.tasks_run ? sg.tasks_run : sg.tasks;
-    a.ntasks = (int32_t)sg.tasks_bound;
-    a.ntasks_dev = e.split > 1 ? sg.task_ptr + sg.Rp : nullptr;
+    a.ntasks = (int32_t)sg.run_bound;
+    a.ntasks_dev = sg.slices > 1 ? sg.task_ptr + sg.Rp : nullptr;
     a.order = sg.order;
     a.kv_tile = sg.compact ? sg.run_kv : sg.tile_kv;
     a.member = sg.compact ? sg.run_member : sg.member;
@@ -896,7 +965,7 @@ bsa_status bsa_forward(bsa_plan_t plan, const void* q, const void* k, const void
     for (int g = 0; g < 5; ++g) a.share_lo[g] = sg.share_lo[g];
     a.nslots = sg.nslots;
     HIP_TRY(launch_attention(e.tq, e.tkv, e.waves, e.stages, a, stream));
-    if (e.split > 1) HIP_TRY(launch_splitk_merge(e.tq, a, stream));
+    if (sg.slices > 1) HIP_TRY(launch_splitk_merge(e.tq, a, stream));
   }
   HIP_TRY(hipEventRecord(plan->done, stream));
   return BSA_OK;
@@ -936,11 +1005,7 @@ bsa_status bsa_plan_info(bsa_plan_t plan, int32_t segment, bsa_segment_info* out
   } else if ((st = read_device_i64(plan, sg.tile_ptr + sg.Rp, &i.n_tiles)) != BSA_OK) {
     return st;
   }
-  if (sg.plan.split == 1) {
-    i.n_tasks = sg.Rp;
-  } else if ((st = read_device_i64(plan, sg.task_ptr + sg.Rp, &i.n_tasks)) != BSA_OK) {
-    return st;
-  }
+  if ((st = plan_task_count(plan, sg, &i.n_tasks)) != BSA_OK) return st;
   *out = i;
   return BSA_OK;
 }
@@ -987,7 +1052,7 @@ bsa_status bsa_plan_export(bsa_plan_t plan, int32_t segment, int32_t what, void*
   // Direct segments read the logical block-CSR; export their rows rebased
   // onto the segment's own tile list.
   std::vector<int64_t> lrows, lptr, seg_ptr;
-  if (sg.mapping == 0 && what != BSA_EXPORT_TILE_MEMBER) {
+  if (sg.mapping == 0 && (what == BSA_EXPORT_TILE_PTR || what == BSA_EXPORT_TILE_KV)) {
     lrows = segment_logical_rows(plan, sg);
     if ((st = host_vec_i64(plan->row_ptr_dev, plan->R + 1, &lptr)) != BSA_OK) return st;
     seg_ptr.assign(lrows.size() + 1, 0);
@@ -1030,41 +1095,35 @@ bsa_status bsa_plan_export(bsa_plan_t plan, int32_t segment, int32_t what, void*
       return copy_out(sg.member, sizeof(uint64_t) * (size_t)nt);
     }
     case BSA_EXPORT_TASKS: {
-      int64_t nt = sg.Rp;
-      if (sg.plan.split > 1 && (st = read_device_i64(plan, sg.task_ptr + sg.Rp, &nt)) != BSA_OK) return st;
+      // the plan's tasks from its rows' tile ranges (the kernel's own list may
+      // be in dispatch order, compacted or cut further)
+      std::vector<int64_t> ptr;
+      if ((st = segment_tile_ptr(plan, sg, &ptr)) != BSA_OK) return st;
+      const int64_t split = sg.plan.split;
+      int64_t nt = 0;
+      for (int64_t r = 0; r < sg.Rp; ++r) nt += plan_row_tasks(ptr[(size_t)r + 1] - ptr[(size_t)r], split);
       *needed = sizeof(int64_t) * 6 * (size_t)nt;
       if (!host_buf) return BSA_OK;
       if (bytes < *needed) return fail(BSA_ERR_INVALID, "export buffer too small");
-      std::vector<Task> t((size_t)nt);
-      if (nt) HIP_TRY(hipMemcpyAsync(t.data(), sg.tasks, sizeof(Task) * nt, hipMemcpyDeviceToHost, s));
-      HIP_TRY(hipStreamSynchronize(s));
       int64_t* dst = static_cast<int64_t*>(host_buf);
-      // a compacted segment's tasks hold ranges of the compacted list; its
-      // tasks are its rows, so the tile ranges are the rows' own
-      if (sg.compact && (st = host_vec_i64(sg.tile_ptr, sg.Rp + 1, &seg_ptr)) != BSA_OK) return st;
-      std::vector<int32_t> slot_of_head((size_t)plan->H, -1);
-      for (size_t j = 0; j < sg.heads.size(); ++j) slot_of_head[(size_t)sg.heads[j]] = (int32_t)j;
-      for (int64_t i = 0; i < nt; ++i) {
-        int64_t lo = t[i].tile_begin, hi = t[i].tile_end;
-        if (sg.compact) {
-          lo = seg_ptr[(size_t)i];
-          hi = seg_ptr[(size_t)i + 1];
-        } else if (sg.mapping == 0) {
-          // rebase from the global block-CSR onto the segment's tile list
-          const int64_t b = t[i].bh / plan->H, h = t[i].bh % plan->H;
-          const int64_t rs = (b * (int64_t)sg.heads.size() + slot_of_head[(size_t)h]) * sg.npq + t[i].pq;
-          const int64_t shift = seg_ptr[(size_t)rs] - lptr[(size_t)lrows[(size_t)rs]];
-          lo += shift;
-          hi += shift;
+      const int64_t nsh = (int64_t)sg.heads.size();
+      for (int64_t r = 0; r < sg.Rp; ++r) {
+        const int64_t b = r / (nsh * sg.npq), bh = b * plan->H + sg.heads[(size_t)(r / sg.npq % nsh)];
+        const int64_t lo = ptr[(size_t)r], n = ptr[(size_t)r + 1] - lo, parts = plan_row_tasks(n, split);
+        int64_t ordinal = 0;
+        for (int64_t k = 0; k < split; ++k) {
+          const int64_t b0 = lo + k * n / split, b1 = lo + (k + 1) * n / split;
+          if (b1 == b0 && !(n == 0 && k == 0)) continue;
+          const int64_t f[6] = {bh, r % sg.npq, b0, b1, ordinal++, parts};
+          std::memcpy(dst, f, sizeof f);
+          dst += 6;
         }
-        const int64_t f[6] = {t[i].bh, t[i].pq, lo, hi, t[i].split, t[i].nsplit};
-        std::memcpy(dst + 6 * i, f, sizeof f);
       }
       return BSA_OK;
     }
     case BSA_EXPORT_DISPATCH: {
-      int64_t nt = sg.Rp;
-      if (sg.plan.split > 1 && (st = read_device_i64(plan, sg.task_ptr + sg.Rp, &nt)) != BSA_OK) return st;
+      int64_t nt = 0;
+      if ((st = plan_task_count(plan, sg, &nt)) != BSA_OK) return st;
       *needed = sizeof(int64_t) * (size_t)nt;
       if (!host_buf) return BSA_OK;
       if (bytes < *needed) return fail(BSA_ERR_INVALID, "export buffer too small");

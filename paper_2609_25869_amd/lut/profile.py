@@ -22,7 +22,7 @@ Corpus (the paper's profiling masks are not available; these stand in):
   densities -- frame-window masks (long runs, like spatiotemporal windows),
   Bernoulli masks with the diagonal (few runs) and per-row top-k of pooled
   q.k block scores with the diagonal.  Inputs are N(0,1) in bf16.  The
-  wide, mixture and large splits widen this grid (see their constants).
+  wide, mixture, large and cross splits widen this grid (see their constants).
 
     python -m paper_2609_25869_amd.lut.profile --out PATH [--split profile|eval] [--budget SECONDS]
 
@@ -47,7 +47,7 @@ BATCH_HEADS = [4, 24]
 FAMILIES = [("window", 0.05), ("window", 0.15), ("bernoulli", 0.03), ("bernoulli", 0.10), ("bernoulli", 0.30),
             ("topk", 0.12)]
 SPLIT_SEED = {"profile": 0, "eval": 1, "wide": 2, "wide_eval": 3, "mixture": 4, "mixture_eval": 5, "large": 6,
-              "large_eval": 7, "grid2": 8}
+              "large_eval": 7, "grid2": 8, "cross": 9, "cross_eval": 10}
 FRAMES = 16
 
 # The wide splits draw, per request key, random combinations of a larger
@@ -83,6 +83,14 @@ LARGE_PER_KEY = {"large": 12, "large_eval": 6}
 GRID2_SEQ = [32768, 65536, 115200]
 GRID2_BH = [8, 16]
 
+# The cross splits: fewer query tokens than keys (a part of a sequence
+# against all of it), where a few long rows have to fill the chip.
+CROSS_SEQ_Q = [64, 128, 256, 512, 1024, 2048, 4096, 8192]
+CROSS_SEQ = [8192, 16384, 32768, 65536, 131072]
+CROSS_BH = [1, 2, 4, 8, 24]
+CROSS_SOURCES = [(f, r) for f, r in WIDE_SOURCES if f != "window"]
+CROSS_PER_KEY = {"cross": 32, "cross_eval": 16}
+
 
 def log(msg):
     print("[profile] " + msg, flush=True)
@@ -108,6 +116,17 @@ def corpus(split):
                 cases.append(dict(id="%s-%d" % (split, len(cases)), geometry=list(geom), N=rng.choice(LARGE_SEQ),
                                   bh=rng.choice(LARGE_BH), family=fam, rho=rho, seed=rng.randrange(1 << 30)))
         return cases
+    if split in CROSS_PER_KEY:
+        import random
+        rng = random.Random(1000 + SPLIT_SEED[split])
+        for geom in GEOMETRIES:
+            for _ in range(CROSS_PER_KEY[split]):
+                fam, rho = rng.choice(CROSS_SOURCES)
+                N = rng.choice(CROSS_SEQ)
+                cases.append(dict(id="%s-%d" % (split, len(cases)), geometry=list(geom), N=N,
+                                  nq=rng.choice([n for n in CROSS_SEQ_Q if n < N]), bh=rng.choice(CROSS_BH),
+                                  family=fam, rho=rho, seed=rng.randrange(1 << 30)))
+        return cases
     if split in WIDE_PER_KEY:
         import random
         rng = random.Random(1000 + SPLIT_SEED[split])
@@ -132,7 +151,8 @@ def make_mask(torch, case, q, k):
     """[bh, nqb, nkb] uint8 mask for the case, built on the device."""
     bq, bkv = case["geometry"]
     N, bh, rho = case["N"], case["bh"], case["rho"]
-    nqb, nkb = -(-N // bq), -(-N // bkv)
+    Nq = case.get("nq", N)
+    nqb, nkb = -(-Nq // bq), -(-N // bkv)
     dev = q.device
     g = torch.Generator(device=dev)
     g.manual_seed(case["seed"])
@@ -173,8 +193,8 @@ def make_mask(torch, case, q, k):
     else:
         kk = max(1, int(math.floor(rho * nkb + 0.5)))
         for h in range(bh):
-            pq = q[0, :nqb * bq, h, :].float().reshape(nqb, bq, -1).mean(1) if N % bq == 0 else \
-                torch.stack([q[0, i * bq:min(N, (i + 1) * bq), h, :].float().mean(0) for i in range(nqb)])
+            pq = q[0, :nqb * bq, h, :].float().reshape(nqb, bq, -1).mean(1) if Nq % bq == 0 else \
+                torch.stack([q[0, i * bq:min(Nq, (i + 1) * bq), h, :].float().mean(0) for i in range(nqb)])
             pk = k[0, :nkb * bkv, h, :].float().reshape(nkb, bkv, -1).mean(1) if N % bkv == 0 else \
                 torch.stack([k[0, i * bkv:min(N, (i + 1) * bkv), h, :].float().mean(0) for i in range(nkb)])
             idx = torch.topk(pq @ pk.T, kk, dim=1).indices
@@ -211,7 +231,7 @@ def reference_rows(torch, q, k, v, mask, bq, bkv, rows):
     """Masked attention (Eq. 1) for query rows [(h, i), ...] of batch 0, in
     fp32, from the logical mask: a plain per-row evaluation, independent of
     every plan."""
-    N = q.shape[1]
+    N = k.shape[1]
     out = torch.zeros((len(rows), q.shape[3]), dtype=torch.float32, device=q.device)
     scale = 1.0 / math.sqrt(q.shape[3])
     for r, (h, i) in enumerate(rows):
@@ -228,10 +248,11 @@ def reference_rows(torch, q, k, v, mask, bq, bkv, rows):
 def profile_case(torch, bsa, case, reps=3, only=None):
     bq, bkv = case["geometry"]
     N, bh = case["N"], case["bh"]
+    Nq = case.get("nq", N)
     dev = torch.device("cuda")
     g = torch.Generator(device=dev)
     g.manual_seed(case["seed"] + 7)
-    q = torch.randn((1, N, bh, 128), generator=g, device=dev, dtype=torch.float32).to(torch.bfloat16)
+    q = torch.randn((1, Nq, bh, 128), generator=g, device=dev, dtype=torch.float32).to(torch.bfloat16)
     k = torch.randn((1, N, bh, 128), generator=g, device=dev, dtype=torch.float32).to(torch.bfloat16)
     v = torch.randn((1, N, bh, 128), generator=g, device=dev, dtype=torch.float32).to(torch.bfloat16)
     mask = make_mask(torch, case, q, k)
@@ -248,7 +269,7 @@ def profile_case(torch, bsa, case, reps=3, only=None):
     rng = torch.Generator()
     rng.manual_seed(case["seed"] + 11)
     rows = [(int(h), int(i)) for h, i in zip(torch.randint(0, bh, (64,), generator=rng).tolist(),
-                                             torch.randint(0, N, (64,), generator=rng).tolist())]
+                                             torch.randint(0, Nq, (64,), generator=rng).tolist())]
     ref = reference_rows(torch, q, k, v, mask, bq, bkv, rows)
     ri = torch.tensor([i for _, i in rows], device=dev)
     rh = torch.tensor([h for h, _ in rows], device=dev)
@@ -262,7 +283,7 @@ def profile_case(torch, bsa, case, reps=3, only=None):
             continue
         if feats is None:
             info = p.info(0)
-            feats = {"seq_q": N, "seq_kv": N, "batch_heads": bh, "nnz": info["nnz"], "blocks": info["blocks"],
+            feats = {"seq_q": Nq, "seq_kv": N, "batch_heads": bh, "nnz": info["nnz"], "blocks": info["blocks"],
                      "run_blocks": info["run_blocks"], "max_row_nnz": info["max_row_nnz"]}
         t = kernel_time(torch, stream, lambda: bsa.forward(p, q, k, v, o, None, stream=stream), reps)
         p.destroy()
@@ -283,10 +304,11 @@ def case_features(torch, bsa, case):
     with the base plan), without timing any plan."""
     bq, bkv = case["geometry"]
     N, bh = case["N"], case["bh"]
+    Nq = case.get("nq", N)
     dev = torch.device("cuda")
     g = torch.Generator(device=dev)
     g.manual_seed(case["seed"] + 7)
-    q = torch.randn((1, N, bh, 128), generator=g, device=dev, dtype=torch.float32).to(torch.bfloat16)
+    q = torch.randn((1, Nq, bh, 128), generator=g, device=dev, dtype=torch.float32).to(torch.bfloat16)
     k = torch.randn((1, N, bh, 128), generator=g, device=dev, dtype=torch.float32).to(torch.bfloat16)
     mask = make_mask(torch, case, q, k)
     nqb, nkb = mask.shape[1], mask.shape[2]
@@ -294,7 +316,7 @@ def case_features(torch, bsa, case):
                  stride_b=0, force_plan=bsa.base_plan(bq, bkv))
     info = p.info(0)
     p.destroy()
-    return {"seq_q": N, "seq_kv": N, "batch_heads": bh, "nnz": info["nnz"], "blocks": info["blocks"],
+    return {"seq_q": Nq, "seq_kv": N, "batch_heads": bh, "nnz": info["nnz"], "blocks": info["blocks"],
             "run_blocks": info["run_blocks"], "max_row_nnz": info["max_row_nnz"]}
 
 
