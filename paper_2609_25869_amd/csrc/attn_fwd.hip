@@ -211,7 +211,7 @@ void attn_fwd_kernel(AttnArgs a) {
   auto vslot = [&](int i) -> uint8_t* { return kslot(i) + C::kTileBytes; };
 
   const int64_t nt = a.ntasks_dev ? *a.ntasks_dev : a.ntasks;
-  int64_t ti = task_of_slot(blockIdx.x, nt, a.slot_group, a.slot_run, a.balanced ? a.share_lo : nullptr);
+  int64_t ti = task_of_slot((int64_t)blockIdx.x + a.slot0, nt, a.slot_group, a.slot_run, a.balanced ? a.share_lo : nullptr);
   if (ti < 0) return;
   if (a.order) ti = ((const __attribute__((address_space(4))) int32_t*)a.order)[ti];
   const Task task = a.tasks[ti];
@@ -916,8 +916,15 @@ template <int NWAVES, int G, int TKV, int STAGES, int UNIT = TKV>
 hipError_t launch_variant(const AttnArgs& a, hipStream_t s) {
   const int64_t slots = a.nslots > 0 ? a.nslots : default_slots(a.ntasks);
   if (slots == 0) return hipSuccess;
-  hipLaunchKernelGGL((attn_fwd_kernel<NWAVES, G, TKV, STAGES, UNIT>), dim3((unsigned)slots), dim3(64 * NWAVES), 0, s, a);
-  return hipGetLastError();
+  const int64_t per = a.launch_slots > 0 ? a.launch_slots : slots;  // a multiple of 8
+  AttnArgs part = a;
+  for (part.slot0 = 0; part.slot0 < slots; part.slot0 += per) {
+    const unsigned n = (unsigned)(slots - part.slot0 < per ? slots - part.slot0 : per);
+    hipLaunchKernelGGL((attn_fwd_kernel<NWAVES, G, TKV, STAGES, UNIT>), dim3(n), dim3(64 * NWAVES), 0, s, part);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
 }
 
 }  // namespace

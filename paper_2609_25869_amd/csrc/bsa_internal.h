@@ -159,6 +159,8 @@ struct AttnArgs {
   int32_t slot_group, slot_run; // launch-slot to task map: XCDs per group (1, 2, 4 or 8) and run length
   int32_t balanced;             // nonzero: group g's share of the task list is [share_lo[g], share_lo[g + 1])
   int32_t share_lo[5];
+  int64_t slot0;                // first launch slot of this launch
+  int64_t launch_slots;         // slots per launch (0: all in one)
   int64_t nslots;               // launch slots (0: the task count rounded up to 8)
 };
 

@@ -194,6 +194,7 @@ struct Segment {
   int64_t tasks_bound = 0;      // tasks of the plan
   int32_t slices = 1;           // slices the kernel's tasks cut a row into (slice_rows); plan.split or more
   int64_t run_bound = 0;        // tasks the kernel runs
+  int64_t launch_slots = 0;     // launch slots per kernel launch (launch_slots); 0: all
   bool ordered = false;         // the tasks are dispatched in an order of their own
   bool by_rows = false;         // ... formed per (b, head) from row hashes
   int32_t* order = nullptr;     // dispatch order of the tasks (Split-K plans); null: as stored
@@ -353,6 +354,34 @@ int32_t slice_rows(const Segment& sg, int64_t logical_rows) {
   const int64_t keys = sg.nnz * sg.bkv / logical_rows;  // per query-block row; a taller tile's union has more
   const int64_t s = std::min({kSliceTasks / sg.Rp, keys / kSliceKeys, kSliceMost});
   return (int32_t)std::max<int64_t>(split, s);
+}
+
+// Launch slots per kernel launch; 0: all tasks in one launch.  The tasks an
+// XCD runs at once read the same head's K/V in the same order, and share L2
+// lines while they are about equally far.  They start together but drift
+// apart over the generations of a long launch; a launch per generation lines
+// them up again, for the wait on its slowest task and about 6 us.  That pays
+// for the T_Q = 64 kernels, which read the most K/V per flop, and there
+// - where a head's K/V is several times an XCD's L2 (4 MB): over the rule's
+//   other conditions a mean of 0.83 of the time at 115200 tokens (none of 258
+//   slower by 3%), 0.89 at 65536 (none of 174), 0.98 at 32768 (33 of 162);
+// - where the rows are about equally long (with the longest above 1.4 times
+//   the mean the wait costs more: 0.89 within, 1.0 above);
+// - where they are scattered: the long runs of windows share lines between
+//   neighbours anyway (5% window of 131072 tokens 4.20 and 4.59 ms);
+// - where a query block is at most one task's rows: the tasks of a larger
+//   block share their list and run side by side (128-token blocks: 0.97, the
+//   fastest plan unchanged).
+// 12% top-k of 64-token blocks, T = (64, 32) in two slots, 24 heads x 115200
+// tokens 35.1 -> 21.9 ms (the fastest without: 24.5 ms), 12 x 65536 4.83 ->
+// 3.39; 12% Bernoulli 12 x 65536 5.45 -> 4.19; T_Q = 128 within 2%.
+constexpr int64_t kGenerationSlots = 1024;      // four 2-wave workgroups on each of 256 CUs
+constexpr int64_t kGenerationKvBytes = 32 << 20;
+int64_t launch_slots(const Segment& sg, int64_t logical_rows, int32_t seq_kv) {
+  if (sg.plan.tq != 64 || sg.bq > 64 || sg.slices != 1 || sg.Rp < 2 * kGenerationSlots) return 0;
+  if ((int64_t)seq_kv * kHeadDim * 4 < kGenerationKvBytes) return 0;
+  if (sg.max_row_nnz * logical_rows * 5 > sg.nnz * 7 || sg.run_blocks * 3 > sg.nnz * 2) return 0;
+  return kGenerationSlots;
 }
 
 bool runs_compacted(const Segment& sg) {
@@ -711,6 +740,7 @@ bsa_status bsa_plan(const bsa_mask* mask, const int32_t* B_Q, const int32_t* B_K
     sg.tasks_bound = e.split == 1 ? sg.Rp : std::min(sg.Rp * e.split, sg.Rp + sg.tiles_bound);
     if (sg.tasks_bound >= INT32_MAX) return fail(BSA_ERR_UNSUPPORTED, "too many tasks for one launch");
     sg.slices = slice_rows(sg, (int64_t)B * (int64_t)sg.heads.size() * sg.nqb);
+    sg.launch_slots = launch_slots(sg, (int64_t)B * (int64_t)sg.heads.size() * sg.nqb, s.seq_kv);
     sg.run_bound = sg.slices == e.split ? sg.tasks_bound : std::min(sg.Rp * sg.slices, sg.Rp + sg.tiles_bound);
     sg.balanced = sg.slices == 1 && (e.xcd_group == 2 || e.xcd_group == 4);
     if (sg.balanced) {
@@ -964,6 +994,7 @@ bsa_status bsa_forward(bsa_plan_t plan, const void* q, const void* k, const void
     a.balanced = sg.balanced ? 1 : 0;
     for (int g = 0; g < 5; ++g) a.share_lo[g] = sg.share_lo[g];
     a.nslots = sg.nslots;
+    a.launch_slots = sg.launch_slots;
     HIP_TRY(launch_attention(e.tq, e.tkv, e.waves, e.stages, a, stream));
     if (sg.slices > 1) HIP_TRY(launch_splitk_merge(e.tq, a, stream));
   }
