@@ -46,7 +46,8 @@ def common_flags():
 # Its score tiles are VALU operands, so MFMA results stay in VGPRs; the
 # compiler's default for kernels with one wave per SIMD is AGPRs, from which
 # every score element would first be copied.
-EXTRA_FLAGS = {"attn_fwd.hip": ["-fno-honor-nans", "-mllvm", "-amdgpu-mfma-vgpr-form"]}
+EXTRA_FLAGS = {"attn_fwd.hip": ["-fno-honor-nans", "-mllvm", "-amdgpu-mfma-vgpr-form"],
+               "sparsify.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"]}
 
 
 def _compile(src: str) -> str:
