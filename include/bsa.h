@@ -112,8 +112,8 @@ typedef struct {
   int64_t max_row_nnz;       /* largest active-block count of one query-block row */
   int64_t n_rows;            /* physical query rows */
   int64_t n_tiles;           /* active physical tiles */
-  int64_t n_tasks;           /* workgroup tasks */
-  int64_t workspace_bytes;   /* Split-K partial-state workspace */
+  int64_t n_tasks;           /* workgroup tasks of the plan (a segment of few rows may run in finer slices) */
+  int64_t workspace_bytes;   /* partial-state workspace: Split-K's, or that of the slices */
 } bsa_segment_info;
 
 /* One catalog entry (Section 4.4): a native kernel configuration, i.e. a
