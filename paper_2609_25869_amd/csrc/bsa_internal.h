@@ -197,7 +197,7 @@ struct MeanArgs {
   double* out[2];
 };
 struct SelectArgs {
-  const float* scores;
+  float* scores;  // room for sparsify_score_rows(rows) rows; not kept
   const float* knorm;
   int32_t nparts;
   const double* pq;
@@ -207,6 +207,7 @@ struct SelectArgs {
   uint8_t* mask;
 };
 int32_t sparsify_max_kv_blocks();
+int64_t sparsify_score_rows(int64_t rows);  // score rows of whole selection workgroups
 int32_t sparsify_norm_parts(int32_t nkb);  // room per head for the partial maxima
 hipError_t launch_block_mean(const MeanArgs& a, hipStream_t s);
 hipError_t launch_block_scores(const double* pq, const double* pk, int32_t nqb, int32_t nkb, int32_t nbh,

@@ -1197,16 +1197,17 @@ bsa_status sparsify_validate(const void* q, const void* k, const bsa_shapes* sha
   return BSA_OK;
 }
 
-// Device bytes of one head's block means (queries and keys), score rows and
-// key norms.
-int64_t sparsify_head_bytes(int64_t nqb, int64_t nkb) {
-  return (nqb + nkb) * kHeadDim * (int64_t)sizeof(double) + nqb * nkb * (int64_t)sizeof(float) +
-         sparsify_norm_parts((int32_t)nkb) * (int64_t)sizeof(float);
+// Device bytes of the block means (queries and keys), score rows and key norms
+// of `heads` heads.
+int64_t sparsify_bytes(int64_t heads, int64_t nqb, int64_t nkb) {
+  return heads * (nqb + nkb) * kHeadDim * (int64_t)sizeof(double) +
+         sparsify_score_rows(heads * nqb) * nkb * (int64_t)sizeof(float) +
+         heads * sparsify_norm_parts((int32_t)nkb) * (int64_t)sizeof(float);
 }
 
 // The sparsifier's passes over the heads, at most `most` heads at a time
 // (shared out evenly), with the block means, score rows and norms of a pass in
-// `work` (at least `most` * head bytes).
+// `work` (sparsify_bytes(most, ...)).
 hipError_t sparsify_passes(const void* q, const void* k, const bsa_shapes& s, int32_t bq, int32_t bkv, int32_t topk,
                            int32_t diagonal, uint8_t* mask, int64_t nqb, int64_t nkb, int64_t most, void* work,
                            hipStream_t stream) {
@@ -1214,7 +1215,7 @@ hipError_t sparsify_passes(const void* q, const void* k, const bsa_shapes& s, in
   const int64_t chunk = cdiv(nbh, cdiv(nbh, most));
   const size_t bytes_q = (size_t)(chunk * nqb * kHeadDim) * sizeof(double);
   const size_t bytes_k = (size_t)(chunk * nkb * kHeadDim) * sizeof(double);
-  const size_t bytes_s = (size_t)(chunk * nqb * nkb) * sizeof(float);
+  const size_t bytes_s = (size_t)(sparsify_score_rows(chunk * nqb) * nkb) * sizeof(float);
   uint8_t* w8 = static_cast<uint8_t*>(work);
   MeanArgs m{};
   m.x[0] = static_cast<const uint16_t*>(q);
@@ -1315,7 +1316,7 @@ bsa_status bsa_sparsify_topk(const void* q, const void* k, const bsa_shapes* sha
   const int64_t chunk = sparsify_heads_per_pass((int64_t)s.batch * s.heads, int64_t(256) << 20,
                                                 nqb * nkb * (int64_t)sizeof(float));
   void* work = nullptr;
-  HIP_TRY(hipMallocAsync(&work, (size_t)(chunk * sparsify_head_bytes(nqb, nkb)), stream));
+  HIP_TRY(hipMallocAsync(&work, (size_t)sparsify_bytes(chunk, nqb, nkb), stream));
   const hipError_t e = sparsify_passes(q, k, s, bq, bkv, topk, diagonal, mask, nqb, nkb, chunk, work, stream);
   const hipError_t ef = hipFreeAsync(work, stream);
   if (e != hipSuccess) return fail(BSA_ERR_HIP, std::string("sparsifier launch: ") + hipGetErrorString(e));
@@ -1328,8 +1329,9 @@ bsa_status bsa_sparsify_topk_noalloc(const void* q, const void* k, const bsa_sha
   int64_t nqb = 0, nkb = 0;
   bsa_status st = sparsify_validate(q, k, shapes, bq, bkv, mask, &nqb, &nkb);
   if (st != BSA_OK) return st;
-  // the documented limit counts eight bytes a score; what is used is less, but
-  // for the key norms of single rows (the array's last 4096 bytes)
+  // the documented limit counts eight bytes a score; what is used is less
+  // (rows rounded up to four and the norms take at most 73 KB more than four
+  // bytes a score, and a head of fewer than four rows at most 7 MB in all)
   const int64_t per_head = (nqb + nkb) * kHeadDim * (int64_t)sizeof(double) + nqb * nkb * (int64_t)sizeof(double);
   if (per_head > kNoAllocScratchBytes)
     return fail(BSA_ERR_INVALID, "one head needs " + std::to_string(per_head) +
@@ -1340,8 +1342,9 @@ bsa_status bsa_sparsify_topk_noalloc(const void* q, const void* k, const bsa_sha
   HIP_TRY(hipGetDevice(&dev));
   void* work = nullptr;
   if ((st = scratch_address(dev, &work)) != BSA_OK) return st;
-  const int64_t chunk = sparsify_heads_per_pass((int64_t)s.batch * s.heads, kNoAllocScratchBytes,
-                                                sparsify_head_bytes(nqb, nkb));
+  const int64_t slack = sparsify_score_rows(1) * nkb * (int64_t)sizeof(float);  // rows rounded up
+  const int64_t chunk = sparsify_heads_per_pass((int64_t)s.batch * s.heads, kNoAllocScratchBytes - slack,
+                                                sparsify_bytes(1, nqb, nkb));
   // every byte of the scratch that a pass reads is written earlier in the
   // same pass (means before scores, scores before the selection), so nothing
   // needs clearing

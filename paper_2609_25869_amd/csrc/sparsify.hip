@@ -32,7 +32,10 @@
 //   topk_select_kernel   (232 us) one wave per score row with the row's keys
 //                        in registers, counted against a threshold that
 //                        interpolation and bisection move (VALU-bound; no
-//                        LDS, no barrier)
+//                        LDS, no barrier).  Rows that fp32 leaves undecided
+//                        (most of a row's columns tied, non-finite or extreme
+//                        values, one block thousands of times the others)
+//                        cost more: 3.5 ms in all with every row such a row
 #include "bsa_internal.h"
 
 namespace bsa {
@@ -280,62 +283,139 @@ __device__ inline uint32_t order_key32(float x) {
 }
 __device__ inline float key32_value(uint32_t k) { return __uint_as_float((k >> 31) ? (k & 0x7FFFFFFFu) : ~k); }
 
-// The pinned score of (mean query row q, mean key row k), by one thread.
-__device__ inline double pinned_score(const double* q, const double* k) {
-#pragma clang fp contract(off)
-  double acc = 0.0;
-#pragma unroll 4
-  for (int c = 0; c < kHeadDim; ++c) {
-    const double prod = q[c] * k[c];
-    acc = acc + prod;
-  }
-  return acc;
+// A mean query row that is the same for the whole wave, read through the
+// scalar cache.
+typedef const __attribute__((address_space(4))) double* UniformRow;
+__device__ inline UniformRow uniform_row(const double* p) {
+  const uint64_t u = (uint64_t)p;
+  const uint32_t lo = __builtin_amdgcn_readfirstlane((int)(uint32_t)u), hi = __builtin_amdgcn_readfirstlane((int)(u >> 32));
+  return (UniformRow)((uint64_t)hi << 32 | lo);
 }
 
-// The same by one wave: the products in parallel, then the sum in order.
-__device__ inline double pinned_score_wave(const double* q, const double* k) {
+// The pinned score of (mean query row q, mean key row k), by one thread.
+__device__ inline double pinned_score(UniformRow q, const double* k) {
 #pragma clang fp contract(off)
-  const int lane = threadIdx.x & 63;
   double acc = 0.0;
+#pragma unroll 1
+  for (int c = 0; c < kHeadDim; c += 8) {
+    f64x2 v[4];
 #pragma unroll
-  for (int half = 0; half < kHeadDim; half += 64) {
-    const double prod = q[half + lane] * k[half + lane];
-    const uint64_t u = (uint64_t)__double_as_longlong(prod);
-#pragma unroll 8
-    for (int c = 0; c < 64; ++c) {
-      const uint32_t lo = __builtin_amdgcn_readlane((int)(uint32_t)u, c);
-      const uint32_t hi = __builtin_amdgcn_readlane((int)(uint32_t)(u >> 32), c);
-      acc = acc + __longlong_as_double((long long)((uint64_t)hi << 32 | lo));
+    for (int j = 0; j < 4; ++j) v[j] = *reinterpret_cast<const f64x2*>(k + c + 2 * j);
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      const double prod = q[c + j] * v[j / 2][j % 2];
+      acc = acc + prod;
     }
   }
   return acc;
 }
 
-// One row in the pinned arithmetic throughout, by the whole workgroup:
-// MSB-first radix select of the k-th largest score (8 passes of 8 bits over
-// order-preserving 64-bit keys in LDS), ties ranked by column with a
-// workgroup prefix count.  Fills take[0 .. nkb).
-__device__ void select_row_pinned(const double* q, const double* pk, int32_t nkb, int32_t k, uint64_t* keys,
-                                  uint8_t* take) {
-  __shared__ uint32_t hist[256];
-  __shared__ uint32_t chunk_ties[256];
-  __shared__ uint64_t s_prefix;
-  __shared__ int32_t s_remaining;
-  const int tid = threadIdx.x;
+constexpr int kSelWaves = 4;
+constexpr int kMaxCand = 64;
+
+// x, but addresses formed from it are formed where they are used: kept across
+// the loops around, they would cost the whole kernel registers.
+__device__ inline int not_hoisted(int x) {
+  asm volatile("" : "+v"(x));
+  return x;
+}
+
+// Rows in the pinned arithmetic throughout, by the whole workgroup, two rows
+// of one head at a time.
+//
+// Scores: a wave takes 64 columns at a time, eight head-dim columns per step.
+// Its lanes read the mean keys as whole 64-byte pieces, pass them on through
+// LDS (kPinStage bytes per wave, 16-byte chunks of row r permuted by
+// (r / 2) % 4, so that neither side conflicts), and lane l accumulates its
+// column's two scores in order.  Bound by the latency of those steps.  (A
+// thread that walked a mean key row by itself, one row of scores at a time,
+// read 64 lines per instruction: with every row undecided, 115200 tokens x 24
+// heads in (64, 64) blocks took 14.9 ms with it and 3.5 so, 0.87 with none.)
+constexpr int kPinDims = 8;
+
+constexpr int kPinStage = 64 * kPinDims * 8;
+
+__device__ inline void pinned_keys(UniformRow q0, UniformRow q1, const double* pk, int32_t nkb, uint64_t* key0,
+                                   uint64_t* key1, uint8_t* smem) {
+#pragma clang fp contract(off)
+  const int wv = threadIdx.x >> 6;
+  uint8_t* stage = smem + wv * kPinStage;
 #pragma unroll 1
-  for (int32_t kb = tid; kb < nkb; kb += 256) keys[kb] = order_key(pinned_score(q, pk + (int64_t)kb * kHeadDim));
-  __syncthreads();
+  for (int32_t c0 = 64 * wv; c0 < nkb; c0 += 64 * kSelWaves) {
+    const int lane = not_hoisted(threadIdx.x & 63);
+    f64x2 v[4];
+    auto fetch = [&](int d) {
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const uint32_t c = min(c0 + 16 * j + (lane >> 2), nkb - 1);
+        v[j] = *reinterpret_cast<const f64x2*>(pk + (c * kHeadDim + d + 2 * (lane & 3)));
+      }
+    };
+    double acc0 = 0.0, acc1 = 0.0;
+    fetch(0);
+#pragma unroll 1
+    for (int d = 0; d < kHeadDim; d += kPinDims) {
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const int r = 16 * j + (lane >> 2);
+        *reinterpret_cast<f64x2*>(stage + r * 64 + (((lane & 3) ^ ((r >> 1) & 3)) << 4)) = v[j];
+      }
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      if (d + kPinDims < kHeadDim) fetch(d + kPinDims);
+#pragma unroll
+      for (int p = 0; p < kPinDims / 2; ++p) {
+        const f64x2 k2 = *reinterpret_cast<const f64x2*>(stage + lane * 64 + ((p ^ ((lane >> 1) & 3)) << 4));
+#pragma unroll
+        for (int e = 0; e < 2; ++e) {
+          const double prod0 = q0[d + 2 * p + e] * k2[e], prod1 = q1[d + 2 * p + e] * k2[e];
+          acc0 = acc0 + prod0;
+          acc1 = acc1 + prod1;
+        }
+        __builtin_amdgcn_sched_barrier(0);  // (so do products formed ahead)
+      }
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+    }
+    if (c0 + lane < nkb) {
+      key0[c0 + lane] = order_key(acc0);
+      key1[c0 + lane] = order_key(acc1);
+    }
+  }
+}
+
+// Selection from a row's pinned keys: MSB-first radix select of the k-th
+// largest (8 passes of 8 bits), ties ranked by column, the mask row written
+// with the diagonal [d0, d1].
+struct PinnedSelect {
+  uint32_t hist[256];
+  uint32_t wave_ties[kSelWaves];
+  uint64_t prefix;
+  int32_t remaining;
+};
+
+__device__ inline void select_pinned(const uint64_t* keys, int32_t nkb, int32_t k, int32_t d0, int32_t d1,
+                                     uint8_t* out, PinnedSelect& sh) {
+  const int tid = not_hoisted(threadIdx.x), lane = tid & 63, wv = tid >> 6;
   // k-th largest key: fix one byte per pass from the most significant
   uint64_t prefix = 0, pmask = 0;
   int32_t remaining = k;  // rank of the sought key among those matching prefix
 #pragma unroll 1
   for (int shift = 56; shift >= 0; shift -= 8) {
-    hist[tid] = 0;
+    sh.hist[tid] = 0;
     __syncthreads();
 #pragma unroll 1
-    for (int32_t kb = tid; kb < nkb; kb += 256) {
+    for (int32_t kb = tid; kb < nkb; kb += 64 * kSelWaves) {
       const uint64_t key = keys[kb];
-      if ((key & pmask) == prefix) atomicAdd(&hist[(key >> shift) & 255], 1u);
+      const bool in = (key & pmask) == prefix;
+      const uint32_t digit = (uint32_t)(key >> shift) & 255u;
+      // equal digits (all of them among tied scores) take one add per wave
+      const uint64_t active = __ballot(in);
+      if (active == 0) continue;
+      const uint32_t common = (uint32_t)__builtin_amdgcn_readlane((int)digit, __builtin_ctzll(active));
+      const uint64_t same = __ballot(in && digit == common);
+      if (in && digit != common) atomicAdd(&sh.hist[digit], 1u);
+      if (lane == __builtin_ctzll(active)) atomicAdd(&sh.hist[common], (uint32_t)__popcll(same));
     }
     __syncthreads();
     if (tid < 64) {
@@ -345,7 +425,7 @@ __device__ void select_row_pinned(const double* q, const double* pk, int32_t nkb
       uint32_t cnt[4], local = 0;
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
-        cnt[j] = hist[255 - 4 * tid - j];
+        cnt[j] = sh.hist[255 - 4 * tid - j];
         local += cnt[j];
       }
       const uint32_t incl = wave_inclusive_scan(local);
@@ -360,50 +440,34 @@ __device__ void select_row_pinned(const double* q, const double* pk, int32_t nkb
           above += (int32_t)cnt[j];
           --d;
         }
-        s_remaining = remaining - above;
-        s_prefix = prefix | ((uint64_t)d << shift);
+        sh.remaining = remaining - above;
+        sh.prefix = prefix | ((uint64_t)d << shift);
       }
     }
     __syncthreads();
-    remaining = s_remaining;
-    prefix = s_prefix;
+    remaining = sh.remaining;
+    prefix = sh.prefix;
     pmask |= 0xFFull << shift;
   }
   // prefix is the k-th largest key; `remaining` of the keys equal to it are
-  // taken, the lowest columns first
-  const int32_t per = (nkb + 255) / 256;
-  const int32_t c0 = min(nkb, tid * per), c1 = min(nkb, c0 + per);
+  // taken, the lowest columns first.  Wave w holds the w-th quarter of the row.
+  const int32_t per = ((nkb + kSelWaves - 1) / kSelWaves + 63) & ~63;
+  const int32_t c0 = min(nkb, wv * per), c1 = min(nkb, c0 + per);
   uint32_t ties = 0;
 #pragma unroll 1
-  for (int32_t kb = c0; kb < c1; ++kb) ties += keys[kb] == prefix;
-  chunk_ties[tid] = ties;
+  for (int32_t b = c0; b < c1; b += 64) ties += __popcll(__ballot(b + lane < c1 && keys[b + lane] == prefix));
+  if (lane == 0) sh.wave_ties[wv] = ties;
   __syncthreads();
-  if (tid < 64) {
-    // exclusive prefix over the 256 chunks, four per lane
-    uint32_t t[4], local = 0;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      t[j] = chunk_ties[4 * tid + j];
-      local += t[j];
-    }
-    uint32_t run = wave_inclusive_scan(local) - local;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      chunk_ties[4 * tid + j] = run;
-      run += t[j];
-    }
-  }
-  __syncthreads();
-  int32_t rank = (int32_t)chunk_ties[tid];
+  int32_t rank = 0;
+  for (int w = 0; w < wv; ++w) rank += (int32_t)sh.wave_ties[w];
 #pragma unroll 1
-  for (int32_t kb = c0; kb < c1; ++kb) {
-    const uint64_t key = keys[kb];
-    if (key == prefix) {
-      take[kb] = rank < remaining;
-      ++rank;
-    } else {
-      take[kb] = key > prefix;
-    }
+  for (int32_t b = c0; b < c1; b += 64) {
+    const int32_t kb = b + lane;
+    const uint64_t key = kb < c1 ? keys[kb] : 0ull;
+    const uint64_t tie = __ballot(kb < c1 && key == prefix);
+    const int32_t mine = rank + (int32_t)__popcll(tie & ((1ull << lane) - 1));
+    if (kb < c1) out[kb] = (key > prefix || (key == prefix && mine < remaining) || (kb >= d0 && kb <= d1)) ? 1 : 0;
+    rank += (int32_t)__popcll(tie);
   }
   __syncthreads();
 }
@@ -417,23 +481,29 @@ __device__ void select_row_pinned(const double* q, const double* pk, int32_t nkb
 // at most the error bound, so columns above T by more than twice the bound
 // are taken, those below T by more than that are not, and the candidates in
 // between (usually T's own column alone) are settled by their pinned scores,
-// ties to the lower column.  Up to 64 of them are scored and ranked by the
-// wave; rows with more, with scores that are not finite, or with norms
-// outside the bound's range go through select_row_pinned.
-constexpr int kSelWaves = 4;
-constexpr int kMaxCand = 64;
+// ties to the lower column.  Up to 64 of them are scored by the wave's lanes
+// and ranked; rows with more, with scores that are not finite, or with norms
+// outside the bound's range are selected in the pinned arithmetic throughout
+// once all rows of the workgroup are through: their fp32 scores are done with
+// then, and the space of the workgroup's four score rows holds the keys of two.
 
 template <int KPL, bool VEC>
-__global__ __launch_bounds__(64 * kSelWaves) void topk_select_kernel(SelectArgs a) {
-  extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
-  __shared__ int32_t cand[kSelWaves][kMaxCand];
-  __shared__ uint8_t cand_take[kSelWaves][kMaxCand];
+__global__ __launch_bounds__(64 * kSelWaves) __attribute__((amdgpu_waves_per_eu(KPL <= 64 ? 3 : 1)))
+void topk_select_kernel(SelectArgs a) {
+  struct Candidates {
+    int32_t column[kMaxCand];
+    uint8_t take[kMaxCand];
+  };
+  static_assert(kPinStage * kSelWaves >= (int)sizeof(Candidates) * kSelWaves, "one array for both");
+  __shared__ __attribute__((aligned(16))) uint8_t smem[kPinStage * kSelWaves];
+  __shared__ PinnedSelect pinned;
   __shared__ int32_t unsettled[kSelWaves];
   constexpr int kG = VEC ? 4 : 1;  // registers of one column group
   constexpr bool kLong = KPL > 16;
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   const int64_t row0 = (int64_t)blockIdx.x * kSelWaves;
   const int32_t nkb = a.nkb;
+  Candidates& cand = reinterpret_cast<Candidates*>(smem)[wv];
   auto column = [&](int j) { return VEC ? 256 * (j / 4) + 4 * lane + j % 4 : 64 * j + lane; };
   // the diagonal: columns [lo / bkv, (hi - 1) / bkv] for the row's tokens
   // [lo, hi) that also exist as keys
@@ -599,23 +669,20 @@ __global__ __launch_bounds__(64 * kSelWaves) void topk_select_kernel(SelectArgs 
         int32_t pos = group(g, base, bits);
 #pragma unroll
         for (int j = 0; j < kG; ++j)
-          if ((bits[j] >> lane) & 1ull) cand[wv][pos++] = column(g + j);
+          if ((bits[j] >> lane) & 1ull) cand.column[pos++] = column(g + j);
       }
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
       __builtin_amdgcn_wave_barrier();
       uint64_t mine = 0;  // lane i: candidate i's pinned score
-#pragma unroll 1
-      for (int32_t i = 0; i < m; ++i) {
-        const int32_t c = __builtin_amdgcn_readfirstlane(cand[wv][i]);
-        const uint64_t s = order_key(pinned_score_wave(q, pk + (int64_t)c * kHeadDim));
-        if (lane == i) mine = s;
-      }
+      if (lane < m) mine = order_key(pinned_score(uniform_row(q), pk + (int64_t)cand.column[lane] * kHeadDim));
       int32_t rank = 0;
 #pragma unroll 1
       for (int32_t i = 0; i < m; ++i) {
         const uint64_t other = (uint64_t)__shfl((unsigned long long)mine, i, 64);
         rank += (other > mine || (other == mine && i < lane)) ? 1 : 0;
       }
-      if (lane < m) cand_take[wv][lane] = rank < need ? 1 : 0;
+      if (lane < m) cand.take[lane] = rank < need ? 1 : 0;
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
       __builtin_amdgcn_wave_barrier();
     }
     int32_t base = 0;
@@ -628,7 +695,7 @@ __global__ __launch_bounds__(64 * kSelWaves) void topk_select_kernel(SelectArgs 
       for (int j = 0; j < kG; ++j) {
         bool take = key[g + j] > to;
         if ((bits[j] >> lane) & 1ull) {
-          take = zero ? pos < need : cand_take[wv][pos] != 0;
+          take = zero ? pos < need : cand.take[pos] != 0;
           ++pos;
         }
         word |= (take ? 1u : 0u) << (8 * j);
@@ -642,19 +709,27 @@ __global__ __launch_bounds__(64 * kSelWaves) void topk_select_kernel(SelectArgs 
   if (lane == 0) unsettled[wv] = settled ? 0 : 1;
   __syncthreads();
   // (rare, and kept small: its registers would halve the waves in flight)
+  uint64_t* keys = reinterpret_cast<uint64_t*>(a.scores + row0 * nkb);
 #pragma unroll 1
   for (int w = 0; w < kSelWaves; ++w) {
     if (!unsettled[w]) continue;
-    const int64_t row = row0 + w;
-    uint64_t* keys = reinterpret_cast<uint64_t*>(smem);
-    uint8_t* take = smem + (size_t)nkb * 8;
-    select_row_pinned(a.pq + row * kHeadDim, a.pk + row / a.nqb * nkb * kHeadDim, nkb, a.k, keys, take);
-    int32_t d0, d1;
-    diagonal(row, &d0, &d1);
-    uint8_t* out = mask_row(row);
-#pragma unroll 1
-    for (int32_t kb = tid; kb < nkb; kb += 64 * kSelWaves) out[kb] = (take[kb] || (kb >= d0 && kb <= d1)) ? 1 : 0;
+    const int64_t row = row0 + w, bhl = (uint32_t)row / (uint32_t)a.nqb;
+    // the next such row of the same head goes with it
+    int w2 = w + 1;
+    while (w2 < kSelWaves && !unsettled[w2]) ++w2;
+    const bool pair = w2 < kSelWaves && (uint32_t)(row0 + w2) / (uint32_t)a.nqb == bhl;
+    const double* q = a.pq + row * kHeadDim;
+    pinned_keys(uniform_row(q), uniform_row(pair ? a.pq + (row0 + w2) * kHeadDim : q), a.pk + bhl * nkb * kHeadDim, nkb,
+                keys, keys + nkb, smem);
     __syncthreads();
+#pragma unroll 1
+    for (int i = 0; i < (pair ? 2 : 1); ++i) {
+      const int64_t r = i ? row0 + w2 : row;
+      int32_t d0, d1;
+      diagonal(r, &d0, &d1);
+      select_pinned(keys + i * nkb, nkb, a.k, d0, d1, mask_row(r), pinned);
+    }
+    if (pair) w = w2;
   }
 }
 
@@ -663,9 +738,8 @@ hipError_t launch_select(const SelectArgs& a, hipStream_t s) {
   const bool vec = a.nkb % 4 == 0 && (reinterpret_cast<uintptr_t>(a.scores) & 15) == 0 &&
                    (reinterpret_cast<uintptr_t>(a.mask) & 3) == 0;
   const dim3 grid((unsigned)((a.rows + kSelWaves - 1) / kSelWaves)), block(64 * kSelWaves);
-  const size_t lds = (size_t)a.nkb * 9;  // the pinned path's keys and flags
-  if (vec) hipLaunchKernelGGL((topk_select_kernel<KPL, true>), grid, block, lds, s, a);
-  else hipLaunchKernelGGL((topk_select_kernel<KPL, false>), grid, block, lds, s, a);
+  if (vec) hipLaunchKernelGGL((topk_select_kernel<KPL, true>), grid, block, 0, s, a);
+  else hipLaunchKernelGGL((topk_select_kernel<KPL, false>), grid, block, 0, s, a);
   return hipGetLastError();
 }
 
@@ -674,9 +748,10 @@ constexpr int64_t kBigTileMin = 512;
 
 }  // namespace
 
-// KV blocks per score row: the keys and flags of a row (9 bytes per block)
-// stay within 64 KB of LDS
+// KV blocks per score row: a wave holds its row's keys in registers, 96 a lane
 int32_t sparsify_max_kv_blocks() { return 6144; }
+
+int64_t sparsify_score_rows(int64_t rows) { return (rows + kSelWaves - 1) / kSelWaves * kSelWaves; }
 
 hipError_t launch_block_mean(const MeanArgs& a, hipStream_t s) {
   const int64_t blocks = (int64_t)a.nbh * (a.nb[0] + (int64_t)a.nb[1]);

@@ -106,3 +106,48 @@ def test_layouts_of_the_block_means(offset, pad):
     got = bsa.sparsify_topk(strided(qb), strided(kb), 32, 32, 4)
     torch.cuda.synchronize()
     assert np.array_equal(got.cpu().numpy(), want)
+
+
+# two heads of seven rows: rows of both in one workgroup, a last one of two
+# rows; rows shorter and longer than a wave's and a workgroup's step
+@pytest.mark.parametrize("nkb", [2, 63, 65, 257, 1026, 4100, 6144])
+def test_undecided_rows_of_every_length(nkb):
+    q, k = _qk(nkb + 1, 1, 2, 7 * 16 - 3, nkb * 16)
+    log("nkb %d" % nkb)
+    _check(q, k * np.float32(1e-14), 16, 16, max(1, nkb // 8), what="out of range, nkb %d" % nkb)
+    k[:, nkb // 3 * 16:] = 0.0
+    _check(q, k, 16, 16, max(1, nkb // 2), diagonal=False, what="tied, nkb %d" % nkb)
+
+
+def test_undecided_rows_stay_within_a_few_times_the_usual_cost():
+    """Rows that fp32 cannot decide (tied, not finite or out of range) are
+    selected in the pinned arithmetic.  With every row such a row the whole
+    selection takes 3.3 times the usual at this size; walking the mean keys
+    row by row it took 12 times."""
+    import torch
+    N, H, blk, topk = 65536, 8, 64, 123
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(17)
+    q, k = (torch.randn((1, N, H, 128), generator=gen, device="cuda").to(torch.bfloat16) for _ in range(2))
+    mask = torch.empty((1, H, N // blk, N // blk), dtype=torch.uint8, device="cuda")
+
+    def ms(kk):
+        best = float("inf")
+        for _ in range(6):
+            e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            e0.record()
+            bsa.sparsify_topk(q, kk, blk, blk, topk, mask=mask)
+            e1.record()
+            e1.synchronize()
+            best = min(best, e0.elapsed_time(e1))
+        return best
+    usual = ms(k)
+    tail = k.clone()
+    tail[:, N // 10:] = 0
+    nan = k.clone()
+    nan[:, 5] = float("nan")
+    for name, kk in (("zero tail", tail), ("all zero", torch.zeros_like(k)), ("not a number", nan),
+                     ("out of range", k * 1e-14)):
+        t = ms(kk)
+        log("%s: %.3f ms, usual %.3f ms" % (name, t, usual))
+        assert t < 7.0 * usual, (name, t, usual)
