@@ -1266,10 +1266,11 @@ hipError_t sparsify_passes(const void* q, const void* k, const bsa_shapes& s, in
   return e;
 }
 
-// Heads of one pass: at most `room` bytes of `per` bytes a head, and what one
-// launch's grid can hold.
-int64_t sparsify_heads_per_pass(int64_t nbh, int64_t room, int64_t per) {
-  return std::max<int64_t>(1, std::min<int64_t>({nbh, room / per, 65535}));
+// Heads of one pass: at most `room` bytes of `per` bytes a head, and what a
+// launch can hold, fewer than 2^32 threads: the block means take up to 128
+// threads a block of queries or keys, the other kernels less.
+int64_t sparsify_heads_per_pass(int64_t nbh, int64_t room, int64_t per, int64_t nqb, int64_t nkb) {
+  return std::max<int64_t>(1, std::min<int64_t>({nbh, room / per, ((int64_t(1) << 25) - 2) / (nqb + nkb)}));
 }
 
 // Scratch of the allocation-free sparsifier: one copy per device, resident
@@ -1314,7 +1315,7 @@ bsa_status bsa_sparsify_topk(const void* q, const void* k, const bsa_shapes* sha
   prepare_pool(dev);
   // heads per pass: score rows of at most 256 MiB
   const int64_t chunk = sparsify_heads_per_pass((int64_t)s.batch * s.heads, int64_t(256) << 20,
-                                                nqb * nkb * (int64_t)sizeof(float));
+                                                nqb * nkb * (int64_t)sizeof(float), nqb, nkb);
   void* work = nullptr;
   HIP_TRY(hipMallocAsync(&work, (size_t)sparsify_bytes(chunk, nqb, nkb), stream));
   const hipError_t e = sparsify_passes(q, k, s, bq, bkv, topk, diagonal, mask, nqb, nkb, chunk, work, stream);
@@ -1344,7 +1345,7 @@ bsa_status bsa_sparsify_topk_noalloc(const void* q, const void* k, const bsa_sha
   if ((st = scratch_address(dev, &work)) != BSA_OK) return st;
   const int64_t slack = sparsify_score_rows(1) * nkb * (int64_t)sizeof(float);  // rows rounded up
   const int64_t chunk = sparsify_heads_per_pass((int64_t)s.batch * s.heads, kNoAllocScratchBytes - slack,
-                                                sparsify_bytes(1, nqb, nkb));
+                                                sparsify_bytes(1, nqb, nkb), nqb, nkb);
   // every byte of the scratch that a pass reads is written earlier in the
   // same pass (means before scores, scores before the selection), so nothing
   // needs clearing

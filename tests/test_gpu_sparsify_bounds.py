@@ -151,3 +151,24 @@ def test_undecided_rows_stay_within_a_few_times_the_usual_cost():
         t = ms(kk)
         log("%s: %.3f ms, usual %.3f ms" % (name, t, usual))
         assert t < 7.0 * usual, (name, t, usual)
+
+
+def test_more_blocks_than_one_launch_holds():
+    """10922 heads of 6144 one-token blocks, 2-byte aligned: more threads than
+    one launch of the block means takes, so the heads go in several passes."""
+    import torch
+    H, n = 10922, 6144
+    free = torch.cuda.mem_get_info()[0]
+    if free < 40 << 30:
+        pytest.skip("needs 40 GB of device memory")
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(19)
+    q = torch.randn((1, 1, H, 128), generator=gen, device="cuda").to(torch.bfloat16)
+    flat = torch.empty(n * H * 128 + 1, dtype=torch.bfloat16, device="cuda")
+    k = flat[1:].view(1, n, H, 128)
+    for i in range(0, n, 256):
+        k[:, i:i + 256].normal_(generator=gen)
+    got = bsa.sparsify_topk(q, k, 1, 1, 100)
+    for h0 in range(0, H, 4000):
+        part = bsa.sparsify_topk(q[:, :, h0:h0 + 4000], k[:, :, h0:h0 + 4000], 1, 1, 100)
+        assert torch.equal(got[:, h0:h0 + 4000], part), h0
