@@ -855,15 +855,13 @@ void attn_fwd_kernel(AttnArgs a) {
 // whole forward pass of a 16384-token, 12-head, 15% top-k request with S = 8
 // went from 2.53 to 0.78 ms, of 104 rows of 314 tiles from 0.134 to 0.085 ms.
 constexpr int kMergeBatch = 8;  // partial states loaded together
-constexpr int kMergeRows = 8;
 
 template <int TQ>
-__global__ __launch_bounds__(32 * kMergeRows) void splitk_merge_kernel(AttnArgs a) {
-  constexpr int kParts = TQ / kMergeRows;
-  const int64_t ti = a.row_task[blockIdx.x / kParts];
+__global__ __launch_bounds__(kMergeThreads) void splitk_merge_kernel(AttnArgs a) {
+  const int64_t ti = a.row_task[blockIdx.x];
   const Task task = a.tasks[ti];
   if (task.nsplit <= 1) return;
-  const int ql = (int)(blockIdx.x % kParts) * kMergeRows + (threadIdx.x >> 5);
+  const int ql = (int)blockIdx.y * (int)kMergeRows + (threadIdx.x >> 5);
   const int col = (threadIdx.x & 31) * 4;
   const int qrow = task.pq * TQ + ql;
   if (qrow >= a.Nq) return;
@@ -957,7 +955,7 @@ hipError_t launch_attention(int tq, int tkv, int waves, int stages, const AttnAr
 
 hipError_t launch_splitk_merge(int tq, const AttnArgs& a, hipStream_t s) {
   if (a.nrows == 0) return hipSuccess;
-  const dim3 grid((unsigned)(a.nrows * (tq / kMergeRows))), block(32 * kMergeRows);
+  const dim3 grid((unsigned)merge_grid_x(a.nrows), (unsigned)merge_grid_y(tq)), block(kMergeThreads);
   if (tq == 64) hipLaunchKernelGGL(splitk_merge_kernel<64>, grid, block, 0, s, a);
   else if (tq == 128) hipLaunchKernelGGL(splitk_merge_kernel<128>, grid, block, 0, s, a);
   else if (tq == 256) hipLaunchKernelGGL(splitk_merge_kernel<256>, grid, block, 0, s, a);

@@ -1,5 +1,5 @@
-// Which task each launch slot of the attention kernel runs, and the shares of
-// the task list that the XCD groups take.  Plain integer code: the kernel
+// Which task each launch slot of the attention kernel runs, the shares of the
+// task list that the XCD groups take, and the merge's grid.  Plain integer code: the kernel
 // evaluates task_of_slot on the device (a constexpr function is callable from
 // device code), the planner and the host tests on the host.
 #pragma once
@@ -57,6 +57,15 @@ constexpr int64_t task_of_slot(int64_t slot, int64_t nt, int64_t group, int64_t 
 
 // Launch slots for equal shares: the task count rounded up to a multiple of 8.
 constexpr int64_t default_slots(int64_t nt) { return (nt + 7) / 8 * 8; }
+
+// Workgroups of the Split-K merge, kMergeRows query rows each: (physical rows,
+// parts of a row).  A launch dimension holds fewer than 2^32 threads, so with
+// kMergeThreads a workgroup the rows of the largest plans (below 2^24) have one
+// to themselves.
+constexpr int64_t kMergeRows = 8;
+constexpr int64_t kMergeThreads = 32 * kMergeRows;
+constexpr int64_t merge_grid_x(int64_t nrows) { return nrows; }
+constexpr int64_t merge_grid_y(int64_t tq) { return tq / kMergeRows; }
 
 // Launch slots for given shares share_lo[0 .. 8 / group] (group >= 2): eight
 // times the most tasks one XCD of any group takes.

@@ -1,6 +1,6 @@
 // Host check of the attention kernel's slot map (slot_map.h): for equal
 // shares and for work-balanced shares, every task of [0, nt) has exactly one
-// launch slot and every other slot maps to -1.  Exit status 0 and "ok N"
+// launch slot and every other slot maps to -1; and of the merge's grid.  Exit status 0 and "ok N"
 // when all configurations pass; the first failure is printed and exits 1.
 #include <cstdint>
 #include <cstdio>
@@ -94,6 +94,18 @@ int main() {
       }
     }
   }
+  // the merge's grid: 8 query rows per workgroup, and launchable (fewer than
+  // 2^32 threads a dimension) for every row count whose tasks are
+  for (int64_t tq : {64, 128, 256})
+    for (int64_t nrows : {int64_t(1), int64_t(1) << 21, (int64_t(1) << 24) - 1}) {
+      const int64_t x = bsa::merge_grid_x(nrows), y = bsa::merge_grid_y(tq);
+      if (x * y != nrows * tq / 8 || x * bsa::kMergeThreads >= (int64_t(1) << 32) || y > 65535) {
+        std::printf("FAIL merge grid: %lld x %lld for %lld rows of %lld\n", (long long)x, (long long)y,
+                    (long long)nrows, (long long)tq);
+        return 1;
+      }
+      ++checks;
+    }
   std::printf("ok %ld\n", checks);
   return 0;
 }
