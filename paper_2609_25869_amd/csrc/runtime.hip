@@ -356,32 +356,20 @@ int32_t slice_rows(const Segment& sg, int64_t logical_rows) {
   return (int32_t)std::max<int64_t>(split, s);
 }
 
-// Launch slots per kernel launch; 0: all tasks in one launch.  The tasks an
-// XCD runs at once read the same head's K/V in the same order, and share L2
-// lines while they are about equally far.  They start together but drift
-// apart over the generations of a long launch; a launch per generation lines
-// them up again, for the wait on its slowest task and about 6 us.  That pays
-// for the T_Q = 64 kernels, which read the most K/V per flop, and there
-// - where a head's K/V is several times an XCD's L2 (4 MB): over the rule's
-//   other conditions a mean of 0.83 of the time at 115200 tokens (none of 258
-//   slower by 3%), 0.89 at 65536 (none of 174), 0.98 at 32768 (33 of 162);
-// - where the rows are about equally long (with the longest above 1.4 times
-//   the mean the wait costs more: 0.89 within, 1.0 above);
-// - where they are scattered: the long runs of windows share lines between
-//   neighbours anyway (5% window of 131072 tokens 4.20 and 4.59 ms);
-// - where a query block is at most one task's rows: the tasks of a larger
-//   block share their list and run side by side (128-token blocks: 0.97, the
-//   fastest plan unchanged).
-// 12% top-k of 64-token blocks, T = (64, 32) in two slots, 24 heads x 115200
-// tokens 35.1 -> 21.9 ms (the fastest without: 24.5 ms), 12 x 65536 4.83 ->
-// 3.39; 12% Bernoulli 12 x 65536 5.45 -> 4.19; T_Q = 128 within 2%.
-constexpr int64_t kGenerationSlots = 1024;      // four 2-wave workgroups on each of 256 CUs
-constexpr int64_t kGenerationKvBytes = 32 << 20;
+// Launch slots per kernel launch of a segment (generation_slots).
 int64_t launch_slots(const Segment& sg, int64_t logical_rows, int32_t seq_kv) {
-  if (sg.plan.tq != 64 || sg.bq > 64 || sg.slices != 1 || sg.Rp < 2 * kGenerationSlots) return 0;
-  if ((int64_t)seq_kv * kHeadDim * 4 < kGenerationKvBytes) return 0;
-  if (sg.max_row_nnz * logical_rows * 5 > sg.nnz * 7 || sg.run_blocks * 3 > sg.nnz * 2) return 0;
-  return kGenerationSlots;
+  GenerationQuery z{};
+  z.tq = sg.plan.tq;
+  z.bq = sg.bq;
+  z.bkv = sg.bkv;
+  z.slices = sg.slices;
+  z.tasks = sg.Rp;
+  z.logical_rows = logical_rows;
+  z.nnz = sg.nnz;
+  z.max_row_nnz = sg.max_row_nnz;
+  z.run_blocks = sg.run_blocks;
+  z.kv_bytes = (int64_t)seq_kv * kHeadDim * 4;
+  return generation_slots(z);
 }
 
 bool runs_compacted(const Segment& sg) {

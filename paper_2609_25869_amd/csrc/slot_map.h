@@ -1,5 +1,6 @@
 // Which task each launch slot of the attention kernel runs, the shares of the
-// task list that the XCD groups take, and the merge's grid.  Plain integer code: the kernel
+// task list that the XCD groups take, how many slots a launch has, and the
+// merge's grid.  Plain integer code: the kernel
 // evaluates task_of_slot on the device (a constexpr function is callable from
 // device code), the planner and the host tests on the host.
 #pragma once
@@ -57,6 +58,48 @@ constexpr int64_t task_of_slot(int64_t slot, int64_t nt, int64_t group, int64_t 
 
 // Launch slots for equal shares: the task count rounded up to a multiple of 8.
 constexpr int64_t default_slots(int64_t nt) { return (nt + 7) / 8 * 8; }
+
+// Launch slots per kernel launch; 0: all tasks in one launch.  The tasks an
+// XCD runs at once read the same head's K/V in the same order, and share L2
+// lines while they are about equally far.  They start together but drift
+// apart over the generations of a long launch; a launch per generation lines
+// them up again, for the wait on its slowest task and about 7 us.  That pays
+// for the T_Q = 64 kernels, which read the most K/V per flop, and there
+// - where a head's K/V is several times an XCD's L2 (4 MB): over the rule's
+//   other conditions a mean of 0.83 of the time at 115200 tokens (none of 258
+//   slower by 3%), 0.89 at 65536 (none of 174), 0.98 at 32768 (33 of 162);
+// - where the rows are about equally long (with the longest above 1.4 times
+//   the mean the wait costs more: 0.89 within, 1.0 above);
+// - where they are scattered: the long runs of windows share lines between
+//   neighbours anyway (5% window of 131072 tokens 4.20 and 4.59 ms);
+// - where a query block is at most one task's rows: the tasks of a larger
+//   block share their list and run side by side (128-token blocks: 0.97, the
+//   fastest plan unchanged);
+// - where a task has about 2048 keys or more: 131072 tokens x 24 heads with
+//   equally long random rows under the three T_Q = 64 kernels 1.6 times at none,
+//   1.25 at 512, 1.08 to 1.15 at 1024, 0.99 to 1.06 at 1536, 0.94 to 1.0 at
+//   2048 and 0.70 to 0.92 at 8192 keys a row; of 32-token blocks, two to a
+//   task, 0.97 to 1.06 at 512 and 0.84 to 0.97 at 1024.
+// 12% top-k of 64-token blocks, T = (64, 32) in two slots, 24 heads x 115200
+// tokens 35.1 -> 21.9 ms (the fastest without: 24.5 ms), 12 x 65536 4.83 ->
+// 3.39; 12% Bernoulli 12 x 65536 5.45 -> 4.19; T_Q = 128 within 2%.
+constexpr int64_t kGenerationSlots = 1024;      // four 2-wave workgroups on each of 256 CUs
+constexpr int64_t kGenerationKvBytes = 32 << 20;
+constexpr int64_t kGenerationKeys = 2048;
+struct GenerationQuery {
+  int32_t tq, bq, bkv, slices;
+  int64_t tasks, logical_rows, nnz, max_row_nnz, run_blocks;
+  int64_t kv_bytes;  // K and V of one head
+};
+constexpr int64_t generation_slots(const GenerationQuery& z) {
+  if (z.tq != 64 || z.bq > 64 || z.slices != 1 || z.tasks < 2 * kGenerationSlots) return 0;
+  if (z.kv_bytes < kGenerationKvBytes) return 0;
+  if (z.max_row_nnz * z.logical_rows * 5 > z.nnz * 7 || z.run_blocks * 3 > z.nnz * 2) return 0;
+  // a task's keys are at most the keys of its query blocks' rows together,
+  // and close to them where few blocks are active
+  if (z.nnz * z.bkv / z.logical_rows * (z.tq / z.bq) < kGenerationKeys) return 0;
+  return kGenerationSlots;
+}
 
 // Workgroups of the Split-K merge, kMergeRows query rows each: (physical rows,
 // parts of a row).  A launch dimension holds fewer than 2^32 threads, so with

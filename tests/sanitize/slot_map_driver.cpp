@@ -1,7 +1,8 @@
 // Host check of the attention kernel's slot map (slot_map.h): for equal
 // shares and for work-balanced shares, every task of [0, nt) has exactly one
-// launch slot and every other slot maps to -1; and of the merge's grid.  Exit status 0 and "ok N"
-// when all configurations pass; the first failure is printed and exits 1.
+// launch slot and every other slot maps to -1; and of the rule for a launch
+// per generation and the merge's grid.  Exit status 0 and "ok N" when all
+// configurations pass; the first failure is printed and exits 1.
 #include <cstdint>
 #include <cstdio>
 #include <random>
@@ -93,6 +94,31 @@ int main() {
         ++checks;
       }
     }
+  }
+  // a launch per generation: rows of no, one, few and enough keys
+  {
+    bsa::GenerationQuery z{};
+    z.tq = 64;
+    z.bq = 64;
+    z.bkv = 64;
+    z.slices = 1;
+    z.tasks = z.logical_rows = 24 * 2048;
+    z.kv_bytes = int64_t(131072) * 512;
+    for (int64_t blocks : {0, 1, 8, 31, 32, 256})
+      for (int32_t bq : {64, 32, 16}) {
+        z.bq = bq;
+        z.logical_rows = z.tasks * (64 / bq);
+        z.max_row_nnz = blocks;
+        z.nnz = blocks * z.logical_rows;
+        z.run_blocks = z.nnz / 16;
+        const int64_t want = blocks * 64 * (64 / bq) >= 2048 ? 1024 : 0;
+        if (bsa::generation_slots(z) != want) {
+          std::printf("FAIL generations: %lld slots for %lld blocks a row of %d\n",
+                      (long long)bsa::generation_slots(z), (long long)blocks, bq);
+          return 1;
+        }
+        ++checks;
+      }
   }
   // the merge's grid: 8 query rows per workgroup, and launchable (fewer than
   // 2^32 threads a dimension) for every row count whose tasks are
