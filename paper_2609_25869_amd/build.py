@@ -40,13 +40,13 @@ def common_flags():
             "-fvisibility=hidden"]
 
 
-# Per-file flags.  The attention kernel never produces NaN from finite
-# inputs (masked scores are -inf, and exp2(-inf) = 0), so NaN-quieting of
-# max operands is not needed there.
-# Its score tiles are VALU operands, so MFMA results stay in VGPRs; the
-# compiler's default for kernels with one wave per SIMD is AGPRs, from which
-# every score element would first be copied.
-EXTRA_FLAGS = {"attn_fwd.hip": ["-fno-honor-nans", "-mllvm", "-amdgpu-mfma-vgpr-form"],
+# Per-file flags.  The score tiles are VALU operands, so MFMA results stay in
+# VGPRs; the compiler's default for kernels with one wave per SIMD is AGPRs,
+# from which every score element would first be copied.  No flag may let the
+# compiler assume that there is no NaN: the attention kernel masks through the
+# addend of the exponent and finds masked scores that are not finite by the
+# NaN they give.
+EXTRA_FLAGS = {"attn_fwd.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
                "sparsify.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"]}
 
 

@@ -54,18 +54,24 @@ def test_tile_lists_match_oracle(name):
         p.destroy()
 
 
-def test_infinite_keys_of_inactive_blocks_change_nothing():
-    """Masking must hold for scores that are not finite: infinite K rows in
-    blocks a query row does not use leave its output bitwise unchanged, also
-    where a tile shares the block with rows that do use it."""
-    for geom, ids in (((16, 16), (0, 4, 8, 12, 30)), ((32, 32), (0, 4, 8, 12, 20, 30)), ((64, 64), (8, 12, 20))):
+# K rows of +inf (scores of +inf, -inf or NaN), and finite ones whose scores
+# overflow to +inf and -inf (the queries have one sign)
+@pytest.mark.parametrize("fill,one_sign", [(np.inf, False), (3e38, True), (-3e38, True), (np.inf, True)])
+def test_infinite_keys_of_inactive_blocks_change_nothing(fill, one_sign):
+    """Masking must hold for scores that are not finite: K rows that make them
+    so, in blocks a query row does not use, leave its output bitwise unchanged,
+    also where a tile shares the block with rows that do use it."""
+    for geom, ids in (((16, 16), (0, 4, 8, 12, 20, 30, 32)), ((32, 32), (0, 4, 8, 12, 16, 20, 30)),
+                      ((64, 64), (8, 12, 16, 20, 32))):
         q, k, v, mask = random_case(907, 1, 1, 384, 384, 128, [geom], 0.3)
+        if one_sign:
+            q = q & np.uint16(0x7FFF)
         m = mask.head(0, 0) != 0
         kb = int(np.argmax((~m).sum(0) * m.any(0)))   # used by some rows, not by others
         rows = [r for r in range(m.shape[0]) if not m[r, kb]]
         assert rows and len(rows) < m.shape[0]
         k2 = k.copy()
-        k2[0, kb * geom[1]:(kb + 1) * geom[1], 0, :] = bf16_bits_from_f32(np.full((geom[1], 128), np.inf, np.float32))
+        k2[0, kb * geom[1]:(kb + 1) * geom[1], 0, :] = bf16_bits_from_f32(np.full((geom[1], 128), fill, np.float32))
         for pid in ids:
             log("geometry %s plan %d" % (geom, pid))
             p, a, la, _ = run_plan(bsa, mask, q, k, v, force_plan=pid)
