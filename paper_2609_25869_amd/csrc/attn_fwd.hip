@@ -95,13 +95,27 @@ struct Cfg {
   static constexpr int kTileBytes = TKV * kRowBytes;
 };
 
-// Value of the same register in lane l ^ 32 (the other half of the wave).
-__device__ inline uint32_t other_half_u32(uint32_t x) {
+// The lane index, formed again where it is used: the rare paths and the
+// epilogue then keep no registers through the loop for it.  (The 8-wave kernel
+// with four slots had 2 to 8 of them in scratch memory: (128, 128) top-k blocks,
+// 115200 tokens, 4 heads 6.8 ms with 8, 6.2 with 2, 6.0 with none.  The kernel
+// of two row groups, G = 2, has them in AGPRs and does not gain.)
+__device__ inline int lane_now() {
+  int l = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
+  asm volatile("" : "+v"(l));
+  return l;
+}
+
+// Value of the same register in lane l ^ 32 (the other half of the wave that
+// lane `lane` is in).
+__device__ inline uint32_t other_half_u32(uint32_t x, int lane) {
   const auto r = __builtin_amdgcn_permlane32_swap(x, x, false, false);
   // lanes 0-31 find the partner in r[1], lanes 32-63 in r[0]; the other entry is x itself
-  return (threadIdx.x & 32) ? r[0] : r[1];
+  return (lane & 32) ? r[0] : r[1];
 }
-__device__ inline float other_half(float x) { return __uint_as_float(other_half_u32(__float_as_uint(x))); }
+__device__ inline float other_half(float x, int lane) {
+  return __uint_as_float(other_half_u32(__float_as_uint(x), lane));
+}
 
 // In-place updates for the rare paths (rescale, masking).  The tied
 // operands pin each result to the register it came from; written as plain
@@ -230,6 +244,7 @@ void attn_fwd_kernel(AttnArgs a) {
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave index (uniform)
   const int n = lane & 31;   // query row of this lane inside a 32-row group
   const int hh = lane >> 5;  // lane half
+  auto lane_late = [&]() -> int { return G == 1 ? lane_now() : lane; };  // for the rare paths and the epilogue
   const int b = task.bh / a.H, h = task.bh - b * a.H;
   const int q0 = task.pq * C::kTQ;
   // row of group g inside the task's query tile, and in the sequence
@@ -267,8 +282,8 @@ void attn_fwd_kernel(AttnArgs a) {
   const int tb = task.tile_begin;
   const int n_ent = task.tile_end - tb;
   const int nkv_tiles = (n_ent + kEnt - 1) / kEnt;
-  auto load_ids = [&](int base) -> int { return a.kv_tile[tb + min(base + lane, n_ent - 1)]; };
-  auto load_bits = [&](int base) -> uint64_t { return a.member[tb + min(base + lane, n_ent - 1)]; };
+  auto load_ids = [&](int base) -> int { return a.kv_tile[tb + min(base + lane_late(), n_ent - 1)]; };
+  auto load_bits = [&](int base) -> uint64_t { return a.member[tb + min(base + lane_late(), n_ent - 1)]; };
 
   // ---- K/V tiles: buffer loads straight into LDS
   // One instruction moves 64 lanes x 16 bytes = 4 token rows into 1 KB of
@@ -450,7 +465,7 @@ void attn_fwd_kernel(AttnArgs a) {
       keys &= nvalid >= 64 ? ~0ull : ((1ull << nvalid) - 1);
       allowed |= keys << (e * UNIT);
     }
-    const uint64_t mine = allowed >> (4 * hh);
+    const uint64_t mine = allowed >> (4 * (lane_late() >> 5));
 #pragma unroll
     for (int kb = 0; kb < kNKB; ++kb) {
 #pragma unroll
@@ -464,6 +479,29 @@ void attn_fwd_kernel(AttnArgs a) {
     return allowed != 0;
   };
 
+  // The same for 64-key tiles of 16-token blocks with every key inside the
+  // sequence: the eight scores of a lane that share a block share a condition
+  // (an addend per block, see below, would need registers that these kernels do
+  // not have).  10% of (16, 16) blocks, 65536 tokens, 4 heads, T = (128, 64):
+  // 9.2 ms masked score by score, 8.2 so; T = (64, 64) 11.0 and 9.7.
+  constexpr bool kMask16 = TKV == 64;
+  auto mask_blocks16 = [&](f32x16* s, const Bits& bits, int mrow) -> bool {
+    const uint32_t row = (uint32_t)(bits.m[0] >> (mrow * 4));
+    bool any = false;
+#pragma unroll
+    for (int blk = 0; blk < 4; ++blk) {
+      const bool keep = (row >> blk) & 1u;
+      any = any || keep;
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        float x = s[blk / 2][8 * (blk % 2) + i];
+        mask_inplace(x, keep);
+        s[blk / 2][8 * (blk % 2) + i] = x;
+      }
+    }
+    return any;
+  };
+
   // Row maximum of one group's raw scores in a tile (the scale is positive),
   // both lane halves combined.
   auto row_max = [&](const f32x16* s) -> float {
@@ -473,7 +511,7 @@ void attn_fwd_kernel(AttnArgs a) {
 #pragma unroll
       for (int i = 0; i < 16; i += 2) mx = max3(mx, s[kb][i], s[kb][i + 1]);
     }
-    return max3(mx, mx, other_half(mx));
+    return max3(mx, mx, other_half(mx, lane_late()));
   };
 
   // Distribution of the VALU work of one iteration over its MFMAs.
@@ -557,6 +595,9 @@ void attn_fwd_kernel(AttnArgs a) {
           }
           active[g] = any;
         }
+      } else if (kMask16 && a.gkv == 4 && !past) {
+#pragma unroll
+        for (int g = 0; g < G; ++g) active[g] = mask_blocks16(s_cur + g * kNKB, bits_cur, mem_row[g]);
       } else {
 #pragma unroll
         for (int g = 0; g < G; ++g) active[g] = apply_mask(s_cur + g * kNKB, kv0_cur, bits_cur, mem_row[g]);
@@ -764,7 +805,7 @@ void attn_fwd_kernel(AttnArgs a) {
           // runs in every lane (under a short-circuit || it would run only in
           // some lanes, and a lane swap there reads inactive partners)
           const uint32_t mine = needs_raise(g) ? 1u : 0u;
-          const bool row = (mine | other_half_u32(mine)) != 0;
+          const bool row = (mine | other_half_u32(mine, lane_late())) != 0;
           if (__ballot(row) != 0) lsum[g] = raise_reference(g, s_cur, pw_cur, row, lsum[g]);
         }
       }
@@ -810,10 +851,11 @@ void attn_fwd_kernel(AttnArgs a) {
   wait_vm_lgkm<0>();
 
   // ---- epilogue
+  const int n_end = lane_late() & 31, hh_end = lane_late() >> 5;
 #pragma unroll
   for (int g = 0; g < G; ++g) {
-    const float l_tot = l_run[g] + other_half(l_run[g]);
-    const int ql = q_local(g), qr = q_row(g);
+    const float l_tot = l_run[g] + other_half(l_run[g], lane_late());
+    const int ql = C::kRowsPerWave * w + 32 * g + n_end, qr = q0 + ql;
     if (task.nsplit == 1) {
       if (qr < a.Nq) {
         const float inv = l_tot > 0.f ? 1.f / l_tot : 0.f;
@@ -825,10 +867,10 @@ void attn_fwd_kernel(AttnArgs a) {
             bf16x4 v4;
 #pragma unroll
             for (int e = 0; e < 4; ++e) v4[e] = (__bf16)(o[g][dblk][4 * gg + e] * inv);
-            *reinterpret_cast<bf16x4*>(op + dblk * 32 + 8 * gg + 4 * hh) = v4;
+            *reinterpret_cast<bf16x4*>(op + dblk * 32 + 8 * gg + 4 * hh_end) = v4;
           }
         }
-        if (a.lse && hh == 0) {
+        if (a.lse && hh_end == 0) {
           a.lse[((int64_t)b * a.H + h) * a.Nq + qr] =
               l_tot > 0.f ? (m_run[g] + __log2f(l_tot)) * 0.69314718055994530942f : kNegInf;
         }
@@ -836,7 +878,7 @@ void attn_fwd_kernel(AttnArgs a) {
     } else {
       // Split-K partial state: reference m (log2 domain), l, O unnormalised
       float* slot = a.ws + ti * (int64_t)C::kTQ * (kD + 2);
-      if (hh == 0) {
+      if (hh_end == 0) {
         slot[ql] = l_tot > 0.f ? m_run[g] : kNegInf;
         slot[C::kTQ + ql] = l_tot;
       }
@@ -848,7 +890,7 @@ void attn_fwd_kernel(AttnArgs a) {
           f32x4 v4;
 #pragma unroll
           for (int e = 0; e < 4; ++e) v4[e] = o[g][dblk][4 * gg + e];
-          *reinterpret_cast<f32x4*>(os + dblk * 32 + 8 * gg + 4 * hh) = v4;
+          *reinterpret_cast<f32x4*>(os + dblk * 32 + 8 * gg + 4 * hh_end) = v4;
         }
       }
     }

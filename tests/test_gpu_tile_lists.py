@@ -30,7 +30,10 @@ CASES = [
     ("b32_long", 1, 200, 4700, (32, 32), 0.9, (0, 4, 8, 12, 20, 30)),    # 147 tiles with member words
     ("b64_long", 1, 200, 8200, (64, 64), 0.95, (0, 4, 8, 12, 16, 20, 30, 32)),
     ("b64_chunk", 1, 130, 64 * 64, (64, 64), 1.0, (0, 4, 12, 30)),  # exactly one and two chunks
-    ("b16_in_64", 1, 300, 1079, (16, 16), 0.25, (4, 12, 20)),       # four blocks along a 64-key tile
+    ("b16_in_64", 1, 300, 1079, (16, 16), 0.25, (4, 12, 20, 32)),   # four blocks along a 64-key tile
+    ("b32x16_in_64", 2, 513, 1216, (32, 16), 0.4, (4, 12, 20, 32)),  # whole tiles
+    ("b256x16_in_64", 1, 600, 1079, (256, 16), 0.4, (4, 12, 20, 32)),  # one query block and more per tile
+    ("b16x8_in_64", 1, 300, 1079, (64, 8), 0.4, (4, 12, 20, 32)),   # eight blocks along a tile
 ]
 
 
