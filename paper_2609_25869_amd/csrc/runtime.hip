@@ -426,6 +426,70 @@ bsa_status segment_tile_ptr(bsa_plan_t plan, const Segment& sg, std::vector<int6
 // Tasks of a physical row of n tiles under the plan's Split-K factor.
 int64_t plan_row_tasks(int64_t n, int64_t split) { return n == 0 ? 1 : std::min(n, split); }
 
+// The plan's tasks, from the task list that the device holds: read back and
+// expressed in the segment's own tile list.  The kernel's tasks may cut rows
+// further than the plan does (slice_rows) or run over the packed list; those
+// are joined into the ranges of their rows first, and the rows cut by the
+// plan's Split-K factor.
+struct TaskRow {
+  int64_t bh, pq, tile_begin, tile_end, split, nsplit;
+};
+static_assert(sizeof(TaskRow) == 48, "six 64-bit fields");
+
+bsa_status plan_tasks(bsa_plan_t plan, const Segment& sg, std::vector<TaskRow>* out) {
+  std::vector<int64_t> tiles;  // tile list offsets of the physical rows
+  bsa_status st = segment_tile_ptr(plan, sg, &tiles);
+  if (st != BSA_OK) return st;
+  int64_t nt = sg.Rp;
+  if (sg.slices > 1 && (st = read_device_i64(plan, sg.task_ptr + sg.Rp, &nt)) != BSA_OK) return st;
+  if (nt < 0 || nt > sg.run_bound) return fail(BSA_ERR_HIP, "the device's task count is out of range");
+  // offsets of the list the device's tasks refer to
+  const bool direct = sg.mapping == 0;
+  const int64_t nptr = (direct ? plan->R : sg.Rp) + 1;
+  std::vector<int64_t> ptr((size_t)nptr), logical;
+  std::vector<Task> t((size_t)nt);
+  HIP_TRY(hipMemcpyAsync(ptr.data(), direct ? plan->row_ptr_dev : sg.compact ? sg.run_ptr : sg.tile_ptr,
+                         sizeof(int64_t) * nptr, hipMemcpyDeviceToHost, plan->stream));
+  if (nt) HIP_TRY(hipMemcpyAsync(t.data(), sg.tasks, sizeof(Task) * nt, hipMemcpyDeviceToHost, plan->stream));
+  HIP_TRY(hipStreamSynchronize(plan->stream));
+  if (direct) logical = segment_logical_rows(plan, sg);
+  std::vector<int64_t> slot_of_head((size_t)plan->H, -1);
+  for (size_t j = 0; j < sg.heads.size(); ++j) slot_of_head[(size_t)sg.heads[j]] = (int64_t)j;
+  const int64_t nsh = (int64_t)sg.heads.size();
+  out->clear();
+  for (int64_t i = 0; i < nt;) {
+    const Task& f = t[(size_t)i];
+    const int64_t slot = f.bh < 0 ? -1 : slot_of_head[(size_t)(f.bh % plan->H)];
+    const int64_t r = (f.bh / plan->H * nsh + slot) * sg.npq + f.pq;
+    if (slot < 0 || f.pq < 0 || f.pq >= sg.npq || r >= sg.Rp) return fail(BSA_ERR_HIP, "a task of the device names no row");
+    const int64_t p = direct ? logical[(size_t)r] : r;
+    const int64_t shift_lo = tiles[(size_t)r] - ptr[(size_t)p], shift_hi = tiles[(size_t)r + 1] - ptr[(size_t)p + 1];
+    if (sg.slices == sg.plan.split && !sg.compact) {
+      out->push_back({f.bh, f.pq, f.tile_begin + shift_lo, f.tile_end + shift_lo, f.split, f.nsplit});
+      ++i;
+      continue;
+    }
+    int64_t n = 1;
+    for (; n < f.nsplit && i + n < nt; ++n) {
+      const Task& g = t[(size_t)(i + n)];
+      if (g.bh != f.bh || g.pq != f.pq || g.split != n || g.nsplit != f.nsplit ||
+          g.tile_begin != t[(size_t)(i + n - 1)].tile_end)
+        break;
+    }
+    if (f.split != 0 || n != f.nsplit) return fail(BSA_ERR_HIP, "the device's slices of a row do not join");
+    const int64_t lo = f.tile_begin + shift_lo, hi = t[(size_t)(i + n - 1)].tile_end + shift_hi;
+    i += n;
+    const int64_t parts = plan_row_tasks(hi - lo, sg.plan.split);
+    int64_t ordinal = 0;
+    for (int64_t k = 0; k < sg.plan.split; ++k) {
+      const int64_t b0 = lo + k * (hi - lo) / sg.plan.split, b1 = lo + (k + 1) * (hi - lo) / sg.plan.split;
+      if (b1 == b0 && !(hi == lo && k == 0)) continue;
+      out->push_back({f.bh, f.pq, b0, b1, ordinal++, parts});
+    }
+  }
+  return BSA_OK;
+}
+
 // Number of the plan's tasks (the kernel may run more: slice_rows).
 bsa_status plan_task_count(bsa_plan_t plan, const Segment& sg, int64_t* n) {
   *n = sg.Rp;
@@ -1114,30 +1178,12 @@ bsa_status bsa_plan_export(bsa_plan_t plan, int32_t segment, int32_t what, void*
       return copy_out(sg.member, sizeof(uint64_t) * (size_t)nt);
     }
     case BSA_EXPORT_TASKS: {
-      // the plan's tasks from its rows' tile ranges (the kernel's own list may
-      // be in dispatch order, compacted or cut further)
-      std::vector<int64_t> ptr;
-      if ((st = segment_tile_ptr(plan, sg, &ptr)) != BSA_OK) return st;
-      const int64_t split = sg.plan.split;
-      int64_t nt = 0;
-      for (int64_t r = 0; r < sg.Rp; ++r) nt += plan_row_tasks(ptr[(size_t)r + 1] - ptr[(size_t)r], split);
-      *needed = sizeof(int64_t) * 6 * (size_t)nt;
+      std::vector<TaskRow> rows;
+      if ((st = plan_tasks(plan, sg, &rows)) != BSA_OK) return st;
+      *needed = sizeof(TaskRow) * rows.size();
       if (!host_buf) return BSA_OK;
       if (bytes < *needed) return fail(BSA_ERR_INVALID, "export buffer too small");
-      int64_t* dst = static_cast<int64_t*>(host_buf);
-      const int64_t nsh = (int64_t)sg.heads.size();
-      for (int64_t r = 0; r < sg.Rp; ++r) {
-        const int64_t b = r / (nsh * sg.npq), bh = b * plan->H + sg.heads[(size_t)(r / sg.npq % nsh)];
-        const int64_t lo = ptr[(size_t)r], n = ptr[(size_t)r + 1] - lo, parts = plan_row_tasks(n, split);
-        int64_t ordinal = 0;
-        for (int64_t k = 0; k < split; ++k) {
-          const int64_t b0 = lo + k * n / split, b1 = lo + (k + 1) * n / split;
-          if (b1 == b0 && !(n == 0 && k == 0)) continue;
-          const int64_t f[6] = {bh, r % sg.npq, b0, b1, ordinal++, parts};
-          std::memcpy(dst, f, sizeof f);
-          dst += 6;
-        }
-      }
+      std::memcpy(host_buf, rows.data(), *needed);
       return BSA_OK;
     }
     case BSA_EXPORT_DISPATCH: {
