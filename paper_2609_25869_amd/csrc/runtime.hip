@@ -56,11 +56,6 @@ size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
 // Task count above which the planner sorts a segment's tasks into KV order.
 constexpr int64_t kOrderMinTasks = 512;
 
-// Slices of rows that are too few to fill the chip (slice_rows below).
-constexpr int64_t kSliceTasks = 512;   // two workgroups on each of 256 CUs
-constexpr int64_t kSliceKeys = 448;    // active keys a slice should keep
-constexpr int64_t kSliceMost = 64;     // slices of one row
-
 // Length of the runs of consecutive tasks that the XCDs of one group take
 // turns over (see the plan's traversal order, CatalogEntry::xcd_group).
 constexpr int32_t kSlotRun = 8;
@@ -339,21 +334,28 @@ namespace {
 // inactive columns; the packed list leaves those out and is never longer in
 // keys than the tile list (plus one half tile).  Split-K plans cut rows by
 // tiles and keep the tile list.
-// Slices per physical row for the kernel.  A request of few rows leaves CUs
-// idle however long its rows are, and the plan's Split-K factor ends at 8, so
-// rows are cut further until the tasks fill the chip or a slice would hold
-// fewer than kSliceKeys active keys (the tile loop's start and the merge then
-// cost more than the slice saves).  The partial states merge as for Split-K;
-// the plan, its tasks and their exports stay what they are.  T_Q = 64, rows x
-// active keys: 104 x 10000 in 0.187 ms uncut, 0.078 in four slices (0.087 in
-// nine); 2 x 13000 in 0.236 and 0.024 ms (40 slices); 64 x 640 in 0.020 uncut
-// and 0.023 in four, 64 x 820 in 0.022 and 0.024 in two, which sets the line.
-int32_t slice_rows(const Segment& sg, int64_t logical_rows) {
-  const int32_t split = sg.plan.split;
-  if (sg.Rp * split * 2 > kSliceTasks || logical_rows == 0) return split;
-  const int64_t keys = sg.nnz * sg.bkv / logical_rows;  // per query-block row; a taller tile's union has more
-  const int64_t s = std::min({kSliceTasks / sg.Rp, keys / kSliceKeys, kSliceMost});
-  return (int32_t)std::max<int64_t>(split, s);
+bool runs_compacted(const Segment& sg) {
+  const CatalogEntry& e = sg.plan;
+  return sg.bkv == 16 && e.tkv == 32 && e.split == 1 && (e.waves == 2 || e.waves == 4) && e.tq == 32 * e.waves;
+}
+
+// Slices per physical row for the kernel (row_slices).
+int32_t slice_rows(const Segment& sg, int32_t seq_kv) {
+  const CatalogEntry& e = sg.plan;
+  SliceQuery z{};
+  z.tq = e.tq;
+  z.tkv = e.tkv;
+  z.split = e.split;
+  z.rows = sg.Rp;
+  z.masked = sg.gq * sg.gkv > 1;
+  z.kv_bytes = (int64_t)seq_kv * kHeadDim * 4;
+  // A tile is active when one of its members is: between the keys of one query
+  // block's row (members that agree, as the long runs of windows do) and those of
+  // independent members.  The packed list has no tiles along KV.
+  const double density = sg.blocks > 0 ? (double)sg.nnz / (double)sg.blocks : 0.0;
+  const int32_t members = sg.run_blocks * 3 > sg.nnz * 2 ? 1 : sg.gq * (runs_compacted(sg) ? 1 : sg.gkv);
+  z.keys = (double)seq_kv * 0.5 * (density + 1.0 - std::pow(1.0 - density, members));
+  return row_slices(z);
 }
 
 // Launch slots per kernel launch of a segment (generation_slots).
@@ -370,11 +372,6 @@ int64_t launch_slots(const Segment& sg, int64_t logical_rows, int32_t seq_kv) {
   z.run_blocks = sg.run_blocks;
   z.kv_bytes = (int64_t)seq_kv * kHeadDim * 4;
   return generation_slots(z);
-}
-
-bool runs_compacted(const Segment& sg) {
-  const CatalogEntry& e = sg.plan;
-  return sg.bkv == 16 && e.tkv == 32 && e.split == 1 && (e.waves == 2 || e.waves == 4) && e.tq == 32 * e.waves;
 }
 
 // Every logical mask row starts on a 4-byte boundary and spans whole words,
@@ -791,7 +788,7 @@ bsa_status bsa_plan(const bsa_mask* mask, const int32_t* B_Q, const int32_t* B_K
       return fail(BSA_ERR_UNSUPPORTED, "too many active tiles for 32-bit tile indices");
     sg.tasks_bound = e.split == 1 ? sg.Rp : std::min(sg.Rp * e.split, sg.Rp + sg.tiles_bound);
     if (sg.tasks_bound >= INT32_MAX) return fail(BSA_ERR_UNSUPPORTED, "too many tasks for one launch");
-    sg.slices = slice_rows(sg, (int64_t)B * (int64_t)sg.heads.size() * sg.nqb);
+    sg.slices = slice_rows(sg, s.seq_kv);
     sg.launch_slots = launch_slots(sg, (int64_t)B * (int64_t)sg.heads.size() * sg.nqb, s.seq_kv);
     sg.run_bound = sg.slices == e.split ? sg.tasks_bound : std::min(sg.Rp * sg.slices, sg.Rp + sg.tiles_bound);
     sg.balanced = sg.slices == 1 && (e.xcd_group == 2 || e.xcd_group == 4);

@@ -1,8 +1,8 @@
 // Which task each launch slot of the attention kernel runs, the shares of the
-// task list that the XCD groups take, how many slots a launch has, and the
-// merge's grid.  Plain integer code: the kernel
-// evaluates task_of_slot on the device (a constexpr function is callable from
-// device code), the planner and the host tests on the host.
+// task list that the XCD groups take, the slices of a row, how many slots a
+// launch has, and the merge's grid.  Plain code: the kernel evaluates
+// task_of_slot on the device (a constexpr function is callable from device
+// code), the planner and the host tests on the host.
 #pragma once
 
 #include <cstdint>
@@ -58,6 +58,61 @@ constexpr int64_t task_of_slot(int64_t slot, int64_t nt, int64_t group, int64_t 
 
 // Launch slots for equal shares: the task count rounded up to a multiple of 8.
 constexpr int64_t default_slots(int64_t nt) { return (nt + 7) / 8 * 8; }
+
+// Slices per physical row for the kernel.  A request of few rows leaves CUs
+// idle however long its rows are, and the plan's Split-K factor ends at 8, so
+// its rows are cut further where that is expected to pay.  The partial states
+// merge as for Split-K; the plan, its tasks and their exports stay what they
+// are.
+//
+// Expected time of a row's slices: the keys of one slice, at the rate of a
+// workgroup that has its SIMDs to itself (slower where tiles mask their
+// members), or where more workgroups run than that at the rate of the CU or the
+// L2 behind it; and the partial states' way through memory.  The rates are
+// fitted to 1550 measurements of 1 to 64 slices (seven kernels, 2 to 256 rows,
+// 0.2K to 130K keys a row, K/V of 2 to 64 MB a head).  Over them the slices
+// chosen take 1.05 times the time of the fastest number, one slice takes 2.9
+// times, and none of the chosen takes 3% more than one slice.  (A cut until 512
+// tasks run or a slice has 448 keys took 1.16 times, and up to 1.6 times one
+// slice: T = (256, 64), 160 rows of 1024 keys 38 us in one slice, 60 in three.)
+constexpr int64_t kSliceTasks = 512;  // tasks that cut rows may become
+constexpr int64_t kSliceKeys = 192;   // keys a slice keeps at least
+constexpr int32_t kSliceMost = 64;
+struct SliceQuery {
+  int32_t tq, tkv, split;
+  int64_t rows;     // physical rows
+  double keys;      // keys of a physical row
+  bool masked;      // tiles have several member blocks
+  int64_t kv_bytes; // K and V of one head
+};
+inline int32_t row_slices(const SliceQuery& z) {
+  if (z.rows < 1 || z.rows * z.split * 2 > kSliceTasks) return z.split;
+  const int i = z.tq <= 64 ? 0 : z.tq <= 128 ? 1 : 2;
+  // us per 1024 keys: alone (plus masking), and per workgroup on each of 256
+  // CUs (T_Q = 64 streams the most K/V per key: less from an XCD's own L2); us
+  // per task and merge
+  const double alone = (i == 0 ? (z.tkv >= 64 ? 14.0 : 17.0) : i == 1 ? 16.0 : 17.0) +
+                       (z.masked ? (i == 0 ? 2.5 : i == 1 ? 2.0 : 3.5) : 0.0);
+  const double shared = i == 0 ? (z.kv_bytes <= (4 << 20) ? 8.0 : 11.5) : i == 1 ? 14.0 : 26.0;
+  const double state = i == 0 ? 0.018 : i == 1 ? 0.03 : 0.06, merge = i == 2 ? 4.0 : 1.5;
+  auto time = [&](int32_t s) -> double {
+    const int64_t tasks = z.rows * s;
+    // whole rounds of CUs weigh more than the mean: the last round waits
+    const double load = 0.6 * (double)((tasks + 255) / 256) + 0.4 * (double)tasks / 256.0;
+    const double rate = alone > shared * load ? alone : shared * load;
+    return z.keys / s / 1024.0 * rate + (s > 1 ? merge + state * (double)tasks : 0.0);
+  };
+  int32_t best = z.split;
+  double best_time = time(z.split) - 1.0;  // (a microsecond has to be won)
+  for (int32_t s = z.split + 1; s <= kSliceMost && z.rows * s <= kSliceTasks && z.keys >= (double)kSliceKeys * s; ++s) {
+    const double t = time(s);
+    if (t < best_time) {
+      best = s;
+      best_time = t;
+    }
+  }
+  return best;
+}
 
 // Launch slots per kernel launch; 0: all tasks in one launch.  The tasks an
 // XCD runs at once read the same head's K/V in the same order, and share L2

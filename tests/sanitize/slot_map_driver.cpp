@@ -1,7 +1,7 @@
 // Host check of the attention kernel's slot map (slot_map.h): for equal
 // shares and for work-balanced shares, every task of [0, nt) has exactly one
-// launch slot and every other slot maps to -1; and of the rule for a launch
-// per generation and the merge's grid.  Exit status 0 and "ok N" when all
+// launch slot and every other slot maps to -1; and of the rules for slices and
+// for a launch per generation, and the merge's grid.  Exit status 0 and "ok N" when all
 // configurations pass; the first failure is printed and exits 1.
 #include <cstdint>
 #include <cstdio>
@@ -93,6 +93,45 @@ int main() {
         if (!covers_once(nt, bsa::shares_slots(lo, g, r), g, r, lo, "balanced shares")) return 1;
         ++checks;
       }
+    }
+  }
+  // slices: never fewer than the plan's or more tasks and shorter slices than
+  // allowed, none that was measured to lose, and enough where few rows are long
+  {
+    struct Known {
+      int32_t tq, tkv;
+      int64_t rows;
+      double keys;
+      int32_t lo, hi;
+    };
+    const Known known[] = {{256, 64, 160, 1024, 1, 1}, {256, 32, 192, 4096, 1, 1}, {256, 64, 224, 16384, 1, 1},
+                           {128, 64, 256, 1638, 1, 1}, {128, 32, 224, 1024, 1, 1}, {64, 64, 256, 1024, 1, 1},
+                           {64, 32, 224, 1024, 1, 1},  {64, 64, 104, 10000, 4, 4}, {64, 32, 2, 13000, 24, 64},
+                           {128, 64, 64, 8192, 4, 8},  {256, 64, 32, 8192, 4, 8}};
+    for (const Known& k : known) {
+      bsa::SliceQuery z{k.tq, k.tkv, 1, k.rows, k.keys, false, int64_t(32768) * 512};
+      const int32_t got = bsa::row_slices(z);
+      if (got < k.lo || got > k.hi) {
+        std::printf("FAIL slices: T (%d, %d), %lld rows of %.0f keys: %d\n", k.tq, k.tkv, (long long)k.rows, k.keys, got);
+        return 1;
+      }
+      ++checks;
+    }
+    for (int i = 0; i < 20000; ++i) {
+      bsa::SliceQuery z{};
+      z.tq = 64 << (rng() % 3);
+      z.tkv = 32 << (rng() % 2);
+      z.split = 1 << (rng() % 4);
+      z.rows = 1 + (int64_t)(rng() % 600);
+      z.keys = (double)(rng() % 200000);
+      z.masked = rng() % 2;
+      z.kv_bytes = (int64_t)(rng() % 200000) * 512;
+      const int32_t got = bsa::row_slices(z);
+      if (got < z.split || got > 64 || (got > z.split && (z.rows * got > 512 || z.keys < 192.0 * got))) {
+        std::printf("FAIL slices: %d of %lld rows\n", got, (long long)z.rows);
+        return 1;
+      }
+      ++checks;
     }
   }
   // a launch per generation: rows of no, one, few and enough keys
