@@ -121,8 +121,9 @@ __device__ inline float other_half(float x, int lane) {
 // operands pin each result to the register it came from; written as plain
 // C++ the compiler gives the updated values new registers and then copies
 // the whole accumulator on the common path where the update did not run.
-// With G = 2 the accumulators live in AGPRs, which VALU instructions cannot
-// address, and the multiply is left to the compiler.
+// With G = 2 the state does not fit the 256 VGPRs and part of it lives in
+// AGPRs, which VALU instructions cannot address: there the multiply is left to
+// the compiler.
 template <bool kInVgpr>
 __device__ inline void scale_inplace(f32x16& v, float alpha) {
   if constexpr (kInVgpr) {
@@ -183,7 +184,6 @@ __device__ inline void block_sync() {
 // workgroups with 64 KB rings, of which only two share a CU.
 template <int NWAVES, int G, int TKV, int STAGES>
 constexpr int waves_per_simd() { return (G == 1 && (NWAVES > 2 || TKV * STAGES <= 64)) ? 2 : 1; }
-
 
 // UNIT is the number of tokens of one tile-list entry: TKV, or 16 for
 // compacted lists, whose iterations pack the next TKV / 16 active 16-token
@@ -301,8 +301,8 @@ void attn_fwd_kernel(AttnArgs a) {
   const char* vbase = reinterpret_cast<const char*>(a.v + b * a.vs0 + h * a.vs1);
   const int64_t kstride = a.ks2 * 2, vstride = a.vs2 * 2;  // bytes per token
   // The swizzle depends on the row modulo 16, which repeats every kRep loads
-  // of a wave; later loads reuse those lane offsets and add whole rows
-  // through the scalar offset (which the descriptor's range check includes).
+  // of a wave; later loads reuse those lane offsets and add whole rows to
+  // them.
   constexpr int kRep = NWAVES % 4 == 0 ? 1 : 4 / (NWAVES % 4 == 2 ? 2 : 1);
   constexpr int kRepN = kRep < kLoadsPerWave ? kRep : kLoadsPerWave;
   uint32_t koffs[kRepN], voffs[kRepN];
@@ -532,7 +532,7 @@ void attn_fwd_kernel(AttnArgs a) {
   constexpr int kNS = kNU * G;            // MFMA slots of one iteration
   // elements whose exponential is formed by the end of slot ss
   auto a_end = [&](int ss) -> int { return ss < 0 ? 0 : ss < kNS - 1 ? (ss + 1) * kEAll / (kNS - 1) : kEAll; };
-    constexpr int kAhead = 3;  // operand read distance, in units
+  constexpr int kAhead = 3;  // operand read distance, in units
   // Rings of four or more slots: the barrier at the end of iteration t makes
   // slot t+3 visible, one iteration before it is needed, so the first operands
   // of iteration t+1 are read during the last units of iteration t and the
@@ -572,7 +572,6 @@ void attn_fwd_kernel(AttnArgs a) {
   auto iteration = [&](f32x16* s_cur, f32x16* s_nxt, const Kv0& kv0_cur, const Bits& bits_cur, const uint8_t* ks_next,
                        const uint8_t* vs_prev, const uint8_t* ks_after, u32x4* pw_cur, const u32x4* pw_prev, const Kv0& kv0_refill_k,
                        const Kv0& kv0_refill_v, uint8_t* k_refill, uint8_t* v_refill, bool* active, float* lsum) {
-    // the ring refill of this iteration goes out one load every kDmaEvery units
     float nm[G][kSub];  // exponent addend of each key group
 #pragma unroll
     for (int g = 0; g < G; ++g) {

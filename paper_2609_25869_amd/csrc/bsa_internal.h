@@ -9,6 +9,14 @@ namespace bsa {
 
 constexpr int kHeadDim = 128;
 
+// SplitMix64 finaliser (Steele, Lea and Flood, "Fast splittable pseudorandom
+// number generators", OOPSLA 2014).
+__device__ inline uint64_t mix64(uint64_t z) {
+  z = (z ^ (z >> 30)) * 0xbf58476d1ce4e5b9ull;
+  z = (z ^ (z >> 27)) * 0x94d049bb133111ebull;
+  return z ^ (z >> 31);
+}
+
 // One workgroup task (Section 4.3): a contiguous slice [tile_begin, tile_end)
 // of the active KV tiles of physical query tile `pq` of head `bh`
 // (= b * heads + h).  `split` is the slice's ordinal among the row's `nsplit`
@@ -149,7 +157,6 @@ struct AttnArgs {
   float* ws;                   // Split-K partial states (may be null when no row splits)
   const int64_t* row_task;     // Split-K: first task of each physical row (may be null otherwise)
   int64_t nrows;               // physical rows
-  const uint16_t* zero_page;   // 256 zero bytes, read for K/V rows past the sequence end
   int64_t qs0, qs1, qs2, ks0, ks1, ks2, vs0, vs1, vs2, os0, os1, os2;
   int32_t H, Nq, Nkv;
   int32_t bq_shift, bkv_shift;  // log2 of the logical block sizes

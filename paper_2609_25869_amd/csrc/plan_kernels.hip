@@ -28,13 +28,6 @@ __device__ inline int find_bh(const int64_t* row_base, int nbh, int64_t r) {
 // hash, which can only cost locality in the dispatch order.  A list is in
 // column order, so the sum of its entries' hashes stands for it.
 struct RowHash {
-  // SplitMix64 finaliser (Steele, Lea and Flood, "Fast splittable
-  // pseudorandom number generators", OOPSLA 2014)
-  __device__ static uint64_t mix64(uint64_t z) {
-    z = (z ^ (z >> 30)) * 0xbf58476d1ce4e5b9ull;
-    z = (z ^ (z >> 27)) * 0x94d049bb133111ebull;
-    return z ^ (z >> 31);
-  }
   uint64_t h = 0;
   __device__ void add(int column, uint64_t members) {
     h += mix64(members + 0x9e3779b97f4a7c15ull * (uint64_t)(column + 1));
@@ -210,9 +203,10 @@ __global__ __launch_bounds__(kStatThreads) void row_stats_kernel(MaskStateArgs a
 // Exclusive scan int32 -> int64 with the total in out[n].  These scans are
 // bound by launches and latency, not by their bytes: up to kScanOneBlock
 // elements (8 per thread) one workgroup does it all in 3 to 8 us (21600
-// elements would take it 24 us, the two launches below 10), beyond that per-block sums and per-block rescans, where every
-// block adds up the sums before its own; above kScanSelfSum blocks a scan of
-// the sums comes in between.
+// elements would take it 24 us, the two launches below 10), beyond that
+// per-block sums and per-block rescans, where every block adds up the sums
+// before its own; above kScanSelfSum blocks a scan of the sums comes in
+// between.
 constexpr int kScanThreads = 256;
 constexpr int kScanItems = 8;
 constexpr int kScanTile = kScanThreads * kScanItems;

@@ -217,8 +217,6 @@ struct bsa_plan_s {
   std::vector<void*> allocs;
   hipEvent_t ready = nullptr, done = nullptr;
   // device
-  uint16_t* zero_page = nullptr;
-
   HeadDesc* heads_dev = nullptr;
   int64_t* row_base_dev = nullptr;
   int32_t* seg_heads_dev = nullptr;
@@ -690,8 +688,7 @@ bsa_status bsa_plan(const bsa_mask* mask, const int32_t* B_Q, const int32_t* B_K
     }
 
   // ---- device buffer before the statistics synchronisation
-  const size_t o_zero = 0;
-  const size_t o_heads = align256(o_zero + 256);
+  const size_t o_heads = 0;
   const size_t o_rbase = align256(o_heads + sizeof(HeadDesc) * H);
   const size_t o_sheads = align256(o_rbase + sizeof(int64_t) * p->row_base.size());
   const size_t o_stats = align256(o_sheads + sizeof(int32_t) * seg_heads.size());
@@ -707,7 +704,6 @@ bsa_status bsa_plan(const bsa_mask* mask, const int32_t* B_Q, const int32_t* B_K
   void* pre = nullptr;
   if ((st = p->alloc(&pre, pre_bytes)) != BSA_OK) return st;
   uint8_t* pre8 = static_cast<uint8_t*>(pre);
-  p->zero_page = reinterpret_cast<uint16_t*>(pre8 + o_zero);
   p->heads_dev = reinterpret_cast<HeadDesc*>(pre8 + o_heads);
   p->row_base_dev = reinterpret_cast<int64_t*>(pre8 + o_rbase);
   p->seg_heads_dev = reinterpret_cast<int32_t*>(pre8 + o_sheads);
@@ -1025,7 +1021,6 @@ bsa_status bsa_forward(bsa_plan_t plan, const void* q, const void* k, const void
     a.ws = sg.ws;
     a.row_task = sg.task_ptr;
     a.nrows = sg.Rp;
-    a.zero_page = plan->zero_page;
     a.qs0 = s.q_stride[0]; a.qs1 = s.q_stride[1]; a.qs2 = s.q_stride[2];
     a.ks0 = s.k_stride[0]; a.ks1 = s.k_stride[1]; a.ks2 = s.k_stride[2];
     a.vs0 = s.v_stride[0]; a.vs1 = s.v_stride[1]; a.vs2 = s.v_stride[2];
@@ -1309,7 +1304,7 @@ int64_t sparsify_heads_per_pass(int64_t nbh, int64_t room, int64_t per, int64_t 
 // kernel (in host code it names a host-side stand-in); it uses the device
 // address that hipGetSymbolAddress returns for the current device.
 constexpr int64_t kNoAllocScratchBytes = int64_t(64) << 20;
-static __device__ __attribute__((aligned(256))) uint8_t scratch[kNoAllocScratchBytes + 4096];
+static __device__ __attribute__((aligned(256))) uint8_t scratch[kNoAllocScratchBytes];
 
 constexpr int kMaxDevices = 64;
 std::mutex g_scratch_mu;
@@ -1361,9 +1356,9 @@ bsa_status bsa_sparsify_topk_noalloc(const void* q, const void* k, const bsa_sha
   int64_t nqb = 0, nkb = 0;
   bsa_status st = sparsify_validate(q, k, shapes, bq, bkv, mask, &nqb, &nkb);
   if (st != BSA_OK) return st;
-  // the documented limit counts eight bytes a score; what is used is less
-  // (rows rounded up to four and the norms take at most 73 KB more than four
-  // bytes a score, and a head of fewer than four rows at most 7 MB in all)
+  // the documented limit counts eight bytes a score; what is used is less: four
+  // bytes a score with rows rounded up to whole fours, and the key norms (a head
+  // of fewer than four rows takes at most 7 MB in all)
   const int64_t per_head = (nqb + nkb) * kHeadDim * (int64_t)sizeof(double) + nqb * nkb * (int64_t)sizeof(double);
   if (per_head > kNoAllocScratchBytes)
     return fail(BSA_ERR_INVALID, "one head needs " + std::to_string(per_head) +
@@ -1374,8 +1369,7 @@ bsa_status bsa_sparsify_topk_noalloc(const void* q, const void* k, const bsa_sha
   HIP_TRY(hipGetDevice(&dev));
   void* work = nullptr;
   if ((st = scratch_address(dev, &work)) != BSA_OK) return st;
-  const int64_t slack = sparsify_score_rows(1) * nkb * (int64_t)sizeof(float);  // rows rounded up
-  const int64_t chunk = sparsify_heads_per_pass((int64_t)s.batch * s.heads, kNoAllocScratchBytes - slack,
+  const int64_t chunk = sparsify_heads_per_pass((int64_t)s.batch * s.heads, kNoAllocScratchBytes,
                                                 sparsify_bytes(1, nqb, nkb), nqb, nkb);
   // every byte of the scratch that a pass reads is written earlier in the
   // same pass (means before scores, scores before the selection), so nothing

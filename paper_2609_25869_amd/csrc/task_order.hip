@@ -23,14 +23,6 @@ namespace bsa {
 
 namespace {
 
-// SplitMix64 finaliser (Steele, Lea and Flood, "Fast splittable
-// pseudorandom number generators", OOPSLA 2014).
-__device__ inline uint64_t mix64(uint64_t z) {
-  z = (z ^ (z >> 30)) * 0xbf58476d1ce4e5b9ull;
-  z = (z ^ (z >> 27)) * 0x94d049bb133111ebull;
-  return z ^ (z >> 31);
-}
-
 constexpr int kWavesPerBlock = 4;
 
 // Hash of task t's (bh, tile count, tile list, member bits), one wave per
