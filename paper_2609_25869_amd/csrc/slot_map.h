@@ -124,7 +124,12 @@ inline int32_t row_slices(const SliceQuery& z) {
 //   other conditions a mean of 0.83 of the time at 115200 tokens (none of 258
 //   slower by 3%), 0.89 at 65536 (none of 174), 0.98 at 32768 (33 of 162);
 // - where the rows are about equally long (with the longest above 1.4 times
-//   the mean the wait costs more: 0.89 within, 1.0 above);
+//   the mean the wait costs more: 0.89 within, 1.0 above), and of up to about
+//   two generations with a block's rows to a task nearly equal, since the wait
+//   is then for half of the tasks: 65536 tokens, 2 heads, 15% and 40%
+//   Bernoulli of (64, 64) blocks 0.92 -> 0.96 and 2.25 -> 2.39 ms (longest
+//   rows 1.26 and 1.13 times the mean), top-k 0.64 -> 0.65 and, in two slots,
+//   0.79 -> 0.68; at 2304 tasks 0.93 to 1.01, at 3072 0.90 to 0.98;
 // - where they are scattered: the long runs of windows share lines between
 //   neighbours anyway (5% window of 131072 tokens 4.20 and 4.59 ms);
 // - where a query block is at most one task's rows: the tasks of a larger
@@ -141,6 +146,7 @@ inline int32_t row_slices(const SliceQuery& z) {
 constexpr int64_t kGenerationSlots = 1024;      // four 2-wave workgroups on each of 256 CUs
 constexpr int64_t kGenerationKvBytes = 32 << 20;
 constexpr int64_t kGenerationKeys = 2048;
+constexpr int64_t kGenerationTasksUneven = 2304;  // tasks from which rows may be uneven
 struct GenerationQuery {
   int32_t tq, bq, bkv, slices;
   int64_t tasks, logical_rows, nnz, max_row_nnz, run_blocks;
@@ -150,6 +156,7 @@ constexpr int64_t generation_slots(const GenerationQuery& z) {
   if (z.tq != 64 || z.bq > 64 || z.slices != 1 || z.tasks < 2 * kGenerationSlots) return 0;
   if (z.kv_bytes < kGenerationKvBytes) return 0;
   if (z.max_row_nnz * z.logical_rows * 5 > z.nnz * 7 || z.run_blocks * 3 > z.nnz * 2) return 0;
+  if (z.bq == z.tq && z.tasks < kGenerationTasksUneven && z.max_row_nnz * z.logical_rows * 10 > z.nnz * 11) return 0;
   // a task's keys are at most the keys of its query blocks' rows together,
   // and close to them where few blocks are active
   if (z.nnz * z.bkv / z.logical_rows * (z.tq / z.bq) < kGenerationKeys) return 0;

@@ -159,6 +159,31 @@ int main() {
         ++checks;
       }
   }
+  // about two generations: only where a task's rows are nearly equal, or
+  // several query blocks make up a task; from 2304 tasks on up to 1.4 times the mean
+  {
+    bsa::GenerationQuery z{};
+    z.tq = 64;
+    z.bkv = 64;
+    z.slices = 1;
+    z.kv_bytes = int64_t(65536) * 512;
+    for (int32_t bq : {64, 32})
+      for (int64_t tasks : {2047, 2048, 2303, 2304, 4096})
+        for (int64_t longest : {100, 110, 111, 140, 141}) {
+          z.bq = bq;
+          z.tasks = tasks;
+          z.logical_rows = tasks * (64 / bq);
+          z.nnz = 100 * z.logical_rows;
+          z.max_row_nnz = longest;
+          const bool want = tasks >= 2048 && longest <= (bq == 64 && tasks < 2304 ? 110 : 140);
+          if (bsa::generation_slots(z) != (want ? 1024 : 0)) {
+            std::printf("FAIL generations: %lld tasks of %d, longest row %lld%%\n", (long long)tasks, bq,
+                        (long long)longest);
+            return 1;
+          }
+          ++checks;
+        }
+  }
   // the merge's grid: 8 query rows per workgroup, and launchable (fewer than
   // 2^32 threads a dimension) for every row count whose tasks are
   for (int64_t tq : {64, 128, 256})
