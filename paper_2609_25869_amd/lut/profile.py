@@ -25,6 +25,7 @@ Corpus (the paper's profiling masks are not available; these stand in):
   wide, mixture, large and cross splits widen this grid (see their constants).
 
     python -m paper_2609_25869_amd.lut.profile --out PATH [--split profile|eval] [--budget SECONDS]
+    python -m paper_2609_25869_amd.lut.profile --out PATH --split fill --fill 2
 
 Plans added to the catalog later (or whose launch changed) are timed into
 existing records and then put on each split's original clock:
@@ -47,7 +48,7 @@ BATCH_HEADS = [4, 24]
 FAMILIES = [("window", 0.05), ("window", 0.15), ("bernoulli", 0.03), ("bernoulli", 0.10), ("bernoulli", 0.30),
             ("topk", 0.12)]
 SPLIT_SEED = {"profile": 0, "eval": 1, "wide": 2, "wide_eval": 3, "mixture": 4, "mixture_eval": 5, "large": 6,
-              "large_eval": 7, "grid2": 8, "cross": 9, "cross_eval": 10}
+              "large_eval": 7, "grid2": 8, "cross": 9, "cross_eval": 10, "fill": 11}
 FRAMES = 16
 
 # The wide splits draw, per request key, random combinations of a larger
@@ -57,7 +58,11 @@ WIDE_BH = [1, 2, 4, 8, 24]
 WIDE_SOURCES = [("window", 0.03), ("window", 0.08), ("window", 0.15), ("window", 0.30),
                 ("bernoulli", 0.02), ("bernoulli", 0.05), ("bernoulli", 0.10), ("bernoulli", 0.20),
                 ("bernoulli", 0.40), ("topk", 0.06), ("topk", 0.12), ("topk", 0.25)]
-WIDE_PER_KEY = {"wide": 96, "wide_eval": 48}
+WIDE_PER_KEY = {"wide": 96, "wide_eval": 48, "fill": 640}
+
+# The fill split: further draws of the wide grid, of which --fill N profiles
+# those whose cell of the plan table has fewer than N training cases (a request
+# in a cell without any runs its key's base plan).
 
 # The mixture splits: requests whose heads draw their masks from different
 # families (window 40%, top-k 40%, Bernoulli 20%) at densities from
@@ -444,6 +449,8 @@ def main():
     ap.add_argument("--split", default="profile", choices=sorted(SPLIT_SEED))
     ap.add_argument("--budget", type=float, default=600.0, help="stop starting new cases after this many seconds")
     ap.add_argument("--only", default="", help="comma-separated geometries 'bq:bkv' to profile")
+    ap.add_argument("--fill", type=int, default=0,
+                    help="profile only cases whose cell of the plan table has fewer training cases than this")
     ap.add_argument("--refeature", action="store_true",
                     help="only add the max_row_nnz statistic to the existing records in --out (no timing)")
     ap.add_argument("--add-plans", default="",
@@ -474,6 +481,13 @@ def main():
         keep = {tuple(int(x) for x in s.split(":")) for s in args.only.split(",")}
         cases = [c for c in cases if tuple(c["geometry"]) in keep]
     log("%d cases to profile (%d already in %s)" % (len(cases), len(done), args.out))
+    filled = {}
+    if args.fill:
+        from . import compile as table
+        others = [p for p in table.PROFILES if os.path.basename(p) != os.path.basename(args.out) and os.path.exists(p)]
+        for r in table.load_records(others + ([args.out] if os.path.exists(args.out) else [])):
+            cell = (tuple(r["key"]), table.bucket(r["features"], table.SCHEMA))
+            filled[cell] = filled.get(cell, 0) + 1
     t0 = time.time()
     with open(args.out, "a") as f:
         for i, c in enumerate(cases):
@@ -481,6 +495,15 @@ def main():
                 log("budget reached after %d cases" % i)
                 break
             tc = time.time()
+            if args.fill:
+                key = [*c["geometry"], 0, 128]
+                feats = table.with_query_rows({"key": key, "features": case_features(torch, bsa, c)})["features"]
+                cell = (tuple(key), table.bucket(feats, table.SCHEMA))
+                if i % 100 == 0:
+                    log("case %d of %d" % (i, len(cases)))
+                if filled.get(cell, 0) >= args.fill:
+                    continue
+                filled[cell] = filled.get(cell, 0) + 1
             rec = profile_case(torch, bsa, c)
             f.write(json.dumps(rec) + "\n")
             f.flush()
