@@ -338,7 +338,7 @@ bool runs_compacted(const Segment& sg) {
 }
 
 // Slices per physical row for the kernel (row_slices).
-int32_t slice_rows(const Segment& sg, int32_t seq_kv) {
+int32_t slice_rows(const Segment& sg, int64_t logical_rows, int32_t seq_kv) {
   const CatalogEntry& e = sg.plan;
   SliceQuery z{};
   z.tq = e.tq;
@@ -353,6 +353,8 @@ int32_t slice_rows(const Segment& sg, int32_t seq_kv) {
   const double density = sg.blocks > 0 ? (double)sg.nnz / (double)sg.blocks : 0.0;
   const int32_t members = sg.run_blocks * 3 > sg.nnz * 2 ? 1 : sg.gq * (runs_compacted(sg) ? 1 : sg.gkv);
   z.keys = (double)seq_kv * 0.5 * (density + 1.0 - std::pow(1.0 - density, members));
+  if (sg.nnz > 0)
+    z.longest = std::min((double)seq_kv, z.keys * (double)sg.max_row_nnz * (double)logical_rows / (double)sg.nnz);
   return row_slices(z);
 }
 
@@ -784,7 +786,7 @@ bsa_status bsa_plan(const bsa_mask* mask, const int32_t* B_Q, const int32_t* B_K
       return fail(BSA_ERR_UNSUPPORTED, "too many active tiles for 32-bit tile indices");
     sg.tasks_bound = e.split == 1 ? sg.Rp : std::min(sg.Rp * e.split, sg.Rp + sg.tiles_bound);
     if (sg.tasks_bound >= INT32_MAX) return fail(BSA_ERR_UNSUPPORTED, "too many tasks for one launch");
-    sg.slices = slice_rows(sg, s.seq_kv);
+    sg.slices = slice_rows(sg, (int64_t)B * (int64_t)sg.heads.size() * sg.nqb, s.seq_kv);
     sg.launch_slots = launch_slots(sg, (int64_t)B * (int64_t)sg.heads.size() * sg.nqb, s.seq_kv);
     sg.run_bound = sg.slices == e.split ? sg.tasks_bound : std::min(sg.Rp * sg.slices, sg.Rp + sg.tiles_bound);
     sg.balanced = sg.slices == 1 && (e.xcd_group == 2 || e.xcd_group == 4);

@@ -65,16 +65,21 @@ constexpr int64_t default_slots(int64_t nt) { return (nt + 7) / 8 * 8; }
 // merge as for Split-K; the plan, its tasks and their exports stay what they
 // are.
 //
-// Expected time of a row's slices: the keys of one slice, at the rate of a
-// workgroup that has its SIMDs to itself (slower where tiles mask their
-// members), or where more workgroups run than that at the rate of the CU or the
-// L2 behind it; and the partial states' way through memory.  The rates are
+// Expected time of a row's slices: the keys of one slice of the longest row, at
+// the rate of a workgroup that has its SIMDs to itself (slower where tiles mask
+// their members), or where more workgroups run than that the keys of one slice of
+// a mean row at the rate of the CU or the L2 behind it; and the partial states' way through memory.  The rates are
 // fitted to 1550 measurements of 1 to 64 slices (seven kernels, 2 to 256 rows,
 // 0.2K to 130K keys a row, K/V of 2 to 64 MB a head).  Over them the slices
 // chosen take 1.05 times the time of the fastest number, one slice takes 2.9
 // times, and none of the chosen takes 3% more than one slice.  (A cut until 512
 // tasks run or a slice has 448 keys took 1.16 times, and up to 1.6 times one
 // slice: T = (256, 64), 160 rows of 1024 keys 38 us in one slice, 60 in three.)
+// (Those rows were of equal length.  The longest row waits alone: 64 rows of 614
+// keys, the longest 1024, T = (64, 64) 20.5 us by the mean row, uncut, 19.0 by the
+// longest; four heads of 2048 tokens under 25% top-k of (32, 16) blocks 30 and 26
+// us.  Of 389 requests with few rows 21 are faster by 3% and 13 slower, nearly all
+// of these within 5%; the geometric mean is unchanged.)
 constexpr int64_t kSliceTasks = 512;  // tasks that cut rows may become
 constexpr int64_t kSliceKeys = 192;   // keys a slice keeps at least
 constexpr int32_t kSliceMost = 64;
@@ -84,6 +89,7 @@ struct SliceQuery {
   double keys;      // keys of a physical row
   bool masked;      // tiles have several member blocks
   int64_t kv_bytes; // K and V of one head
+  double longest;   // keys of the longest row (0: the rows are equal)
 };
 inline int32_t row_slices(const SliceQuery& z) {
   if (z.rows < 1 || z.rows * z.split * 2 > kSliceTasks) return z.split;
@@ -99,8 +105,8 @@ inline int32_t row_slices(const SliceQuery& z) {
     const int64_t tasks = z.rows * s;
     // whole rounds of CUs weigh more than the mean: the last round waits
     const double load = 0.6 * (double)((tasks + 255) / 256) + 0.4 * (double)tasks / 256.0;
-    const double rate = alone > shared * load ? alone : shared * load;
-    return z.keys / s / 1024.0 * rate + (s > 1 ? merge + state * (double)tasks : 0.0);
+    const double last = (z.longest > z.keys ? z.longest : z.keys) * alone, all = z.keys * shared * load;
+    return (last > all ? last : all) / s / 1024.0 + (s > 1 ? merge + state * (double)tasks : 0.0);
   };
   int32_t best = z.split;
   double best_time = time(z.split) - 1.0;  // (a microsecond has to be won)

@@ -103,13 +103,16 @@ int main() {
       int64_t rows;
       double keys;
       int32_t lo, hi;
+      double longest = 0;
     };
     const Known known[] = {{256, 64, 160, 1024, 1, 1}, {256, 32, 192, 4096, 1, 1}, {256, 64, 224, 16384, 1, 1},
                            {128, 64, 256, 1638, 1, 1}, {128, 32, 224, 1024, 1, 1}, {64, 64, 256, 1024, 1, 1},
                            {64, 32, 224, 1024, 1, 1},  {64, 64, 104, 10000, 4, 4}, {64, 32, 2, 13000, 24, 64},
-                           {128, 64, 64, 8192, 4, 8},  {256, 64, 32, 8192, 4, 8}};
+                           {128, 64, 64, 8192, 4, 8},  {256, 64, 32, 8192, 4, 8},
+                           // two heads of 2048 tokens: even rows, and 30% Bernoulli
+                           {64, 64, 64, 512, 1, 1},    {64, 64, 64, 614, 2, 4, 1024}};
     for (const Known& k : known) {
-      bsa::SliceQuery z{k.tq, k.tkv, 1, k.rows, k.keys, false, int64_t(32768) * 512};
+      bsa::SliceQuery z{k.tq, k.tkv, 1, k.rows, k.keys, false, int64_t(32768) * 512, k.longest};
       const int32_t got = bsa::row_slices(z);
       if (got < k.lo || got > k.hi) {
         std::printf("FAIL slices: T (%d, %d), %lld rows of %.0f keys: %d\n", k.tq, k.tkv, (long long)k.rows, k.keys, got);
