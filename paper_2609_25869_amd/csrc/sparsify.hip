@@ -20,16 +20,17 @@
 // arithmetic.
 //
 // Kernels, at 115200 tokens, 24 heads, (64, 64) blocks, k = 216 of 1800 in
-// parentheses (fp64 scores of every pair on the vector units and a radix
-// select of 64-bit keys per workgroup took 335 + 1109 + 481 us):
-//   block_mean_kernel    (312 us, 4.5 TB/s) HBM-bound: the tensors once, 16
+// parentheses, in a trace of whole requests (fp64 scores of every pair on the
+// vector units and a radix select of 64-bit keys per workgroup took 335 + 1109 +
+// 481 us on another run; the calls alone, repeated, 1.91 and 0.82 ms):
+//   block_mean_kernel    (354 us, 4.0 TB/s) HBM-bound: the tensors once, 16
 //                        bytes per lane and row where the layout allows
-//   block_score_kernel   (288 us, 69 TFLOP/s) fp32 matrix instructions on the
+//   block_score_kernel   (313 us, 64 TFLOP/s) fp32 matrix instructions on the
 //                        means rounded to fp32, 128 x 64 or 64 x 64 score
 //                        tiles; the means are converted on the way into LDS.
 //                        128 x 128 tiles need 256 registers: 474 us with two
 //                        waves a SIMD forced, 355 with one
-//   topk_select_kernel   (232 us) one wave per score row with the row's keys
+//   topk_select_kernel   (235 us) one wave per score row with the row's keys
 //                        in registers, counted against a threshold that
 //                        interpolation and bisection move (VALU-bound; no
 //                        LDS, no barrier).  Rows that fp32 leaves undecided
